@@ -565,9 +565,7 @@ def main():
     # secondary figures for the other two hot kernels
     if prof["factor"][1] > 0:
         kern["factor"]["tflops"] = round(n_lu * lu_flop / (prof["factor"][1] * 1e-3) / 1e12, 3)
-    # Newton iterations run on two streams (cells that factor on the solver's
-    # stream, the others beside the factorisation), so per-kernel bandwidths of
-    # the Newton kernels come from the rocprofv3 summary, not from these spans.
+    # the phases' times are means over the workgroups of the persistent launches
 
     out = {
         "metric": ("cell-solves/sec to t_end at rtol 1e-6, 500-sp net; p50/p99 latency; FP32-LU vs FP64"

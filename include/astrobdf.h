@@ -101,7 +101,9 @@ typedef struct abdf_options {
     double atol;               /* absolute tolerance in x units, >= 0 (default 1e-20) */
     int32_t max_steps;         /* step attempts per cell (default 100000) */
     int32_t precision;         /* ABDF_PREC_* (default FP64) */
-    int32_t check_every;       /* step attempts between host polls of the running count (default 8) */
+    int32_t check_every;       /* server: how long its cells run between looks at the queue, in
+                                * units of about 4 ms (default 8; a server's 4).  Batch calls
+                                * poll as their cells need it. */
     int32_t max_order;         /* highest BDF order the order selection may reach, 1..5;
                                 * 0 = 5 (default 5).  1 is the implicit Euler method
                                 * with the same error control. */
@@ -213,7 +215,7 @@ abdf_status abdf_solve(const abdf_network *net, int64_t n_cells,
  * process ends) and static host buffers; it holds as many slots as fit there
  * (e.g. 24 cells of the 500-species network, ~100 of the 200-species one, at
  * most 4096), bounded further by opt->hbm_budget_bytes, and admits further
- * cells as slots free up.  Attempts run on `stream` alone.
+ * cells as slots free up.
  * Requirements and limits:
  *  - the network's device tables must already be on the current device (any
  *    other solving call with this network on this device uploads them);
@@ -455,9 +457,12 @@ abdf_status abdf_lu_solve(int32_t n, int64_t batch, const double *LU, const int3
                           double *b, void *stream);
 
 /* ------------------------------------------------------------- profiling --
- * Process-wide kernel timers: while enabled, the solver brackets each of its
- * kernel launches with HIP events on the launch stream and accumulates the
- * durations per kernel family when it next synchronises.
+ * Process-wide timers: while enabled, admissions, harvests and the standalone
+ * kernels are timed by HIP events, and the phases inside the persistent
+ * integration (factor, newton, rhs, control) and reverse sweep (factor,
+ * adj_solve, adj_step) by the device's clock: their time is the mean over a
+ * launch's workgroups, one launch counted for each phase it ran.  Accumulated
+ * per family when the solver next synchronises.
  */
 enum {
     ABDF_PROF_ADMIT = 0,    /* admission: rates, starting step, first attempt */
@@ -468,18 +473,15 @@ enum {
     ABDF_PROF_RHS = 5,      /* Newton residual: rates times abundances, species sums */
     ABDF_PROF_ADJ_SOLVE = 6,  /* reverse sweep: transposed triangular solves */
     ABDF_PROF_ADJ_STEP = 7,   /* reverse sweep: adjoint step update and parameter gradient */
-    /* Newton residual and correction of the cells that keep their factorisation,
-     * launched on a second stream beside the factorisation kernel; their event
-     * spans include the time spent waiting for compute units it holds. */
-    ABDF_PROF_RHS_SIDE = 8,
-    ABDF_PROF_NEWTON_SIDE = 9,
+    ABDF_PROF_RHS_SIDE = 8,     /* unused (always zero) */
+    ABDF_PROF_NEWTON_SIDE = 9,  /* unused (always zero) */
     ABDF_PROF_RHS_EVAL = 10,  /* abdf_rhs: the right-hand-side kernel on its own */
     ABDF_PROF_KINDS = 11
 };
 
 typedef struct abdf_profile {
     int64_t launches[11];   /* kernel launches per family */
-    double ms[11];          /* summed launch durations [ms] per family */
+    double ms[11];          /* summed durations [ms] per family */
 } abdf_profile;
 
 /* Turns the timers on (nonzero) or off. */

@@ -157,7 +157,7 @@ int Tape::windowed_sweep(const AdjIO &io, hipStream_t st, std::string &err) {
     bool over = false;
     for (size_t c = 0; c < C; ++c) over |= status[c] == ABDF_CELL_OK && len[c] > cap_;
     Slots &s = eng_->slots();
-    if (!over) return eng_->reverse(io, opt_.check_every, st, err);
+    if (!over) return eng_->reverse(io, st, err);
 
     auto al = [](size_t b) { return (b + 255) / 256 * 256; };
     const size_t b_i = al(C * 4), b_lam = al(C * kDRows * S * 8), b_g = al(C * R * 8), b_x = al(C * S * 8);
@@ -229,7 +229,7 @@ int Tape::windowed_sweep(const AdjIO &io, hipStream_t st, std::string &err) {
         s.win_lam = d_lam;
         s.win_g = d_g;
         s.win_resume = pass > 0;
-        rc = eng_->reverse(io, opt_.check_every, st, err);
+        rc = eng_->reverse(io, st, err);
         if (rc != ABDF_OK) break;
         for (size_t c = 0; c < C; ++c)
             if (end[c] >= 0) w1[c] = w0[c] > 0 ? w0[c] : -1;

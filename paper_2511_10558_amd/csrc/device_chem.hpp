@@ -12,10 +12,11 @@ namespace abdf {
 // alpha (T/300)^beta E zeta / (1 - omega), E the reaction's efficiency kept in
 // its gamma field, omega the network's dust albedo); two-body coefficients carry the factor n_H of the
 // fractional-abundance state.  Written to global memory, coalesced over r.
+template <int NT = kBlock>
 __device__ inline void cell_rates(const DeviceNet &n, const double *phi, double *k) {
     const double T = phi[0], nH = phi[1], Av = phi[2], zeta = phi[3], G0 = phi[4];
     const double T300 = T / 300.0;
-    for (int r = threadIdx.x; r < n.R; r += kBlock) {
+    for (int r = threadIdx.x; r < n.R; r += NT) {
         const int t = n.rx_type[r];
         const double a = n.alpha[r];
         double v;
@@ -103,27 +104,28 @@ __device__ __forceinline__ void cell_rhs(const DeviceNet &n, const double *__res
 // k_r (y_a x_b + x_a y_b) (k_r y_a for one reactant; the same expression gives
 // 2 k_r x_a y_a for A + A), then the species sums of cell_rhs.  x, y in LDS;
 // drate[R] LDS scratch.
+template <int NT>
 __device__ __forceinline__ void cell_jvp(const DeviceNet &n, const double *__restrict__ k, const double *x,
                                          const double *y, double *drate, double *out) {
-    for (int r0 = threadIdx.x; r0 < n.R; r0 += 4 * kBlock) {
+    for (int r0 = threadIdx.x; r0 < n.R; r0 += 4 * NT) {
         int ab[4];
         double kr[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const int r = r0 + u * kBlock;
+            const int r = r0 + u * NT;
             ab[u] = r < n.R ? n.rx_ab[r] : 0;
             kr[u] = r < n.R ? k[r] : 0.0;
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const int r = r0 + u * kBlock;
+            const int r = r0 + u * NT;
             const int a = ab[u] & 0xffff, b = (ab[u] >> 16) & 0xffff;
             const double v = b == 0xffff ? kr[u] * y[a] : kr[u] * (y[a] * x[b] + x[a] * y[b]);
             if (r < n.R) drate[r] = v;
         }
     }
     __syncthreads();
-    species_gather(n, drate, out);
+    species_gather<NT>(n, drate, out);
 }
 
 // The Jacobian nonzeros J_e(x) of one cell into jv[nnzJ] (global, written

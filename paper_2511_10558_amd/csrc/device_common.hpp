@@ -21,7 +21,7 @@ constexpr double kMaxFactor = 10.0;
 // status values: >= 0 are the public ABDF_CELL_* codes
 constexpr int32_t kRunning = -1;
 
-// Newton phase of the current step attempt
+// Newton phase of a step attempt
 constexpr int32_t kIter = 0;
 constexpr int32_t kConverged = 1;
 constexpr int32_t kFailed = 2;
@@ -35,9 +35,9 @@ constexpr int32_t kLuRefined32 = 1;
 constexpr int32_t kLu64 = 2;
 
 struct SlotCtl {
-    double t, h, t_end, c, c_lu, eta_old, rtol, atol, newton_tol, err;
+    double t, h, t_end, c, c_lu, rtol, atol, newton_tol;
     double tc;        // expansion time of the conditions (0: constant)
-    int32_t q, n_equal, status, phase, j_fresh, jac_refresh, landing, newton_iter;
+    int32_t q, n_equal, status, j_fresh, jac_refresh, landing;
     int32_t lu_valid, cell, m_last, lu_mode;   // FP32-LU engines: kLuPlain32, kLuRefined32 or kLu64
     int32_t n_steps, n_attempts, n_err_reject, n_newton_fail, n_rhs, n_jac, n_lu, n_newton_iter;
     int32_t n_lu64;                        // FP32-LU engines: factorisations done in FP64 after a fallback
@@ -45,6 +45,20 @@ struct SlotCtl {
     int32_t stage;                         // ESDIRK: the stage being solved (2..7)
     int32_t rejected;                      // ESDIRK: the last attempt was rejected (no growth on the next accept)
 };
+
+// Phases of a workgroup's time (SlotQueue::ticks).
+enum { kPhaseControl, kPhaseFactor, kPhaseRhs, kPhaseNewton, kPhaseAdjSolve, kPhaseAdjStep, kPhases };
+
+// The slots waiting for a workgroup and those finished, on the device.  The
+// rings' counters only grow; entry i of a ring is at i % nslots.
+struct SlotQueue {
+    unsigned long long head, tail;            // admitted slots (Slots::fifo)
+    unsigned long long held_head, held_tail;  // slots interrupted by the end of a launch (Slots::held)
+    unsigned long long ticks[kPhases];        // 100 MHz ticks summed over workgroups, per phase (timers on)
+    int32_t nfin;                             // finished slots since the last harvest (Slots::fin)
+    int32_t stop;                             // the last launch in which a workgroup found the queue empty
+};
+constexpr int kQueueInts = sizeof(SlotQueue) / sizeof(int32_t);
 
 // Device workspace for n slots of one network (all arrays slot-major).
 struct Slots {
@@ -62,22 +76,20 @@ struct Slots {
     double *phi;      // [n][5]: T, n_H, A_V, zeta, G0
     double *k;        // [n][R]
     double *D;        // [n][kDRows][S]: BDF differences; ESDIRK: x_n, F_1, G_2..G_7
-    double *x;        // [n][S] Newton iterate
-    double *d;        // [n][S] accumulated correction
-    double *psi;      // [n][S]
-    double *scl;      // [n][S] Newton weights atol + rtol |x_p|
     double *xJ;       // [n][S] point of the current Jacobian
-    double *rb;       // [n][S] Newton residual c f(x) - psi - d
+    double *x;        // [n][S] reverse sweep: dL/dx_0
+    double *d;        // [n][S] reverse sweep: lambda_xp
+    double *psi;      // [n][S] reverse sweep: lambda_d
+    double *rb;       // [n][S] reverse sweep: right-hand side of the transposed solve
     double *jval;     // [n][nnzJ] Jacobian nonzeros at x_J (the factor kernel's input)
     void *lu;         // [n] factors (double or float, NP x NP), rows in storage order, lu_stride bytes apart
     void *dinv;       // [n] inverses of the diagonal blocks' triangles [NB][2][64][64], dinv_stride bytes apart
     size_t lu_stride, dinv_stride;
     int32_t *perm;    // [n][NP]
-    int32_t *act;     // [3][n] active-slot lists (ring)
-    int32_t *lul;     // [3][n] slots needing a factorisation (ring)
-    int32_t *nol;     // [3][n] active slots whose factorisation is current (ring)
+    int32_t *fifo;    // [n] ring of admitted slots
+    int32_t *held;    // [n] ring of interrupted slots
     int32_t *fin;     // [n] finished slots since the last harvest
-    int32_t *cnt;     // [0..2] active counts, [3..5] factor counts, [6] finished count, [7..9] no-factor counts
+    SlotQueue *q;
     // step tape of the discrete adjoint (null when not recording), indexed by cell
     int tape_cap;     // accepted steps recorded per cell
     double *tape_x;   // [cells][tape_cap][S] x after each accepted step
@@ -119,26 +131,6 @@ __device__ __forceinline__ T *slot_lu(const Slots &s, int slot) {
 template <typename T>
 __device__ __forceinline__ T *slot_dinv(const Slots &s, int slot) {
     return reinterpret_cast<T *>(static_cast<char *>(s.dinv) + size_t(slot) * s.dinv_stride);
-}
-
-// Slot lists of the step-attempt loop: every active slot, those that factor
-// this attempt, those that do not.
-constexpr int kListAll = 0;
-constexpr int kListFactor = 1;
-constexpr int kListNoFactor = 2;
-constexpr int kCountSlots = 16;   // ints in Slots::cnt
-
-__device__ __forceinline__ const int32_t *slot_list(const Slots &s, int which, int ring, int &count) {
-    if (which == kListFactor) {
-        count = s.cnt[3 + ring];
-        return s.lul + ring * s.nslots;
-    }
-    if (which == kListNoFactor) {
-        count = s.cnt[7 + ring];
-        return s.nol + ring * s.nslots;
-    }
-    count = s.cnt[ring];
-    return s.act + ring * s.nslots;
 }
 
 // One step of a wave-wide arg-max (value descending, key ascending on ties)
@@ -213,12 +205,38 @@ __device__ __forceinline__ void wave_argmax_ballot(double &v, int &k) {
     v = m;
 }
 
-// Sum over the workgroup, identical on every thread; fixed reduction order.
+// v of the lane N places on in its row of 16.
+template <int N>
+__device__ __forceinline__ double row_rotate(double v) {
+    const int lo = __double2loint(v), hi = __double2hiint(v);
+    return __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, 0x120 + N, 0xf, 0xf, false),
+                            __builtin_amdgcn_update_dpp(lo, lo, 0x120 + N, 0xf, 0xf, false));
+}
+
+// Sum over each row of 16 lanes, on all of them: the pairwise sums of lanes 8,
+// 4, 2, 1 apart (xor), by rotations, which reach the same partner once the
+// values repeat every 16, 8, 4, 2 lanes.  DPP moves instead of LDS permutes:
+// this sum ends every block of a triangular solve.
+__device__ __forceinline__ double row_sum(double v) {
+    v += row_rotate<8>(v);
+    v += row_rotate<4>(v);
+    v += row_rotate<2>(v);
+    v += row_rotate<1>(v);
+    return v;
+}
+
+// Sum over the wave, on every lane, in the order of xor steps 32, 16, 8, 4, 2, 1.
+__device__ __forceinline__ double wave_sum(double v) {
+    v += __shfl_xor(v, 32);
+    v += __shfl_xor(v, 16);
+    return row_sum(v);
+}
+
 // Sum over a workgroup of NT threads (red: NT / 64 doubles), identical on every
 // thread; fixed reduction order.
 template <int NT>
 __device__ inline double block_sum_nt(double v, double *red) {
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    v = wave_sum(v);
     __syncthreads();
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();

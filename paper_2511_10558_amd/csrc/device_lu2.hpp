@@ -1,5 +1,5 @@
 // Left-looking blocked LU with partial pivoting, one workgroup per matrix
-// (shape per element type: LuShape), and the matching triangular solves.  The matrix is read through a
+// of W waves, and the matching triangular solves.  The matrix is read through a
 // source functor when each block column is first gathered, so it can be
 // formed on the fly (the Newton matrix) instead of being stored first.
 //
@@ -49,22 +49,12 @@ constexpr int kLuMaxNP = 512;     // one thread per row in the panel
 // backward error stays at the level of partial pivoting there.
 constexpr double kPivotThreshold = 4.0;
 
-// Workgroup shape of the factorisation per element type.  FP64: 8 waves of
-// 256 VGPRs, each wave holding four row tiles of the block column.  FP32: 16
-// waves of 128 VGPRs with two row tiles each (its accumulators are half the
-// size), twice the waves to hide latency with.
-template <typename T>
-struct LuShape;
-template <>
-struct LuShape<double> { static constexpr int waves = 8, wave_bits = 3; };
-template <>
-struct LuShape<float> { static constexpr int waves = 16, wave_bits = 4; };
-template <typename T>
-constexpr int lu_waves = LuShape<T>::waves;
-template <typename T>
-constexpr int lu_threads = LuShape<T>::waves * 64;
-template <typename T>
-constexpr int lu_slots = kLuMaxNP / 16 / LuShape<T>::waves;   // row tiles per wave
+// The factorisation runs on W waves, W * 64 >= NP (one thread per row in the
+// panel); each wave holds row tiles w, w + W, ... of the block column in at most
+// lu_slots accumulator tiles.
+template <int W>
+constexpr int lu_slots = W >= 8 ? kLuMaxNP / 16 / W : 4;
+constexpr int lu_wave_bits(int w) { return w <= 1 ? 0 : 1 + lu_wave_bits(w / 2); }
 constexpr int kLdb = 65;          // LDS leading dimension of 64-wide staging buffers
 
 template <typename T>
@@ -92,22 +82,62 @@ __device__ inline int tile_row_reg<float>(int t) { return t & 3; }
 constexpr int kPanLd = 17;        // row stride of the 16-column sub-panel buffer
 constexpr int kU12Ld = 49;        // row stride of the 16 x 48 sub-panel U block
 constexpr int kCrowLd = 17;       // candidate pivot row: 16 entries and the pivot's reciprocal
+// rows of the staging buffers of a block column (64, or the matrix's order)
+__host__ __device__ constexpr int lu2_stage_rows(int NP) { return NP < kLuW ? NP : kLuW; }
 template <typename T>
 __host__ __device__ constexpr size_t lu2_work_elems(int NP) {
-    return size_t(NP) * kPanLd + 16 * kU12Ld > 3 * size_t(kLuW) * kLdb + 1536
-               ? size_t(NP) * kPanLd + 16 * kU12Ld
-               : 3 * size_t(kLuW) * kLdb + 1536;
+    const size_t panel = size_t(NP) * kPanLd + 16 * kU12Ld;
+    const size_t stage = 3 * size_t(lu2_stage_rows(NP)) * kLdb + (sizeof(T) == 4 ? 1536 : 0);
+    return panel > stage ? panel : stage;
 }
-template <typename T>
+template <typename T, int W>
 __host__ __device__ constexpr size_t lu2_lds_bytes(int NP) {
     return 5 * size_t(NP) * sizeof(int32_t)                        // perm, sto, pos_log, log_pos, pidx
            + kLuW * sizeof(int32_t)                                // piv_pos
-           + 2 * lu_waves<T> * (sizeof(double) + sizeof(int32_t))     // arg-max partials, double-buffered
+           + 2 * W * (sizeof(double) + sizeof(int32_t))     // arg-max partials, double-buffered
            + 16 + 18 * sizeof(int32_t)                                // row flags; diagonal positions, flag
-           + 2 * lu_waves<T> * kCrowLd * sizeof(T)                    // candidate pivot rows, double-buffered
+           + 2 * W * kCrowLd * sizeof(T)                    // candidate pivot rows, double-buffered
            + 16 * kCrowLd * sizeof(T)                                 // factored diagonal block
            + lu2_work_elems<T>(NP) * sizeof(T) + 64;
 }
+
+// Its parts.  After a factorisation of one block column (NP <= 64) perm, Xb
+// (inverse of the unit-lower triangle) and Ub (of the upper one) stay valid.
+template <typename T, int W>
+struct LuLds {
+    int32_t *perm;      // logical row -> storage row
+    int32_t *sto;       // position -> storage row (this block column)
+    int32_t *pos_log;   // position -> logical row
+    int32_t *log_pos;   // logical row -> position
+    int32_t *pidx;      // position -> pivot column in this block, or -1
+    int32_t *piv_pos;   // pivot column -> position
+    double *redv;       // [2][waves] arg-max partials
+    int32_t *redi;
+    int32_t *rwave;     // [2] wave holding logical row r; [2] first zero pivot (1-based) or INT_MAX
+    int32_t *dpos;      // [16] positions of the diagonal pivot rows
+    int32_t *spec_bad;  // the diagonal pivots were refused
+    T *crow;            // [2][waves][kCrowLd] candidate rows
+    T *Db;              // [16][kCrowLd] factored diagonal block
+    T *Cb, *Ub, *Xb;    // [64][kLdb] each (rows: lu2_stage_rows); Cb: left-looking, inverses
+    __device__ __forceinline__ LuLds(int NP, unsigned char *smem) {
+        perm = reinterpret_cast<int32_t *>(smem);
+        sto = perm + NP;
+        pos_log = sto + NP;
+        log_pos = pos_log + NP;
+        pidx = log_pos + NP;
+        piv_pos = pidx + NP;
+        redv = reinterpret_cast<double *>(piv_pos + kLuW);
+        redi = reinterpret_cast<int32_t *>(redv + 2 * W);
+        rwave = redi + 2 * W;
+        dpos = rwave + 4;
+        spec_bad = dpos + 16;
+        crow = reinterpret_cast<T *>(dpos + 18);
+        Db = crow + 2 * W * kCrowLd;
+        Cb = Db + 16 * kCrowLd;
+        Ub = Cb + lu2_stage_rows(NP) * kLdb;
+        Xb = Ub + lu2_stage_rows(NP) * kLdb;
+    }
+};
 
 // Orders one wave's LDS accesses before and after this point as written: the
 // LDS executes a wave's instructions in issue order, so a value one lane
@@ -131,25 +161,26 @@ __host__ __device__ constexpr size_t lu2_dinv_elems(int NP) {
 // for inv(U), one lane per column), then the off-diagonal blocks level by
 // level on the matrix cores, one wave per block,
 // X_ij = -X_ii sum_k L_ik X_kj (lower) and Y_ij = -Y_ii sum_k U_ik Y_kj (upper).
-// Xb, Yb: 64 x kLdb LDS outputs; Tb: 1536 elements of LDS scratch.  Every
+// Xb, Yb: W x kLdb LDS outputs; Tb: 1536 elements of LDS scratch (FP32 only).  Every
 // thread of the workgroup must call this (it contains barriers).
-template <typename T>
+template <typename T, int NW>
 __device__ __forceinline__ void diag_inverses(const T *Cb, int W, T *D, T *Xb, T *Yb, T *Tb) {
-    constexpr int HALF = lu_threads<T> / 2;
+    constexpr int HALF = 32 * NW;   // threads of each triangle
     const int tid = threadIdx.x;
     const bool upper = tid >= HALF;
     const int h = tid % HALF;
     const int nb = W / 16;
     T *Z = upper ? Yb : Xb;
     T *Tz = Tb + (upper ? 768 : 0);
-    // zero the outputs
-    for (int e = h; e < 64 * 64; e += HALF) Z[(e >> 6) * kLdb + (e & 63)] = T(0);
+    // zero the outputs (rows of the block; the rest is not read)
+    for (int e = h; e < 64 * W; e += HALF) Z[(e >> 6) * kLdb + (e & 63)] = T(0);
     __syncthreads();
     // diagonal 16 x 16 blocks: one lane per column, the column's entries in
     // registers, by substitution (no barrier, no shuffle); lanes h < 64 of
-    // each half, lane h holding column h of the 64 x 64 block
-    if (h < 64) {
-        const int b = h >> 4, kc = h & 15;
+    // each half, lane h holding column h of the 64 x 64 block (fewer lanes take
+    // several columns in turn)
+    for (int hc = h; hc < 64; hc += HALF) {
+        const int b = hc >> 4, kc = hc & 15;
         if (b < nb) {
             const T *Bd = Cb + 16 * b * kLdb + 16 * b;     // the diagonal block, leading dimension kLdb
             double xs[16];
@@ -191,9 +222,9 @@ __device__ __forceinline__ void diag_inverses(const T *Cb, int W, T *D, T *Xb, T
         using acc_t = typename Mt::acc_t;
         const int wave = tid >> 6, lane = tid & 63, lr = lane & 15, lg = lane >> 4;
         for (int d = 1; d < nb; ++d) {
-            if (wave < 2 * (nb - d)) {
-                const bool up = wave >= nb - d;
-                const int bi = up ? wave - (nb - d) : wave;
+            for (int blk = wave; blk < 2 * (nb - d); blk += NW) {
+                const bool up = blk >= nb - d;
+                const int bi = up ? blk - (nb - d) : blk;
                 const int i = up ? bi : bi + d, jb = up ? bi + d : bi;
                 const int k0 = up ? i + 1 : jb;
                 T *Zt = up ? Yb : Xb;
@@ -213,7 +244,7 @@ __device__ __forceinline__ void diag_inverses(const T *Cb, int W, T *D, T *Xb, T
                     for (int st = 0; st < 4; ++st)
                         acc2 = Mt::mma(Zt[(16 * i + lr) * kLdb + 16 * i + 4 * st + lg], acc[st], acc2);
                 } else {
-                    T *Ts = Tb + 256 * wave;
+                    T *Ts = Tb + 256 * blk;
 #pragma unroll
                     for (int v = 0; v < 4; ++v) Ts[Mt::row(lane, v) * 16 + lr] = acc[v];
                     wave_lds_order();
@@ -228,7 +259,7 @@ __device__ __forceinline__ void diag_inverses(const T *Cb, int W, T *D, T *Xb, T
             __syncthreads();
         }
     }
-    for (int e = h; e < 64 * 64; e += HALF) D[(upper ? kLuW * kLuW : 0) + e] = Z[(e >> 6) * kLdb + (e & 63)];
+    for (int e = h; e < 64 * W; e += HALF) D[(upper ? kLuW * kLuW : 0) + e] = Z[(e >> 6) * kLdb + (e & 63)];
 }
 
 // The value v of lane src (a constant of the unrolled loops), on every lane.
@@ -257,7 +288,7 @@ struct DenseSource {
 
 // Factors the matrix whose entries src yields (read once, when its block
 // column is gathered) into A: A needs no initial contents.
-template <typename T, typename Src>
+template <typename T, int W, typename Src>
 __device__ __forceinline__ void lu_factor_left(T *__restrict__ A, int NP, int32_t *__restrict__ perm_out,
                                                T *__restrict__ dinv, int32_t *info, unsigned char *smem,
                                                const Src &src) {
@@ -269,28 +300,15 @@ __device__ __forceinline__ void lu_factor_left(T *__restrict__ A, int NP, int32_
     const int RT = NP / 16;
     const int NB = (NP + kLuW - 1) / kLuW;
 
-    int32_t *perm = reinterpret_cast<int32_t *>(smem);    // logical row -> storage row
-    int32_t *sto = perm + NP;                              // position -> storage row (this block column)
-    int32_t *pos_log = sto + NP;                           // position -> logical row
-    int32_t *log_pos = pos_log + NP;                       // logical row -> position
-    int32_t *pidx = log_pos + NP;                          // position -> pivot column in this block, or -1
-    int32_t *piv_pos = pidx + NP;                          // pivot column -> position
-    double *redv = reinterpret_cast<double *>(piv_pos + kLuW);   // [2][waves]
-    int32_t *redi = reinterpret_cast<int32_t *>(redv + 2 * lu_waves<T>);
-    int32_t *rwave = redi + 2 * lu_waves<T>;                        // [2] wave holding logical row r;
-                                                                 // [2] first zero pivot (1-based) or INT_MAX
-    int32_t *dpos = rwave + 4;                                   // [16] positions of the diagonal pivot rows
-    int32_t *spec_bad = dpos + 16;                               // [2] the diagonal pivots were refused
-    T *crow = reinterpret_cast<T *>(dpos + 18);                  // [2][waves][kCrowLd] candidate rows
-    T *Db = crow + 2 * lu_waves<T> * kCrowLd;                    // [16][kCrowLd] factored diagonal block
-    T *work = Db + 16 * kCrowLd;
-    T *Cb = work;                                          // [64][kLdb]   (left-looking, inverses)
-    T *Ub = Cb + kLuW * kLdb;                              // [64][kLdb]
-    T *Xb = Ub + kLuW * kLdb;                              // [64][kLdb]
-    T *P = work;                                           // [NP][kPanLd] (panel)
+    const LuLds<T, W> lds(NP, smem);
+    int32_t *perm = lds.perm, *sto = lds.sto, *pos_log = lds.pos_log, *log_pos = lds.log_pos, *pidx = lds.pidx;
+    int32_t *piv_pos = lds.piv_pos, *redi = lds.redi, *rwave = lds.rwave, *dpos = lds.dpos, *spec_bad = lds.spec_bad;
+    double *redv = lds.redv;
+    T *crow = lds.crow, *Db = lds.Db, *Cb = lds.Cb, *Ub = lds.Ub, *Xb = lds.Xb;
+    T *P = Cb;                                             // [NP][kPanLd] (panel)
     T *U12 = P + size_t(NP) * kPanLd;                      // [16][kU12Ld]
 
-    for (int i = tid; i < NP; i += lu_threads<T>) perm[i] = i;
+    for (int i = tid; i < NP; i += (64 * W)) perm[i] = i;
     if (tid < 16) dpos[tid] = 0;      // every position read from it stays in the panel
     if (tid == 0) rwave[2] = 0x7fffffff;
     __syncthreads();
@@ -299,34 +317,34 @@ __device__ __forceinline__ void lu_factor_left(T *__restrict__ A, int NP, int32_
         const int c0 = j * kLuW;
         const int Wj = min(kLuW, NP - c0);
         const int CTj = Wj / 16;
-        for (int q = tid; q < NP; q += lu_threads<T>) {
+        for (int q = tid; q < NP; q += (64 * W)) {
             sto[q] = perm[q];
             pos_log[q] = q;
             log_pos[q] = q;
             pidx[q] = -1;
         }
-        acc_t acc[lu_slots<T>][4];
+        acc_t acc[lu_slots<W>][4];
         // 1. gather the block column (positions = logical rows at this point):
         //    what each of the lane's rows needs first, then every entry, so
         //    that each lane has all its row loads in flight together and then
         //    all its entry loads (the accumulators are not live yet).  Tiles
         //    outside the matrix read column c0 + lc of row 0 and are zeroed.
         {
-            typename Src::Row rw[lu_slots<T>][4];
-            int srow[lu_slots<T>][4];
+            typename Src::Row rw[lu_slots<W>][4];
+            int srow[lu_slots<W>][4];
 #pragma unroll
-            for (int s = 0; s < lu_slots<T>; ++s) {
-                const int rt = wave + lu_waves<T> * s;
+            for (int s = 0; s < lu_slots<W>; ++s) {
+                const int rt = wave + W * s;
 #pragma unroll
                 for (int v = 0; v < 4; ++v) srow[s][v] = rt < RT ? perm[16 * rt + M::row(lane, v)] : 0;
             }
 #pragma unroll
-            for (int s = 0; s < lu_slots<T>; ++s)
+            for (int s = 0; s < lu_slots<W>; ++s)
 #pragma unroll
                 for (int v = 0; v < 4; ++v) rw[s][v] = src.row(srow[s][v], c0);
 #pragma unroll
-            for (int s = 0; s < lu_slots<T>; ++s) {
-                const int rt = wave + lu_waves<T> * s;
+            for (int s = 0; s < lu_slots<W>; ++s) {
+                const int rt = wave + W * s;
 #pragma unroll
                 for (int ct = 0; ct < 4; ++ct)
 #pragma unroll
@@ -340,8 +358,8 @@ __device__ __forceinline__ void lu_factor_left(T *__restrict__ A, int NP, int32_
         for (int i = 0; i < j; ++i) {
             const int r0 = i * kLuW;
 #pragma unroll
-            for (int s = 0; s < lu_slots<T>; ++s) {
-                const int rt = wave + lu_waves<T> * s;
+            for (int s = 0; s < lu_slots<W>; ++s) {
+                const int rt = wave + W * s;
                 if (rt >= 4 * i && rt < 4 * i + 4) {
 #pragma unroll
                     for (int ct = 0; ct < 4; ++ct)
@@ -353,9 +371,9 @@ __device__ __forceinline__ void lu_factor_left(T *__restrict__ A, int NP, int32_
             }
             __syncthreads();
             const T *Li = dinv + size_t(i) * 2 * kLuW * kLuW;   // inverse of the unit-lower block i
-            {
-                // the 16 tiles of U_ij = inv(L_ii) C_i, spread over all waves
-                constexpr int TPW = 16 / lu_waves<T>;
+            if constexpr (W >= 4) {
+                // the 16 tiles of U_ij = inv(L_ii) C_i, spread over all waves (one wave has one block column)
+                constexpr int TPW = 16 / W;
                 const int t0 = wave * TPW, tr = t0 >> 2;
                 v4 a[4];
 #pragma unroll
@@ -380,8 +398,8 @@ __device__ __forceinline__ void lu_factor_left(T *__restrict__ A, int NP, int32_
             // the rows of block i take their tiles of U_ij; the rows below are
             // updated C -= L_{:,i} U_ij
 #pragma unroll
-            for (int s = 0; s < lu_slots<T>; ++s) {
-                const int rt = wave + lu_waves<T> * s;
+            for (int s = 0; s < lu_slots<W>; ++s) {
+                const int rt = wave + W * s;
                 if (rt >= 4 * i && rt < 4 * i + 4) {
                     const int tr = rt - 4 * i;
 #pragma unroll
@@ -416,8 +434,8 @@ __device__ __forceinline__ void lu_factor_left(T *__restrict__ A, int NP, int32_
             //     accumulators keep it until (c), so it can be written again)
             auto panel_to_lds = [&]() {
 #pragma unroll
-                for (int s = 0; s < lu_slots<T>; ++s) {
-                    const int rt = wave + lu_waves<T> * s;
+                for (int s = 0; s < lu_slots<W>; ++s) {
+                    const int rt = wave + W * s;
                     if (rt >= 4 * j && rt < RT)
 #pragma unroll
                         for (int v = 0; v < 4; ++v) {
@@ -579,7 +597,7 @@ __device__ __forceinline__ void lu_factor_left(T *__restrict__ A, int NP, int32_
             const bool busy = __ballot(active) != 0;
             if (!busy && lane == 0) {
                 redv[wave] = -1.0;
-                redv[lu_waves<T> + wave] = -1.0;
+                redv[W + wave] = -1.0;
             }
             T x[16];
 #pragma unroll
@@ -594,14 +612,14 @@ __device__ __forceinline__ void lu_factor_left(T *__restrict__ A, int NP, int32_
                     double bv = (active && ax == ax) ? ax : -1.0;   // NaN never wins
                     int bl = mylog;
                     wave_argmax_ballot(bv, bl);
-                    if (lane == 0) { redv[buf * lu_waves<T> + wave] = bv; redi[buf * lu_waves<T> + wave] = bl; }
+                    if (lane == 0) { redv[buf * W + wave] = bv; redi[buf * W + wave] = bl; }
                     if (active && mylog == r) rwave[buf] = wave;
                     // the wave's candidate row (or row r, kept when nothing is
                     // finite) with the reciprocal of its entry in column c, or 0
                     // where that is below the smallest normal number (then the
                     // multipliers are formed by division, as LAPACK does)
                     if (active && mylog == (bv < 0.0 ? r : bl)) {
-                        T *cr = crow + (buf * lu_waves<T> + wave) * kCrowLd;
+                        T *cr = crow + (buf * W + wave) * kCrowLd;
 #pragma unroll
                         for (int cc = c; cc < 16; ++cc) cr[cc] = x[cc];
                         cr[16] = fabs(x[c]) >= std::numeric_limits<T>::min() ? T(1) / x[c] : T(0);
@@ -613,12 +631,12 @@ __device__ __forceinline__ void lu_factor_left(T *__restrict__ A, int NP, int32_
                 // to the smaller logical row
                 int lp, wv;
                 {
-                    const double fv = lane < lu_waves<T> ? redv[buf * lu_waves<T> + lane] : -2.0;
-                    const int fi = lane < lu_waves<T> ? redi[buf * lu_waves<T> + lane] : 0x7fffffff;
+                    const double fv = lane < W ? redv[buf * W + lane] : -2.0;
+                    const int fi = lane < W ? redi[buf * W + lane] : 0x7fffffff;
                     double m = dpp_max_step<0xB1, 0xf>(fv);    // quad_perm [1,0,3,2]
                     m = dpp_max_step<0x4E, 0xf>(m);            // quad_perm [2,3,0,1]
                     m = dpp_max_step<0x141, 0xf>(m);           // row_half_mirror: lanes 0..7 hold their max
-                    if (lu_waves<T> > 8) m = dpp_max_step<0x140, 0xf>(m);   // row_mirror: lanes 0..15
+                    if (W > 8) m = dpp_max_step<0x140, 0xf>(m);   // row_mirror: lanes 0..15
                     {
                         const int lo = __builtin_amdgcn_readlane(__double2loint(m), 0);
                         const int hi = __builtin_amdgcn_readlane(__double2hiint(m), 0);
@@ -628,20 +646,20 @@ __device__ __forceinline__ void lu_factor_left(T *__restrict__ A, int NP, int32_
                         lp = r;
                         wv = rwave[buf];
                     } else {
-                        const unsigned long long hit = __ballot(lane < lu_waves<T> && fv == m);
+                        const unsigned long long hit = __ballot(lane < W && fv == m);
                         if (__popcll(hit) == 1) {
                             wv = __ffsll(static_cast<unsigned long long>(hit)) - 1;
                             lp = __builtin_amdgcn_readlane(fi, wv);
                         } else {
-                            double tv = (lane < lu_waves<T> && fv == m) ? 1.0 : -1.0;
-                            int tk = (lane < lu_waves<T> && fv == m) ? (fi << LuShape<T>::wave_bits) + lane : 0x7fffffff;
+                            double tv = (lane < W && fv == m) ? 1.0 : -1.0;
+                            int tk = (lane < W && fv == m) ? (fi << lu_wave_bits(W)) + lane : 0x7fffffff;
                             wave_argmax(tv, tk);
-                            lp = tk >> LuShape<T>::wave_bits;
-                            wv = tk & (lu_waves<T> - 1);
+                            lp = tk >> lu_wave_bits(W);
+                            wv = tk & (W - 1);
                         }
                     }
                 }
-                const T *urow = crow + (buf * lu_waves<T> + wv) * kCrowLd;
+                const T *urow = crow + (buf * W + wv) * kCrowLd;
                 const T piv = urow[c];
                 const T rinv = urow[16];
                 if (lane == 0 && piv == T(0)) atomicMin(&rwave[2], r + 1);
@@ -685,8 +703,8 @@ __device__ __forceinline__ void lu_factor_left(T *__restrict__ A, int NP, int32_
             }   // partial pivoting
             // (c) back to the accumulators
 #pragma unroll
-            for (int s = 0; s < lu_slots<T>; ++s) {
-                const int rt = wave + lu_waves<T> * s;
+            for (int s = 0; s < lu_slots<W>; ++s) {
+                const int rt = wave + W * s;
                 if (rt >= 4 * j && rt < RT)
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
@@ -701,8 +719,8 @@ __device__ __forceinline__ void lu_factor_left(T *__restrict__ A, int NP, int32_
             if (sp + 1 < CTj) {
                 const int nct = CTj - sp - 1;
 #pragma unroll
-                for (int s = 0; s < lu_slots<T>; ++s) {
-                    const int rt = wave + lu_waves<T> * s;
+                for (int s = 0; s < lu_slots<W>; ++s) {
+                    const int rt = wave + W * s;
                     if (rt >= 4 * j && rt < RT)
 #pragma unroll
                         for (int ct = 1; ct < 4; ++ct)
@@ -730,8 +748,8 @@ __device__ __forceinline__ void lu_factor_left(T *__restrict__ A, int NP, int32_
                 }
                 __syncthreads();
 #pragma unroll
-                for (int s = 0; s < lu_slots<T>; ++s) {
-                    const int rt = wave + lu_waves<T> * s;
+                for (int s = 0; s < lu_slots<W>; ++s) {
+                    const int rt = wave + W * s;
                     if (rt >= 4 * j && rt < RT) {
                         const bool unused = pidx[16 * rt + lc] < 0;
                         T a[4];
@@ -759,13 +777,13 @@ __device__ __forceinline__ void lu_factor_left(T *__restrict__ A, int NP, int32_
         // the last sub-panel's rows are read back from P before the staging
         // buffer below (which shares P's memory) is written
         __syncthreads();
-        for (int q2 = tid; q2 < NP; q2 += lu_threads<T>)
+        for (int q2 = tid; q2 < NP; q2 += (64 * W))
             if (q2 >= c0) perm[pos_log[q2]] = sto[q2];
         // 4. diagonal block (logical rows c0 .. c0 + Wj - 1) to LDS, its
         //    triangles' inverses, and the block column back to its storage rows
 #pragma unroll
-        for (int s = 0; s < lu_slots<T>; ++s) {
-            const int rt = wave + lu_waves<T> * s;
+        for (int s = 0; s < lu_slots<W>; ++s) {
+            const int rt = wave + W * s;
             if (rt >= 4 * j && rt < RT)
 #pragma unroll
                 for (int ct = 0; ct < 4; ++ct)
@@ -779,8 +797,8 @@ __device__ __forceinline__ void lu_factor_left(T *__restrict__ A, int NP, int32_
         // the block column goes back first, so that the accumulators are free
         // while the inverses are formed
 #pragma unroll
-        for (int s = 0; s < lu_slots<T>; ++s) {
-            const int rt = wave + lu_waves<T> * s;
+        for (int s = 0; s < lu_slots<W>; ++s) {
+            const int rt = wave + W * s;
             if (rt < RT)
 #pragma unroll
                 for (int ct = 0; ct < 4; ++ct)
@@ -790,15 +808,15 @@ __device__ __forceinline__ void lu_factor_left(T *__restrict__ A, int NP, int32_
                             A[size_t(sto[16 * rt + M::row(lane, v)]) * NP + c0 + 16 * ct + lc] = acc[s][ct][v];
         }
         __syncthreads();
-        diag_inverses<T>(Cb, Wj, dinv + size_t(j) * 2 * kLuW * kLuW, Xb, Ub, Xb + kLuW * kLdb);
+        diag_inverses<T, W>(Cb, Wj, dinv + size_t(j) * 2 * kLuW * kLuW, Xb, Ub, Xb + lu2_stage_rows(NP) * kLdb);
         __syncthreads();
     }
-    for (int i = tid; i < NP; i += lu_threads<T>) perm_out[i] = perm[i];
+    for (int i = tid; i < NP; i += (64 * W)) perm_out[i] = perm[i];
     if (tid == 0 && info) *info = rwave[2] == 0x7fffffff ? 0 : rwave[2];
 }
 
 // Solves (P^T L U) z = b for one matrix factored by lu_factor_left, with the
-// kBlock threads of a per-cell workgroup.  Row r of the factors is storage row
+// NT threads of a per-cell workgroup.  Row r of the factors is storage row
 // rowmap[r] (identity if rowmap is null); y starts as b[bperm[.]] (both are
 // perm in the solver).  b[NP] (LDS, FP64) is read, the
 // solution is left in y[NP] (LDS); t is 64 doubles of LDS scratch.  Factor
@@ -808,28 +826,29 @@ __device__ __forceinline__ void lu_factor_left(T *__restrict__ A, int NP, int32_
 // pivot is taken from them before column N), and b is zero there; the
 // products then stop at N and y keeps its zeros past N.  N = NP for factors
 // of unknown padding.
-template <typename T>
+template <typename T, int NT>
 __device__ __forceinline__ void lu_solve_left(const T *__restrict__ A, const T *__restrict__ dinv, const int32_t *__restrict__ rowmap,
                               const int32_t *__restrict__ bperm, int NP, int N, const double *b, double *y, double *t) {
     const int tid = threadIdx.x;
-    const int lane16 = tid & 15, row16 = tid >> 4;   // 16 lanes per row, 16 rows per pass
+    const int lane16 = tid & 15, row16 = tid >> 4;   // 16 lanes per row
+    constexpr int RP = NT / 16, P = kLuW / RP;        // rows per pass, passes
     constexpr int VW = 16 / int(sizeof(T));           // factor entries per 16-byte load
-    for (int i = tid; i < NP; i += kBlock) y[i] = b[bperm[i]];
+    for (int i = tid; i < NP; i += NT) y[i] = b[bperm[i]];
     __syncthreads();
     const int NB = (N + kLuW - 1) / kLuW;
     // t[rr] = y[r0 + rr] - A_row(r0 + rr)[c_begin, c_end) . vec for rr < W (rows through
-    // rowmap); 16 lanes per row, each thread carries 4 rows so that four
-    // 16-byte loads are in flight per step.
+    // rowmap); 16 lanes per row, each thread carries P rows, whose 16-byte
+    // loads are in flight together.
     auto gemv_off = [&](int r0, int W, int c_begin, int c_end, const double *vec) {
         // rows past W (last block) read row W - 1 again; their sums are not stored.
         // No load sits behind a condition, so all of them are in flight together.
-        const T *rows[4];
+        const T *rows[P];
 #pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            const int rr = min(row16 + 16 * p, W - 1);
+        for (int p = 0; p < P; ++p) {
+            const int rr = min(row16 + RP * p, W - 1);
             rows[p] = A + size_t(rowmap ? rowmap[r0 + rr] : r0 + rr) * NP;
         }
-        double acc[4] = {0.0, 0.0, 0.0, 0.0};
+        double acc[P] = {};
         // VW entries (16 bytes) per lane and load: c_begin is a multiple of 64
         // and rows are 64-byte aligned.  FP32 entries past c_end (at most
         // three, within the row) meet zeros of vec.
@@ -837,11 +856,11 @@ __device__ __forceinline__ void lu_solve_left(const T *__restrict__ A, const T *
             double yv[VW];
 #pragma unroll
             for (int k = 0; k < VW; ++k) yv[k] = vec[c + k];
-            T a[4][VW];
+            T a[P][VW];
 #pragma unroll
-            for (int p = 0; p < 4; ++p) __builtin_memcpy(a[p], __builtin_assume_aligned(rows[p] + c, 16), 16);
+            for (int p = 0; p < P; ++p) __builtin_memcpy(a[p], __builtin_assume_aligned(rows[p] + c, 16), 16);
 #pragma unroll
-            for (int p = 0; p < 4; ++p) {
+            for (int p = 0; p < P; ++p) {
                 if constexpr (VW == 2)
                     acc[p] += double(a[p][0]) * yv[0] + double(a[p][1]) * yv[1];
                 else
@@ -850,10 +869,9 @@ __device__ __forceinline__ void lu_solve_left(const T *__restrict__ A, const T *
             }
         }
 #pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            double a = acc[p];
-            for (int o = 8; o > 0; o >>= 1) a += __shfl_xor(a, o);
-            const int rr = row16 + 16 * p;
+        for (int p = 0; p < P; ++p) {
+            const double a = row_sum(acc[p]);
+            const int rr = row16 + RP * p;
             if (lane16 == 0 && rr < W) t[rr] = y[r0 + rr] - a;
         }
     };
@@ -863,22 +881,22 @@ __device__ __forceinline__ void lu_solve_left(const T *__restrict__ A, const T *
     // row needs anyway) and contributes nothing.  Rows past W read row W - 1
     // again and are not stored.
     auto gemv_diag = [&](int r0, int W, const T *D, bool lower) {
-        double acc[4] = {0.0, 0.0, 0.0, 0.0};
+        double acc[P] = {};
         for (int c = VW * lane16; c < W; c += 16 * VW) {
             double tv[VW];
 #pragma unroll
             for (int k = 0; k < VW; ++k) tv[k] = c + k < W ? t[c + k] : 0.0;
             // the 16 bytes holding the diagonal stand in for those on the zero side
-            T a[4][VW];
+            T a[P][VW];
 #pragma unroll
-            for (int p = 0; p < 4; ++p) {
-                const int rr = min(row16 + 16 * p, W - 1), dq = rr & ~(VW - 1);
+            for (int p = 0; p < P; ++p) {
+                const int rr = min(row16 + RP * p, W - 1), dq = rr & ~(VW - 1);
                 __builtin_memcpy(a[p], __builtin_assume_aligned(D + rr * kLuW + (lower ? min(c, dq) : max(c, dq)), 16),
                                  16);
             }
 #pragma unroll
-            for (int p = 0; p < 4; ++p) {
-                const int rr = min(row16 + 16 * p, W - 1);
+            for (int p = 0; p < P; ++p) {
+                const int rr = min(row16 + RP * p, W - 1);
                 double term[VW];
 #pragma unroll
                 for (int k = 0; k < VW; ++k) {
@@ -892,10 +910,9 @@ __device__ __forceinline__ void lu_solve_left(const T *__restrict__ A, const T *
             }
         }
 #pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            double a = acc[p];
-            for (int o = 8; o > 0; o >>= 1) a += __shfl_xor(a, o);
-            const int rr = row16 + 16 * p;
+        for (int p = 0; p < P; ++p) {
+            const double a = row_sum(acc[p]);
+            const int rr = row16 + RP * p;
             if (lane16 == 0 && rr < W) y[r0 + rr] = a;
         }
     };
@@ -924,38 +941,43 @@ __device__ __forceinline__ void lu_solve_left(const T *__restrict__ A, const T *
 // by substitution (one wave, column by column, the block staged in LDS)
 // rather than by their stored inverses: the reverse sweep of the BDF map
 // amplifies solve errors strongly, and substitution keeps them at the level
-// of a backward-stable solver.  b, z, t (>= 5 * kLuW doubles) and Db
-// (kLuW * kLdb doubles) are in LDS; b is consumed.  256 threads.
-template <typename T>
+// of a backward-stable solver.  b, z, t (>= (1 + W) * kLuW doubles) and Db
+// (kLuW * kLdb doubles) are in LDS; b is consumed.
+template <typename T, int W>
 __device__ __forceinline__ void lu_solve_left_T(const T *__restrict__ A, const int32_t *__restrict__ rowmap, int NP,
                                                 double *b, double *z, double *t, double *Db) {
     const int tid = threadIdx.x;
     const int col = tid & 63, grp = tid >> 6;
     const int NB = (NP + kLuW - 1) / kLuW;
     // t[col] = b[r0 + col] - sum_{r in [rb, re)} A_logical[r][r0 + col] vec[r]
-    auto colgemv = [&](int r0, int W, int rb, int re, const double *vec) {
+    auto colgemv = [&](int r0, int Wb, int rb, int re, const double *vec) {
         double acc = 0.0;
-        if (col < W) {
+        if (col < Wb) {
             int r = rb + grp;
-            for (; r + 12 < re; r += 16) {
+            for (; r + 3 * W < re; r += 4 * W) {
                 const double a0 = double(A[size_t(rowmap[r]) * NP + r0 + col]);
-                const double a1 = double(A[size_t(rowmap[r + 4]) * NP + r0 + col]);
-                const double a2 = double(A[size_t(rowmap[r + 8]) * NP + r0 + col]);
-                const double a3 = double(A[size_t(rowmap[r + 12]) * NP + r0 + col]);
-                acc += a0 * vec[r] + a1 * vec[r + 4] + a2 * vec[r + 8] + a3 * vec[r + 12];
+                const double a1 = double(A[size_t(rowmap[r + W]) * NP + r0 + col]);
+                const double a2 = double(A[size_t(rowmap[r + 2 * W]) * NP + r0 + col]);
+                const double a3 = double(A[size_t(rowmap[r + 3 * W]) * NP + r0 + col]);
+                acc += a0 * vec[r] + a1 * vec[r + W] + a2 * vec[r + 2 * W] + a3 * vec[r + 3 * W];
             }
-            for (; r < re; r += 4) acc += double(A[size_t(rowmap[r]) * NP + r0 + col]) * vec[r];
+            for (; r < re; r += W) acc += double(A[size_t(rowmap[r]) * NP + r0 + col]) * vec[r];
         }
         t[kLuW + grp * kLuW + col] = acc;
         __syncthreads();
-        if (tid < W) t[tid] = b[r0 + tid] - ((t[kLuW + tid] + t[2 * kLuW + tid]) + (t[3 * kLuW + tid] + t[4 * kLuW + tid]));
+        if (tid < Wb) {
+            double sum = 0.0;
+#pragma unroll
+            for (int g = 1; g <= W; ++g) sum += t[g * kLuW + tid];
+            t[tid] = b[r0 + tid] - sum;
+        }
         __syncthreads();
     };
     // the W x W diagonal block of logical rows r0.. into Db (row-major, ld kLdb)
-    auto stage = [&](int r0, int W) {
-        for (int e = tid; e < W * kLuW; e += blockDim.x) {
+    auto stage = [&](int r0, int Wb) {
+        for (int e = tid; e < Wb * kLuW; e += 64 * W) {
             const int rr = e >> 6, cc = e & 63;
-            if (cc < W) Db[rr * kLdb + cc] = double(A[size_t(rowmap[r0 + rr]) * NP + r0 + cc]);
+            if (cc < Wb) Db[rr * kLdb + cc] = double(A[size_t(rowmap[r0 + rr]) * NP + r0 + cc]);
         }
         __syncthreads();
     };
@@ -966,36 +988,36 @@ __device__ __forceinline__ void lu_solve_left_T(const T *__restrict__ A, const i
     };
     // U^T w = b: w_k = t_k / U_kk, then t_i -= U_ki w_k for i > k  (w kept in b)
     for (int ib = 0; ib < NB; ++ib) {
-        const int r0 = ib * kLuW, W = min(kLuW, NP - r0);
-        colgemv(r0, W, 0, r0, b);
-        stage(r0, W);
+        const int r0 = ib * kLuW, Wb = min(kLuW, NP - r0);
+        colgemv(r0, Wb, 0, r0, b);
+        stage(r0, Wb);
         if (tid < 64) {
-            double tv = col < W ? t[col] : 0.0;
-            for (int k = 0; k < W; ++k) {
+            double tv = col < Wb ? t[col] : 0.0;
+            for (int k = 0; k < Wb; ++k) {
                 const double wk = bcast(tv, k) / Db[k * kLdb + k];
                 if (col == k) tv = wk;
-                else if (col > k && col < W) tv -= Db[k * kLdb + col] * wk;
+                else if (col > k && col < Wb) tv -= Db[k * kLdb + col] * wk;
             }
-            if (col < W) b[r0 + col] = tv;
+            if (col < Wb) b[r0 + col] = tv;
         }
         __syncthreads();
     }
     // L^T v = w (unit diagonal): v_k = t_k, then t_i -= L_ki v_k for i < k  (v kept in b)
     for (int ib = NB - 1; ib >= 0; --ib) {
-        const int r0 = ib * kLuW, W = min(kLuW, NP - r0);
-        colgemv(r0, W, r0 + W, NP, b);
-        stage(r0, W);
+        const int r0 = ib * kLuW, Wb = min(kLuW, NP - r0);
+        colgemv(r0, Wb, r0 + Wb, NP, b);
+        stage(r0, Wb);
         if (tid < 64) {
-            double tv = col < W ? t[col] : 0.0;
-            for (int k = W - 1; k > 0; --k) {
+            double tv = col < Wb ? t[col] : 0.0;
+            for (int k = Wb - 1; k > 0; --k) {
                 const double vk = bcast(tv, k);
                 if (col < k) tv -= Db[k * kLdb + col] * vk;
             }
-            if (col < W) b[r0 + col] = tv;
+            if (col < Wb) b[r0 + col] = tv;
         }
         __syncthreads();
     }
-    for (int i = tid; i < NP; i += blockDim.x) z[rowmap[i]] = b[i];
+    for (int i = tid; i < NP; i += 64 * W) z[rowmap[i]] = b[i];
     __syncthreads();
 }
 

@@ -1,12 +1,12 @@
-// Host orchestration: slot pool, admission, the step-attempt loop and harvest.
+// Host orchestration: slot pool, admission, the integration launches and harvest.
 //
-// Every loop iteration performs one step attempt for every running slot:
-//   k_factor   (slots whose Newton matrix is stale)
-//   k_newton   x 4 (slots still iterating)
-//   k_control  (accept / reject / order selection, next attempt queued)
-// The slot lists are compacted on the device every attempt.  The host reads
-// the running and finished counts back every `check_every` attempts, copies
-// finished results out, and refills freed slots with pending cells.
+// Cells are admitted into slots and queued on the device; a launch of the
+// persistent integration kernel lets every workgroup carry one queued cell
+// after another to its end (integrate.hip).  The launch returns when the queue
+// is empty, when its time is up (the server looks for new requests, a batch
+// solve for errors), or when a workgroup runs idle while cells still wait on
+// the host for a slot; the host then reads the counts, copies finished results
+// out, and refills freed slots with pending cells.
 #include "engine.hpp"
 
 #include <atomic>
@@ -122,13 +122,10 @@ Engine::~Engine() {
         else
             (void)hipFree(base_);
     }
-    if (h_cnt_) (void)hipHostFree(h_cnt_);
+    if (h_q_) (void)hipHostFree(h_q_);
     if (h_fin_) (void)hipHostFree(h_fin_);
     if (h_admit_slots_) (void)hipHostFree(h_admit_slots_);
     if (h_admit_cells_) (void)hipHostFree(h_admit_cells_);
-    if (ev_lists_) (void)hipEventDestroy(ev_lists_);
-    if (ev_side_) (void)hipEventDestroy(ev_side_);
-    if (side_) (void)hipStreamDestroy(side_);
 }
 
 // Factor storage per slot: FP64-sized in both forms, since an FP32-LU cell can
@@ -137,9 +134,9 @@ size_t Engine::bytes_per_slot(const DeviceNet &dn, int prec) {
     (void)prec;
     const size_t S = dn.S, R = dn.R, NP = dn.NP;
     return sizeof(SlotCtl) + 5 * sizeof(double) + R * sizeof(double) + kDRows * S * sizeof(double) +
-           6 * S * sizeof(double) + size_t(std::max(dn.nnzJ, 1)) * sizeof(double) + lu_bytes(int(NP), ABDF_PREC_FP64) +
+           5 * S * sizeof(double) + size_t(std::max(dn.nnzJ, 1)) * sizeof(double) + lu_bytes(int(NP), ABDF_PREC_FP64) +
            dinv_bytes(int(NP), ABDF_PREC_FP64) +
-           NP * sizeof(int32_t) + 7 * sizeof(int32_t) + sizeof(long long);
+           NP * sizeof(int32_t) + 4 * sizeof(int32_t) + sizeof(long long);
 }
 
 int Engine::set_options(const abdf_options &o, std::string &err, double *atol_host) {
@@ -179,18 +176,17 @@ namespace {
 // The slot arrays of n slots in the order init lays them out (each part
 // 256-byte aligned).
 struct Layout {
-    size_t bytes[22];
-    static constexpr int kParts = 22;
+    static constexpr int kParts = 20;
+    size_t bytes[kParts];
     Layout(const DeviceNet &dn, size_t n) {
         const size_t S = dn.S, R = dn.R, NP = dn.NP;
         const size_t lu_stride = lu_bytes(int(NP), ABDF_PREC_FP64), dinv_stride = dinv_bytes(int(NP), ABDF_PREC_FP64);
         const size_t b[kParts] = {
             n * sizeof(SlotCtl), n * 5 * sizeof(double), n * R * sizeof(double), n * kDRows * S * sizeof(double),
             n * S * sizeof(double), n * S * sizeof(double), n * S * sizeof(double), n * S * sizeof(double),
-            n * S * sizeof(double), n * S * sizeof(double), n * size_t(std::max(dn.nnzJ, 1)) * sizeof(double),
-            n * lu_stride, n * dinv_stride, n * NP * sizeof(int32_t), 3 * n * sizeof(int32_t),
-            3 * n * sizeof(int32_t), 3 * n * sizeof(int32_t), n * sizeof(int32_t), kCountSlots * sizeof(int32_t),
-            n * sizeof(int32_t), n * sizeof(long long), S * sizeof(double)};
+            n * S * sizeof(double), n * size_t(std::max(dn.nnzJ, 1)) * sizeof(double),
+            n * lu_stride, n * dinv_stride, n * NP * sizeof(int32_t), n * sizeof(int32_t), n * sizeof(int32_t),
+            n * sizeof(int32_t), sizeof(SlotQueue), n * sizeof(int32_t), n * sizeof(long long), S * sizeof(double)};
         for (int i = 0; i < kParts; ++i) bytes[i] = b[i];
     }
     size_t total() const {
@@ -224,25 +220,23 @@ int Engine::layout(int nslots, void *base, std::string &err) {
     s_.phi = static_cast<double *>(part[1]);
     s_.k = static_cast<double *>(part[2]);
     s_.D = static_cast<double *>(part[3]);
-    s_.x = static_cast<double *>(part[4]);
-    s_.d = static_cast<double *>(part[5]);
-    s_.psi = static_cast<double *>(part[6]);
-    s_.scl = static_cast<double *>(part[7]);
-    s_.xJ = static_cast<double *>(part[8]);
-    s_.rb = static_cast<double *>(part[9]);
-    s_.jval = static_cast<double *>(part[10]);
-    s_.lu = part[11];
-    s_.dinv = part[12];
+    s_.xJ = static_cast<double *>(part[4]);
+    s_.x = static_cast<double *>(part[5]);
+    s_.d = static_cast<double *>(part[6]);
+    s_.psi = static_cast<double *>(part[7]);
+    s_.rb = static_cast<double *>(part[8]);
+    s_.jval = static_cast<double *>(part[9]);
+    s_.lu = part[10];
+    s_.dinv = part[11];
     s_.lu_stride = lu_bytes(int(NP), ABDF_PREC_FP64);
     s_.dinv_stride = dinv_bytes(int(NP), ABDF_PREC_FP64);
-    s_.perm = static_cast<int32_t *>(part[13]);
-    s_.act = static_cast<int32_t *>(part[14]);
-    s_.lul = static_cast<int32_t *>(part[15]);
-    s_.nol = static_cast<int32_t *>(part[16]);
-    s_.fin = static_cast<int32_t *>(part[17]);
-    s_.cnt = static_cast<int32_t *>(part[18]);
-    d_admit_slots_ = static_cast<int32_t *>(part[19]);
-    d_admit_cells_ = static_cast<long long *>(part[20]);
+    s_.perm = static_cast<int32_t *>(part[12]);
+    s_.fifo = static_cast<int32_t *>(part[13]);
+    s_.held = static_cast<int32_t *>(part[14]);
+    s_.fin = static_cast<int32_t *>(part[15]);
+    s_.q = static_cast<SlotQueue *>(part[16]);
+    d_admit_slots_ = static_cast<int32_t *>(part[17]);
+    d_admit_cells_ = static_cast<long long *>(part[18]);
     s_.lu_reuse = lu_reuse_;
     s_.max_order = max_order_;
     s_.h0 = h0_;
@@ -253,17 +247,11 @@ int Engine::layout(int nslots, void *base, std::string &err) {
     for (int j = 0; j < 5; ++j) s_.phi_exp[j] = phi_exp_[j];
     s_.atol_sp = nullptr;
     if (atol_sp_) {
-        HIP_TRY(hipMemcpy(part[21], atol_sp_, S * sizeof(double), hipMemcpyHostToDevice));
-        s_.atol_sp = static_cast<const double *>(part[21]);
+        HIP_TRY(hipMemcpy(part[19], atol_sp_, S * sizeof(double), hipMemcpyHostToDevice));
+        s_.atol_sp = static_cast<const double *>(part[19]);
     }
     lds_admit_ = admit_lds(dn_);
-    lds_factor_ = factor_lds(dn_, ABDF_PREC_FP64);
-    lds_factor32_ = factor_lds(dn_, ABDF_PREC_FP32_LU);
-    lds_newton_ = newton_lds(dn_);
-    lds_solve_ = solve_lds(dn_);
-    lds_solve32_ = solve_lds32(dn_);
-    if (dn_.NP > 512 || lds_admit_ > kMaxLds || lds_factor_ > kMaxLds || lds_newton_ > kMaxLds ||
-        lds_solve32_ > kMaxLds) {
+    if (dn_.NP > 512 || lds_admit_ > kMaxLds || integrate_lds(dn_, prec_) > kMaxLds) {
         err = "network too large for one workgroup's LDS";
         return ABDF_E_ARG;
     }
@@ -271,14 +259,8 @@ int Engine::layout(int nslots, void *base, std::string &err) {
     hipDeviceProp_t prop;
     if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess && prop.multiProcessorCount > 0)
         cus = prop.multiProcessorCount;
-    const bool f32 = prec_ == ABDF_PREC_FP32_LU;
-    grid_factor64_max_ = cus * resident_per_cu(0, ABDF_PREC_FP64, lds_factor_);
-    grid_solve64_max_ = cus * resident_per_cu(2, ABDF_PREC_FP64, lds_solve_);
-    grid_factor_max_ = f32 ? cus * resident_per_cu(0, prec_, lds_factor32_) : grid_factor64_max_;
-    grid_newton_max_ = cus * newton_rhs_resident_per_cu(dn_, prec_, lds_newton_);
-    grid_solve_max_ = f32 ? cus * resident_per_cu(2, prec_, lds_solve_) : grid_solve64_max_;
-    grid_solve_ref_max_ = cus * resident_per_cu(4, prec_, lds_solve32_);
-    grid_adj_solve_max_ = cus * resident_per_cu(3, prec_, adj_solve_lds(dn_));
+    grid_max_ = cus * integrate_resident_per_cu(dn_, prec_);
+    grid_reverse_max_ = cus * reverse_resident_per_cu(dn_);
     n_free_ = 0;
     for (int i = nslots - 1; i >= 0; --i) free_[n_free_++] = i;
     (void)n;
@@ -303,11 +285,8 @@ int Engine::init(int nslots, std::string &err, bool cache_workspace) {
     free_ = free_store_.data();
     int rc = layout(nslots, base_, err);
     if (rc != ABDF_OK) return rc;
-    HIP_TRY(hipMemset(s_.cnt, 0, kCountSlots * sizeof(int32_t)));
-    HIP_TRY(hipHostMalloc(reinterpret_cast<void **>(&h_cnt_), kCountSlots * sizeof(int32_t), hipHostMallocDefault));
-    HIP_TRY(hipStreamCreateWithFlags(&side_, hipStreamNonBlocking));
-    HIP_TRY(hipEventCreateWithFlags(&ev_lists_, hipEventDisableTiming));
-    HIP_TRY(hipEventCreateWithFlags(&ev_side_, hipEventDisableTiming));
+    HIP_TRY(hipMemset(s_.q, 0, sizeof(SlotQueue)));
+    HIP_TRY(hipHostMalloc(reinterpret_cast<void **>(&h_q_), sizeof(SlotQueue), hipHostMallocDefault));
     HIP_TRY(hipHostMalloc(reinterpret_cast<void **>(&h_fin_), n * sizeof(int32_t), hipHostMallocDefault));
     HIP_TRY(hipHostMalloc(reinterpret_cast<void **>(&h_admit_slots_), n * sizeof(int32_t), hipHostMallocDefault));
     HIP_TRY(hipHostMalloc(reinterpret_cast<void **>(&h_admit_cells_), n * sizeof(long long), hipHostMallocDefault));
@@ -323,7 +302,7 @@ int Engine::init_external(int nslots, void *base, size_t bytes, const HostBuffer
     base_ = base;
     base_bytes_ = bytes;
     free_ = hb.free_list;
-    h_cnt_ = hb.cnt;
+    h_q_ = hb.queue;
     h_fin_ = hb.fin;
     h_admit_slots_ = hb.admit_slots;
     h_admit_cells_ = hb.admit_cells;
@@ -331,7 +310,11 @@ int Engine::init_external(int nslots, void *base, size_t bytes, const HostBuffer
 }
 
 int Engine::reset_counts(hipStream_t st, std::string &err) {
-    HIP_TRY(launch_fill_i32(s_.cnt, 0, kCountSlots, st));
+    HIP_TRY(launch_fill_i32(reinterpret_cast<int32_t *>(s_.q), 0, kQueueInts, st));
+    held_seen_ = 0;
+    for (unsigned long long &t : ticks_seen_) t = 0;
+    launch_ = 0;
+    bound_ = 0;
     return ABDF_OK;
 }
 
@@ -344,7 +327,7 @@ int Engine::admit_cells(const AdmitArgs &a, hipStream_t st, std::string &err) {
     if (a.count <= 0) return ABDF_OK;
     TraceRange tr("abdf admit");
     hipEvent_t t0 = timer_begin(st);
-    HIP_TRY(launch_admit(s_, dn_, a, ring_, lds_admit_, st));
+    HIP_TRY(launch_admit(s_, dn_, a, lds_admit_, st));
     timer_end(ABDF_PROF_ADMIT, t0, st);
     bound_ += a.count;
     return ABDF_OK;
@@ -379,80 +362,40 @@ int Engine::admit(const BatchIO &io, const abdf_options &opt, long long &next, h
     return admit_cells(a, st, err);
 }
 
-int Engine::newton_iterations(int which, hipStream_t st, std::string &err) {
-    for (int m = 0; m < s_.newton_maxiter; ++m) {
-        hipEvent_t t0 = timer_begin(st);
-        HIP_TRY(launch_newton_rhs(s_, dn_, ring_, which, std::min(bound_, grid_newton_max_), lds_newton_, st));
-        timer_end(which == kListNoFactor ? ABDF_PROF_RHS_SIDE : ABDF_PROF_RHS, t0, st);
-        t0 = timer_begin(st);
-        HIP_TRY(launch_newton_solve(s_, dn_, ring_, which, std::min(bound_, grid_solve_max_),
-                                    std::min(bound_, grid_solve_ref_max_), lds_solve_, lds_solve32_, st));
-        timer_end(which == kListNoFactor ? ABDF_PROF_NEWTON_SIDE : ABDF_PROF_NEWTON, t0, st);
-    }
-    return ABDF_OK;
+// One launch of a persistent kernel over the occupied slots.
+IntegrateArgs Engine::next_launch(double ms, bool stop_on_idle) {
+    IntegrateArgs a{};
+    a.held_limit = held_seen_;
+    a.ticks = (unsigned long long)(ms * 1e5);   // the device's constant clock: 100 MHz
+    a.launch = ++launch_;
+    a.stop_on_idle = stop_on_idle;
+    a.prof = !ext_ && Profiler::on();
+    return a;
 }
 
-hipError_t Engine::control(hipStream_t st) {
-    return method_ == ABDF_METHOD_ESDIRK5 ? launch_control_rk(s_, ring_, bound_, st)
-                                          : launch_control(s_, dn_, ring_, bound_, st);
-}
-
-// Below this many occupied slots an attempt runs on one stream.
-constexpr int kSplitMinSlots = 32;
-
-// One step attempt.  The slots whose factorisation is current iterate on the
-// side stream while the others are factored on st: the factorisation kernel is
-// LDS-bound at a few workgroups per CU and leaves CUs idle in its last round,
-// which the side stream's kernels fill.  Control waits for both streams.
-int Engine::attempt(hipStream_t st, std::string &err) {
+int Engine::integrate(double ms, bool stop_on_idle, hipStream_t st, std::string &err) {
     if (bound_ <= 0) return ABDF_OK;
-    TraceRange tr("abdf attempt");
-    if (bound_ < kSplitMinSlots || !side_) {
-        // a handful of cells: launch latency dominates, one stream
-        hipEvent_t t0 = timer_begin(st);
-        HIP_TRY(launch_factor(s_, dn_, ring_, std::min(bound_, grid_factor_max_),
-                              std::min(bound_, grid_factor64_max_), lds_factor_, lds_factor32_, st));
-        timer_end(ABDF_PROF_FACTOR, t0, st);
-        if (prec_ == ABDF_PREC_FP64) {
-            t0 = timer_begin(st);
-            HIP_TRY(launch_newton_fused(s_, dn_, ring_, kListAll, bound_, std::max(lds_newton_, lds_solve_), st));
-            timer_end(ABDF_PROF_NEWTON, t0, st);
-        } else {
-            int rc = newton_iterations(kListAll, st, err);
-            if (rc != ABDF_OK) return rc;
-        }
-        t0 = timer_begin(st);
-        HIP_TRY(control(st));
-        timer_end(ABDF_PROF_CONTROL, t0, st);
-        ring_ = (ring_ + 1) % 3;
-        return ABDF_OK;
-    }
-    HIP_TRY(hipEventRecord(ev_lists_, st));
-    hipEvent_t t0 = timer_begin(st);
-    HIP_TRY(launch_factor(s_, dn_, ring_, std::min(bound_, grid_factor_max_), std::min(bound_, grid_factor64_max_),
-                          lds_factor_, lds_factor32_, st));
-    timer_end(ABDF_PROF_FACTOR, t0, st);
-    HIP_TRY(hipStreamWaitEvent(side_, ev_lists_, 0));
-    int rc = newton_iterations(kListNoFactor, side_, err);
-    if (rc != ABDF_OK) return rc;
-    HIP_TRY(hipEventRecord(ev_side_, side_));
-    rc = newton_iterations(kListFactor, st, err);
-    if (rc != ABDF_OK) return rc;
-    HIP_TRY(hipStreamWaitEvent(st, ev_side_, 0));
-    t0 = timer_begin(st);
-    HIP_TRY(control(st));
-    timer_end(ABDF_PROF_CONTROL, t0, st);
-    ring_ = (ring_ + 1) % 3;
+    TraceRange tr("abdf integrate");
+    grid_ = std::min(bound_, grid_max_);
+    HIP_TRY(launch_integrate(s_, dn_, next_launch(ms, stop_on_idle), grid_, st));
     return ABDF_OK;
 }
 
 int Engine::sync_counts(hipStream_t st, int &nfin, std::string &err) {
     TraceRange tr("abdf poll");
-    HIP_TRY(hipMemcpyAsync(h_cnt_, s_.cnt, kCountSlots * sizeof(int32_t), hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipMemcpyAsync(h_q_, s_.q, sizeof(SlotQueue), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
     flush_timers();
-    nfin = h_cnt_[6];
-    bound_ = h_cnt_[ring_];
+    nfin = h_q_->nfin;
+    held_seen_ = h_q_->held_tail;
+    // a phase's time: the mean over the launch's workgroups
+    static const int kind[kPhases] = {ABDF_PROF_CONTROL, ABDF_PROF_FACTOR,    ABDF_PROF_RHS,
+                                      ABDF_PROF_NEWTON,  ABDF_PROF_ADJ_SOLVE, ABDF_PROF_ADJ_STEP};
+    for (int p = 0; p < kPhases; ++p) {
+        const unsigned long long d = h_q_->ticks[p] - ticks_seen_[p];
+        ticks_seen_[p] = h_q_->ticks[p];
+        if (d > 0 && grid_ > 0) Profiler::add(kind[p], double(d) * 1e-5 / grid_);
+    }
     return ABDF_OK;
 }
 
@@ -467,66 +410,57 @@ int Engine::harvest(HarvestArgs h, hipStream_t st, std::string &err) {
     timer_end(ABDF_PROF_HARVEST, t0, st);
     HIP_TRY(hipStreamSynchronize(st));
     for (int i = 0; i < nfin; ++i) free_[n_free_++] = h_fin_[i];
+    bound_ -= nfin;
     return ABDF_OK;
 }
 
+// Longest launch of a batch solve or sweep (it returns earlier when its cells
+// are done): long enough that the workgroups' wait for the slowest at its end
+// (one attempt, up to 2 ms) is nothing.
+constexpr double kBatchLaunchMs = 500.0;
+
 int Engine::solve(const BatchIO &io, const abdf_options &opt, hipStream_t st, std::string &err) {
     TraceRange tr("abdf solve");
-    ring_ = 0;
-    bound_ = 0;
     long long next = 0;
     {
-        // the slot lists start empty: an external workspace keeps the previous
-        // call's contents, and an engine's earlier sweep leaves its last ring's counts
+        // the queue starts empty: an external workspace keeps the previous
+        // call's contents, and an engine's earlier sweep leaves its counts
         int rc0 = reset_counts(st, err);
         if (rc0 != ABDF_OK) return rc0;
     }
-    const int check_every = std::max(1, opt.check_every);
     int rc = admit(io, opt, next, st, err);
     if (rc != ABDF_OK) return rc;
-    int since_poll = 0;
-    while (true) {
-        if (bound_ > 0) {
-            rc = attempt(st, err);
-            if (rc != ABDF_OK) return rc;
-            ++since_poll;
-        }
-        if (bound_ == 0 || since_poll >= check_every) {
-            since_poll = 0;
-            int nfin = 0;
-            rc = sync_counts(st, nfin, err);
-            if (rc != ABDF_OK) return rc;
-            HarvestArgs h{};
-            h.count = nfin;
-            h.x_out = io.x_out;
-            h.status = io.status;
-            h.stats = io.stats;
-            rc = harvest(h, st, err);
-            if (rc != ABDF_OK) return rc;
-            rc = admit(io, opt, next, st, err);
-            if (rc != ABDF_OK) return rc;
-            if (bound_ == 0 && next >= io.n_cells) break;
-        }
+    while (bound_ > 0) {
+        rc = integrate(kBatchLaunchMs, next < io.n_cells, st, err);
+        if (rc != ABDF_OK) return rc;
+        int nfin = 0;
+        rc = sync_counts(st, nfin, err);
+        if (rc != ABDF_OK) return rc;
+        HarvestArgs h{};
+        h.count = nfin;
+        h.x_out = io.x_out;
+        h.status = io.status;
+        h.stats = io.stats;
+        rc = harvest(h, st, err);
+        if (rc != ABDF_OK) return rc;
+        rc = admit(io, opt, next, st, err);
+        if (rc != ABDF_OK) return rc;
     }
-    HIP_TRY(hipStreamSynchronize(st));
     flush_timers();
     return ABDF_OK;
 }
 
-int Engine::reverse(const AdjIO &io, int check_every, hipStream_t st, std::string &err) {
+int Engine::reverse(const AdjIO &io, hipStream_t st, std::string &err) {
     TraceRange tr("abdf reverse sweep");
-    ring_ = 0;
-    bound_ = 0;
     {
         int rc0 = reset_counts(st, err);
         if (rc0 != ABDF_OK) return rc0;
     }
-    const size_t lds_adj = adj_lds(dn_), lds_adj_solve = adj_solve_lds(dn_);
-    if (lds_adj > kMaxLds || lds_adj_solve > kMaxLds) {
+    const size_t lds_adj = adj_lds(dn_);
+    if (lds_adj > kMaxLds || reverse_lds(dn_) > kMaxLds) {
         err = "network too large for one workgroup's LDS";
         return ABDF_E_ARG;
     }
-    check_every = std::max(1, check_every);
     long long next = 0;
     auto admit_rev = [&]() -> int {
         const long long want = std::min<long long>(static_cast<long long>(n_free_), io.n_cells - next);
@@ -539,7 +473,7 @@ int Engine::reverse(const AdjIO &io, int check_every, hipStream_t st, std::strin
         HIP_TRY(hipMemcpyAsync(d_admit_cells_, h_admit_cells_, want * sizeof(long long), hipMemcpyHostToDevice, st));
         AdjArgs a{int(want), d_admit_slots_, d_admit_cells_, io.phi, io.dLdx, io.status};
         hipEvent_t t0 = timer_begin(st);
-        HIP_TRY(launch_adj_admit(s_, dn_, a, ring_, lds_adj, st));
+        HIP_TRY(launch_adj_admit(s_, dn_, a, lds_adj, st));
         timer_end(ABDF_PROF_ADMIT, t0, st);
         next += want;
         bound_ += int(want);
@@ -547,43 +481,25 @@ int Engine::reverse(const AdjIO &io, int check_every, hipStream_t st, std::strin
     };
     int rc = admit_rev();
     if (rc != ABDF_OK) return rc;
-    int since = 0;
-    while (true) {
-        if (bound_ > 0) {
-            TraceRange ts("abdf reverse step");
+    while (bound_ > 0) {
+        grid_ = std::min(bound_, grid_reverse_max_);
+        HIP_TRY(launch_reverse(s_, dn_, next_launch(kBatchLaunchMs, next < io.n_cells), grid_, st));
+        int nfin = 0;
+        rc = sync_counts(st, nfin, err);
+        if (rc != ABDF_OK) return rc;
+        if (nfin > 0) {
+            HIP_TRY(hipMemcpyAsync(h_fin_, s_.fin, nfin * sizeof(int32_t), hipMemcpyDeviceToHost, st));
+            AdjHarvestArgs h{nfin, s_.fin, io.g_cell, io.dx0, io.dphi};
             hipEvent_t t0 = timer_begin(st);
-            HIP_TRY(launch_factor(s_, dn_, ring_, std::min(bound_, grid_factor_max_),
-                                  std::min(bound_, grid_factor64_max_), lds_factor_, lds_factor32_, st));
-            timer_end(ABDF_PROF_FACTOR, t0, st);
-            t0 = timer_begin(st);
-            HIP_TRY(launch_adj_solve(s_, ring_, std::min(bound_, grid_adj_solve_max_), lds_adj_solve, st));
-            timer_end(ABDF_PROF_ADJ_SOLVE, t0, st);
-            t0 = timer_begin(st);
-            HIP_TRY(launch_adj_step(s_, dn_, ring_, bound_, lds_adj, st));
-            timer_end(ABDF_PROF_ADJ_STEP, t0, st);
-            ring_ = (ring_ + 1) % 3;
-            ++since;
+            HIP_TRY(launch_adj_harvest(s_, dn_, h, st));
+            timer_end(ABDF_PROF_HARVEST, t0, st);
+            HIP_TRY(hipStreamSynchronize(st));
+            for (int i = 0; i < nfin; ++i) free_[n_free_++] = h_fin_[i];
+            bound_ -= nfin;
         }
-        if (bound_ == 0 || since >= check_every) {
-            since = 0;
-            int nfin = 0;
-            rc = sync_counts(st, nfin, err);
-            if (rc != ABDF_OK) return rc;
-            if (nfin > 0) {
-                HIP_TRY(hipMemcpyAsync(h_fin_, s_.fin, nfin * sizeof(int32_t), hipMemcpyDeviceToHost, st));
-                AdjHarvestArgs h{nfin, s_.fin, io.g_cell, io.dx0, io.dphi};
-                hipEvent_t t0 = timer_begin(st);
-                HIP_TRY(launch_adj_harvest(s_, dn_, h, st));
-                timer_end(ABDF_PROF_HARVEST, t0, st);
-                HIP_TRY(hipStreamSynchronize(st));
-                for (int i = 0; i < nfin; ++i) free_[n_free_++] = h_fin_[i];
-            }
-            rc = admit_rev();
-            if (rc != ABDF_OK) return rc;
-            if (bound_ == 0 && next >= io.n_cells) break;
-        }
+        rc = admit_rev();
+        if (rc != ABDF_OK) return rc;
     }
-    HIP_TRY(hipStreamSynchronize(st));
     flush_timers();
     return ABDF_OK;
 }

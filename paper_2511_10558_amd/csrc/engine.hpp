@@ -38,7 +38,7 @@ struct AdjIO {
 // Host buffers of an engine that allocates nothing itself: the caller keeps
 // them (static storage) and they hold up to max_slots slots.
 struct HostBuffers {
-    int32_t *cnt;            // [kCountSlots]
+    SlotQueue *queue;
     int32_t *fin;            // [max_slots]
     int32_t *admit_slots;    // [max_slots]
     long long *admit_cells;  // [max_slots]
@@ -57,7 +57,7 @@ struct Profiler {
 };
 
 // A pool of device slots for one network.  Cells are admitted into free
-// slots, integrated by the step-attempt loop, and harvested when finished;
+// slots, integrated by persistent launches, and harvested when finished;
 // freed slots are refilled from the pending cells (continuous batching).
 class Engine {
   public:
@@ -68,9 +68,8 @@ class Engine {
     // on this device when large enough and returned to it by the destructor.
     int init(int nslots, std::string &err, bool cache_workspace = false);
     // Lays out `nslots` slots in caller-provided device memory (`bytes` at
-    // `base`) with the host buffers `hb`, allocating nothing: no side stream,
-    // no events, no kernel timers; the counters are cleared by a kernel on the
-    // solve's stream.  Returns an abdf_status.
+    // `base`) with the host buffers `hb`, allocating nothing: no events, no
+    // kernel timers; the counters are cleared by a kernel on the solve's stream.  Returns an abdf_status.
     int init_external(int nslots, void *base, size_t bytes, const HostBuffers &hb, std::string &err);
     // Device bytes of the workspace of n slots (as init lays it out).
     static size_t workspace_bytes(const DeviceNet &dn, long long n);
@@ -98,19 +97,20 @@ class Engine {
     int solve(const BatchIO &io, const abdf_options &opt, hipStream_t st, std::string &err);
 
     // Reverse sweep of the recorded steps (the slots' tape pointers must be set).
-    int reverse(const AdjIO &io, int check_every, hipStream_t st, std::string &err);
+    int reverse(const AdjIO &io, hipStream_t st, std::string &err);
 
     // Building blocks of a driver loop (batch solve, server, adjoint).
     int nslots() const { return s_.nslots; }
     int free_count() const { return n_free_; }
-    // Slots on the current attempt list (an upper bound until the next sync_counts).
+    // Occupied slots: admitted and not yet harvested.
     int running() const { return bound_; }
     int take_slot() { return free_[--n_free_]; }
     // Admits a.count cells into the slots a.slots (taken with take_slot).
     int admit_cells(const AdmitArgs &a, hipStream_t st, std::string &err);
-    // One step attempt of every running slot (ESDIRK: one stage).
-    int attempt(hipStream_t st, std::string &err);
-    // Waits for the stream and reads the running and finished counts.
+    // One launch of the integration: it ends when no slot is left to run, after
+    // about `ms` milliseconds, or (stop_on_idle) when a workgroup runs idle.
+    int integrate(double ms, bool stop_on_idle, hipStream_t st, std::string &err);
+    // Waits for the stream and reads the finished count.
     int sync_counts(hipStream_t st, int &nfin, std::string &err);
     // Copies the nfin finished slots out (h.count = nfin, h.slots = the finished
     // list), waits, and returns the slots to the free list; their ids stay
@@ -120,7 +120,6 @@ class Engine {
     const int32_t *device_finished_list() const { return s_.fin; }
     Slots &slots() { return s_; }
     const DeviceNet &net() const { return dn_; }
-    int ring() const { return ring_; }
     // kernel timers: an event before a launch, and after it with its family
     hipEvent_t timer_begin(hipStream_t st);
     void timer_end(int kind, hipEvent_t a, hipStream_t st);
@@ -130,8 +129,7 @@ class Engine {
 
   private:
     int admit(const BatchIO &io, const abdf_options &opt, long long &next, hipStream_t st, std::string &err);
-    int newton_iterations(int which, hipStream_t st, std::string &err);
-    hipError_t control(hipStream_t st);   // the method's control kernel
+    IntegrateArgs next_launch(double ms, bool stop_on_idle);
 
     const HostNetwork &net_;
     const DeviceNet &dn_;
@@ -153,22 +151,19 @@ class Engine {
     int layout(int nslots, void *base, std::string &err);
     int32_t *d_admit_slots_ = nullptr;
     long long *d_admit_cells_ = nullptr;
-    int32_t *h_cnt_ = nullptr;          // pinned [kCountSlots]
-    hipStream_t side_ = nullptr;        // Newton iterations of slots that do not factor (default priority)
-    hipEvent_t ev_lists_ = nullptr, ev_side_ = nullptr;
+    SlotQueue *h_q_ = nullptr;          // pinned copy of the device's queue counters
+    unsigned long long held_seen_ = 0, ticks_seen_[kPhases] = {};
+    int32_t launch_ = 0;                // launches since the counters were reset
     int32_t *h_fin_ = nullptr;          // pinned [nslots]
     int32_t *h_admit_slots_ = nullptr;  // pinned [nslots]
     long long *h_admit_cells_ = nullptr;
     std::vector<int32_t> free_store_;  // free-slot stack when the engine owns it
     int32_t *free_ = nullptr;
     int n_free_ = 0;
-    int ring_ = 0;
     int bound_ = 0;
-    // LDS and persistent grid sizes; the *64 / unsuffixed FP64 values serve the
-    // FP64 variants, *32 / the main grids the FP32 ones in FP32-LU engines
-    size_t lds_admit_ = 0, lds_factor_ = 0, lds_factor32_ = 0, lds_newton_ = 0, lds_solve_ = 0, lds_solve32_ = 0;
-    int grid_factor_max_ = 256, grid_newton_max_ = 512, grid_solve_max_ = 1024;
-    int grid_factor64_max_ = 256, grid_solve64_max_ = 1024, grid_solve_ref_max_ = 512, grid_adj_solve_max_ = 1024;
+    size_t lds_admit_ = 0;
+    int grid_ = 0;                      // workgroups of the last launch
+    int grid_max_ = 256, grid_reverse_max_ = 256;
     // kernel timers of launches not yet read back
     struct Pending { int kind; hipEvent_t a, b; };
     std::vector<Pending> pending_;

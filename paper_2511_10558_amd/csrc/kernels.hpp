@@ -55,50 +55,36 @@ struct PhysArgs {
     const double *T, *nH, *Av, *zeta, *G0;
 };
 
+// One launch of the persistent integration (or reverse sweep).
+struct IntegrateArgs {
+    unsigned long long held_limit;   // slots put back by earlier launches: Slots::q->held_tail as last read
+    unsigned long long ticks;        // workgroups put their cell back once this many 100 MHz ticks have passed
+    int32_t launch;                  // number of this launch (> 0)
+    int32_t stop_on_idle;            // cells wait on the host: end as soon as a workgroup finds the queue empty
+    int32_t prof;                    // accumulate SlotQueue::ticks
+};
+
 // LDS bytes per kernel for a network
 inline size_t admit_lds(const DeviceNet &n) { return sizeof(double) * (4 * size_t(n.S) + n.R); }
-inline size_t newton_lds(const DeviceNet &n) {
-    return sizeof(double) * (2 * size_t(n.S) + n.R);
-}
-inline size_t solve_lds(const DeviceNet &n) { return sizeof(double) * 2 * size_t(n.NP); }
-// the refining FP32 variant also holds the second solution, x_J and the
-// scratch of the Jacobian-vector product
-inline size_t solve_lds32(const DeviceNet &n) {
-    return sizeof(double) * (3 * size_t(n.NP) + n.S + n.R);
-}
-size_t factor_lds(const DeviceNet &n, int prec);
+size_t integrate_lds(const DeviceNet &n, int prec);
+size_t reverse_lds(const DeviceNet &n);
 
-hipError_t launch_admit(const Slots &s, const DeviceNet &n, const AdmitArgs &a, int ring, size_t lds, hipStream_t st);
-// FP32-LU engines launch the FP32 variant (grid, lds32) and then the FP64 one
-// for the slots that fell back (grid64, lds); FP64 engines only the latter (grid).
-hipError_t launch_factor(const Slots &s, const DeviceNet &n, int ring, int grid, int grid64, size_t lds,
-                         size_t lds32, hipStream_t st);
-// Newton kernels take the slot list to work on (kListAll / kListFactor / kListNoFactor).
-hipError_t launch_newton_rhs(const Slots &s, const DeviceNet &n, int ring, int which, int grid, size_t lds,
-                             hipStream_t st);
-// FP32-LU engines launch the plain FP32 (grid), the refining FP32 (grid_ref,
-// lds_ref) and the FP64 (grid64) variants; FP64 engines only the last (grid).
-// All Newton iterations of the listed slots in one launch (FP64 engines; LDS:
-// the larger of newton_lds and solve_lds).
-hipError_t launch_newton_fused(const Slots &s, const DeviceNet &n, int ring, int which, int grid, size_t lds,
-                               hipStream_t st);
-hipError_t launch_newton_solve(const Slots &s, const DeviceNet &n, int ring, int which, int grid, int grid_ref,
-                               size_t lds, size_t lds_ref, hipStream_t st);
-hipError_t launch_control(const Slots &s, const DeviceNet &n, int ring, int grid, hipStream_t st);
-// ESDIRK: the next stage (or the step decision) of every active slot
-hipError_t launch_control_rk(const Slots &s, int ring, int grid, hipStream_t st);
+hipError_t launch_admit(const Slots &s, const DeviceNet &n, const AdmitArgs &a, size_t lds, hipStream_t st);
+// Integrates (sweeps) the queued slots with grid workgroups.
+hipError_t launch_integrate(const Slots &s, const DeviceNet &n, const IntegrateArgs &a, int grid, hipStream_t st);
+hipError_t launch_reverse(const Slots &s, const DeviceNet &n, const IntegrateArgs &a, int grid, hipStream_t st);
+// Their workgroups resident per CU.
+int integrate_resident_per_cu(const DeviceNet &n, int prec);
+int reverse_resident_per_cu(const DeviceNet &n);
 hipError_t launch_harvest(const Slots &s, const HarvestArgs &h, hipStream_t st);
 
-hipError_t launch_adj_admit(const Slots &s, const DeviceNet &n, const AdjArgs &a, int ring, size_t lds, hipStream_t st);
-hipError_t launch_adj_solve(const Slots &s, int ring, int grid, size_t lds, hipStream_t st);
-hipError_t launch_adj_step(const Slots &s, const DeviceNet &n, int ring, int grid, size_t lds, hipStream_t st);
+hipError_t launch_adj_admit(const Slots &s, const DeviceNet &n, const AdjArgs &a, size_t lds, hipStream_t st);
 hipError_t launch_adj_harvest(const Slots &s, const DeviceNet &n, const AdjHarvestArgs &h, hipStream_t st);
 hipError_t launch_grad_sum(const double *g_cell, long long cells, int R, double *out, hipStream_t st);
 // dL/dphi [cells][5] (T, n_H, A_V, zeta, G0) from per-cell dL/dlog alpha [cells][R].
 hipError_t launch_phys_grad(const DeviceNet &n, const PhysArgs &p, long long cells, const double *g_cell,
                             double *out, hipStream_t st);
 inline size_t adj_lds(const DeviceNet &n) { return sizeof(double) * (2 * size_t(n.S) + n.R); }
-inline size_t adj_solve_lds(const DeviceNet &n) { return sizeof(double) * (2 * size_t(n.NP) + 5 * 64 + 64 * 65); }
 
 hipError_t launch_rates(const DeviceNet &n, const PhysArgs &p, long long cells, double *k, hipStream_t st);
 // The standalone right-hand side: the kernel and grid for a batch (host
@@ -123,16 +109,8 @@ hipError_t launch_lu_solve(int n, int NP, long long batch, const double *LU, con
                            void *W, int32_t *permW, void *dinv, hipStream_t st);
 size_t dinv_bytes(int NP, int prec);
 size_t lu_bytes(int NP, int prec);
-// Workgroups resident per CU of the factor (which = 0), Newton residual (1),
-// Newton solve (2), transposed adjoint solve (3) or refining FP32 Newton
-// solve (4) kernel.
-int resident_per_cu(int which, int prec, size_t lds);
-// Workgroups per CU of the kernel launch_newton_rhs runs for this network
-// (lds: the LDS of the non-streaming kernel, used when it is that one).
-int newton_rhs_resident_per_cu(const DeviceNet &n, int prec, size_t lds);
 hipError_t launch_selftest(int *bad, hipStream_t st);
 hipError_t launch_fill_i32(int32_t *v, int32_t value, int n, hipStream_t st);
-size_t lu_work_lds(int NP, int prec);
 
 // Largest dynamic LDS one workgroup may use on the device.
 constexpr size_t kMaxLds = 160 * 1024;

@@ -528,6 +528,7 @@ const DeviceNet *HostNetwork::device_tables(std::string &err) const {
     d->nbw = (NP + 63) / 64;
     d->n_sgroup = int32_t(sg_base.size());
     d->sg_maxlen = 0;
+    d->sg_total = int32_t(sg_ent.size());
     for (int32_t w : sg_len) d->sg_maxlen = std::max(d->sg_maxlen, w & 0xffffff);
     d->nnzJ = int32_t(jcol.size());
     d->nterm = int32_t(jt_coef.size());

@@ -38,6 +38,7 @@ struct DeviceNet {
     // brings the groups down to kRhsResidentGroups.
     int32_t n_sgroup = 0;
     int32_t sg_maxlen = 0;         // longest lane of any group
+    int32_t sg_total = 0;          // entries with padding
     int32_t *sg_base = nullptr;    // [n_sgroup] first entry of the group
     int32_t *sg_len = nullptr;     // [n_sgroup] longest lane | pairwise steps (ceil log2 of the widest species) << 24
     int32_t *sg_lane = nullptr;    // [64 n_sgroup] entries of the lane

@@ -20,7 +20,7 @@ namespace {
 constexpr int kMaxDevices = 16;
 
 struct HostState {
-    int32_t cnt[kCountSlots];
+    SlotQueue queue;
     int32_t fin[kNoAllocMaxSlots];
     int32_t admit_slots[kNoAllocMaxSlots];
     long long admit_cells[kNoAllocMaxSlots];
@@ -53,7 +53,7 @@ int noalloc_workspace(int device, void **scratch_ptr, HostBuffers *host, std::st
     }
     *scratch_ptr = g_scratch[device];
     HostState &h = g_host[device];
-    *host = HostBuffers{h.cnt, h.fin, h.admit_slots, h.admit_cells, h.free_list, h.atol, kNoAllocMaxSlots};
+    *host = HostBuffers{&h.queue, h.fin, h.admit_slots, h.admit_cells, h.free_list, h.atol, kNoAllocMaxSlots};
     return ABDF_OK;
 }
 

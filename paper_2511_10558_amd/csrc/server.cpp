@@ -355,8 +355,9 @@ void Server::run() {
     std::string err;
     int rc = hipSetDevice(device_) == hipSuccess ? ABDF_OK : ABDF_E_DEVICE;
     if (rc != ABDF_OK) err = "hipSetDevice in the server worker";
-    const int check_every = std::max(1, opt_.solve.check_every);
-    int since = 0;
+    // how long a launch may run before the worker looks for new requests and
+    // hands out finished ones: about 4 ms per unit of check_every (default 4)
+    const double launch_ms = 4.0 * std::max(1, opt_.solve.check_every);
     t_last_ = now();
     while (rc == ABDF_OK) {
         std::vector<uint64_t> cancels;
@@ -375,13 +376,9 @@ void Server::run() {
             rc = admit_pending(err);
             if (rc != ABDF_OK) break;
         }
-        if (eng_->running() > 0) {
-            rc = eng_->attempt(st_, err);
+        if (occupied_ > 0) {
+            rc = eng_->integrate(launch_ms, !pending_.empty(), st_, err);
             if (rc != ABDF_OK) break;
-            ++since;
-        }
-        if (occupied_ > 0 && (eng_->running() == 0 || since >= check_every)) {
-            since = 0;
             rc = collect(err);
         }
     }
