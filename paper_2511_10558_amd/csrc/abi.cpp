@@ -557,10 +557,9 @@ abdf_status abdf_lu_factor(int32_t n, int64_t batch, double *A, int32_t *perm, i
     CHECK_DEV(perm, "perm");
     if (info) CHECK_DEV(info, "info");
     const int NP = (n + 15) / 16 * 16;
-    const size_t elt = precision == ABDF_PREC_FP32_LU ? sizeof(float) : sizeof(double);
     void *W = nullptr, *dinv = nullptr;
     int32_t *permW = nullptr;
-    hipError_t e = hipMalloc(&W, size_t(batch) * NP * NP * elt);
+    hipError_t e = hipMalloc(&W, size_t(batch) * abdf::lu_bytes(NP, precision));
     if (e == hipSuccess) e = hipMalloc(&dinv, size_t(batch) * abdf::dinv_bytes(NP, precision));
     if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&permW), size_t(batch) * NP * sizeof(int32_t));
     hipStream_t st = static_cast<hipStream_t>(stream);
@@ -582,7 +581,7 @@ abdf_status abdf_lu_solve(int32_t n, int64_t batch, const double *LU, const int3
     const int NP = (n + 15) / 16 * 16;
     void *W = nullptr, *dinv = nullptr;
     int32_t *permW = nullptr;
-    hipError_t e = hipMalloc(&W, size_t(batch) * NP * NP * sizeof(double));
+    hipError_t e = hipMalloc(&W, size_t(batch) * abdf::lu_bytes(NP, ABDF_PREC_FP64));
     if (e == hipSuccess) e = hipMalloc(&dinv, size_t(batch) * abdf::dinv_bytes(NP, ABDF_PREC_FP64));
     if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&permW), size_t(batch) * NP * sizeof(int32_t));
     hipStream_t st = static_cast<hipStream_t>(stream);

@@ -16,7 +16,7 @@ template <int NT = kBlock>
 __device__ inline void cell_rates(const DeviceNet &n, const double *phi, double *k) {
     const double T = phi[0], nH = phi[1], Av = phi[2], zeta = phi[3], G0 = phi[4];
     const double T300 = T / 300.0;
-    for (int r = threadIdx.x; r < n.R; r += NT) {
+    for (int r = thread_id(); r < n.R; r += NT) {
         const int t = n.rx_type[r];
         const double a = n.alpha[r];
         double v;
@@ -38,8 +38,8 @@ __device__ inline void cell_rates(const DeviceNet &n, const double *phi, double 
 template <int NT = kBlock>
 __device__ __forceinline__ void species_gather(const DeviceNet &n, const double *v, double *out) {
     constexpr int kB = 8;
-    const int lane = threadIdx.x & 63;
-    for (int g = threadIdx.x >> 6; g < n.n_sgroup; g += NT / 64) {
+    const int tid = thread_id(), lane = tid & 63;
+    for (int g = wave_of(tid); g < n.n_sgroup; g += NT / 64) {
         const int mine = n.sg_lane[g * 64 + lane];
         const int lw = n.sg_len[g];
         const int L = lw & 0xffffff, steps = lw >> 24;
@@ -78,7 +78,7 @@ __device__ __forceinline__ void cell_rhs(const DeviceNet &n, const double *__res
                                 double *rate, double *f) {
     // kU reactions per thread per pass, their loads issued before any use
     constexpr int kU = kWide ? 6 : 4;
-    for (int r0 = threadIdx.x; r0 < n.R; r0 += kU * NT) {
+    for (int r0 = thread_id(); r0 < n.R; r0 += kU * NT) {
         int ab[kU];
         double kr[kU];
 #pragma unroll
@@ -107,7 +107,7 @@ __device__ __forceinline__ void cell_rhs(const DeviceNet &n, const double *__res
 template <int NT>
 __device__ __forceinline__ void cell_jvp(const DeviceNet &n, const double *__restrict__ k, const double *x,
                                          const double *y, double *drate, double *out) {
-    for (int r0 = threadIdx.x; r0 < n.R; r0 += 4 * NT) {
+    for (int r0 = thread_id(); r0 < n.R; r0 += 4 * NT) {
         int ab[4];
         double kr[4];
 #pragma unroll
@@ -136,7 +136,7 @@ __device__ __forceinline__ void jacobian_values(const DeviceNet &n, const double
                                                 double *jv) {
     // a nonzero's terms are loaded four at a time before any is used; the sum
     // still runs term by term in order
-    for (int e = threadIdx.x; e < n.nnzJ; e += NT) {
+    for (int e = thread_id(); e < n.nnzJ; e += NT) {
         double v = 0.0;
         const int t0 = n.jterm_ptr[e], t1 = n.jterm_ptr[e + 1];
         for (int tb = t0; tb < t1; tb += 4) {

@@ -205,12 +205,31 @@ __device__ __forceinline__ void wave_argmax_ballot(double &v, int &k) {
     v = m;
 }
 
+// threadIdx.x, opaque to the compiler: what a phase of a persistent kernel
+// derives from it (addresses above all) is formed in that phase, instead of
+// being hoisted out of the loop over attempts into registers that the
+// factorisation and the solves need (hoisted, they pushed some 290 registers of
+// the kernel into scratch memory, whose reloads wait for every load in flight).
+__device__ __forceinline__ int thread_id() {
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
+// The wave's number of a thread id, as a scalar.
+__device__ __forceinline__ int wave_of(int tid) { return __builtin_amdgcn_readfirstlane(tid >> 6); }
+
+// A value that is the same on every lane, as a scalar.
+__device__ __forceinline__ double uniform(double v) {
+    return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(v)),
+                            __builtin_amdgcn_readfirstlane(__double2loint(v)));
+}
+
 // v of the lane N places on in its row of 16.
 template <int N>
 __device__ __forceinline__ double row_rotate(double v) {
     const int lo = __double2loint(v), hi = __double2hiint(v);
-    return __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, 0x120 + N, 0xf, 0xf, false),
-                            __builtin_amdgcn_update_dpp(lo, lo, 0x120 + N, 0xf, 0xf, false));
+    return __hiloint2double(__builtin_amdgcn_mov_dpp(hi, 0x120 + N, 0xf, 0xf, true),
+                            __builtin_amdgcn_mov_dpp(lo, 0x120 + N, 0xf, 0xf, true));
 }
 
 // Sum over each row of 16 lanes, on all of them: the pairwise sums of lanes 8,

@@ -39,6 +39,9 @@
 #include "device_common.hpp"
 #include "device_lu.hpp"
 
+#include <type_traits>
+#include <utility>
+
 namespace abdf {
 
 constexpr int kLuW = 64;          // block-column width
@@ -148,6 +151,10 @@ __device__ __forceinline__ void wave_lds_order() {
     asm volatile("" ::: "memory");
 }
 
+// Leading dimension of the stored factors: rows 4 kB apart would put a block
+// column's rows in the same few channels of the L2 and of the memory.
+__host__ __device__ constexpr int lu_ld(int NP) { return NP % 128 == 0 ? NP + 16 : NP; }
+
 // Elements of the per-matrix inverse diagonal blocks.
 template <typename T>
 __host__ __device__ constexpr size_t lu2_dinv_elems(int NP) {
@@ -166,7 +173,7 @@ __host__ __device__ constexpr size_t lu2_dinv_elems(int NP) {
 template <typename T, int NW>
 __device__ __forceinline__ void diag_inverses(const T *Cb, int W, T *D, T *Xb, T *Yb, T *Tb) {
     constexpr int HALF = 32 * NW;   // threads of each triangle
-    const int tid = threadIdx.x;
+    const int tid = thread_id();
     const bool upper = tid >= HALF;
     const int h = tid % HALF;
     const int nb = W / 16;
@@ -220,7 +227,7 @@ __device__ __forceinline__ void diag_inverses(const T *Cb, int W, T *D, T *Xb, T
     {
         using Mt = Mfma<T>;
         using acc_t = typename Mt::acc_t;
-        const int wave = tid >> 6, lane = tid & 63, lr = lane & 15, lg = lane >> 4;
+        const int wave = wave_of(tid), lane = tid & 63, lr = lane & 15, lg = lane >> 4;
         for (int d = 1; d < nb; ++d) {
             for (int blk = wave; blk < 2 * (nb - d); blk += NW) {
                 const bool up = blk >= nb - d;
@@ -282,7 +289,7 @@ struct DenseSource {
     const T *A;
     int NP;
     struct Row { int32_t off; };
-    __device__ __forceinline__ Row row(int r, int) const { return {r * NP}; }
+    __device__ __forceinline__ Row row(int r, int) const { return {r * lu_ld(NP)}; }
     __device__ __forceinline__ T entry(const Row &w, int, int col) const { return A[w.off + col]; }
 };
 
@@ -295,9 +302,8 @@ __device__ __forceinline__ void lu_factor_left(T *__restrict__ A, int NP, int32_
     using M = Mfma<T>;
     using acc_t = typename M::acc_t;
     using v4 = typename V4<T>::type;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int g = lane >> 4, lc = lane & 15;
-    const int RT = NP / 16;
+    const int tid0 = thread_id();
+    const int RT = NP / 16, lda = lu_ld(NP);
     const int NB = (NP + kLuW - 1) / kLuW;
 
     const LuLds<T, W> lds(NP, smem);
@@ -308,12 +314,16 @@ __device__ __forceinline__ void lu_factor_left(T *__restrict__ A, int NP, int32_
     T *P = Cb;                                             // [NP][kPanLd] (panel)
     T *U12 = P + size_t(NP) * kPanLd;                      // [16][kU12Ld]
 
-    for (int i = tid; i < NP; i += (64 * W)) perm[i] = i;
-    if (tid < 16) dpos[tid] = 0;      // every position read from it stays in the panel
-    if (tid == 0) rwave[2] = 0x7fffffff;
+    for (int i = tid0; i < NP; i += (64 * W)) perm[i] = i;
+    if (tid0 < 16) dpos[tid0] = 0;      // every position read from it stays in the panel
+    if (tid0 == 0) rwave[2] = 0x7fffffff;
     __syncthreads();
 
     for (int j = 0; j < NB; ++j) {
+        // anew for each block column: the accumulators need the registers that
+        // its many LDS addresses would take
+        const int tid = thread_id(), lane = tid & 63, wave = wave_of(tid);
+        const int g = lane >> 4, lc = lane & 15;
         const int c0 = j * kLuW;
         const int Wj = min(kLuW, NP - c0);
         const int CTj = Wj / 16;
@@ -409,7 +419,7 @@ __device__ __forceinline__ void lu_factor_left(T *__restrict__ A, int NP, int32_
                             for (int v = 0; v < 4; ++v) acc[s][ct][v] = Ub[(16 * tr + M::row(lane, v)) * kLdb + 16 * ct + lc];
                 }
                 if (rt >= 4 * (i + 1) && rt < RT) {
-                    const T *Lrow = A + size_t(perm[16 * rt + lc]) * NP + r0;
+                    const T *Lrow = A + size_t(perm[16 * rt + lc]) * lda + r0;
                     v4 a[4];
 #pragma unroll
                     for (int kk = 0; kk < 4; ++kk) a[kk] = *reinterpret_cast<const v4 *>(Lrow + 16 * kk + 4 * g);
@@ -805,131 +815,224 @@ __device__ __forceinline__ void lu_factor_left(T *__restrict__ A, int NP, int32_
                     if (ct < CTj)
 #pragma unroll
                         for (int v = 0; v < 4; ++v)
-                            A[size_t(sto[16 * rt + M::row(lane, v)]) * NP + c0 + 16 * ct + lc] = acc[s][ct][v];
+                            A[size_t(sto[16 * rt + M::row(lane, v)]) * lda + c0 + 16 * ct + lc] = acc[s][ct][v];
         }
         __syncthreads();
         diag_inverses<T, W>(Cb, Wj, dinv + size_t(j) * 2 * kLuW * kLuW, Xb, Ub, Xb + lu2_stage_rows(NP) * kLdb);
         __syncthreads();
     }
-    for (int i = tid; i < NP; i += (64 * W)) perm_out[i] = perm[i];
-    if (tid == 0 && info) *info = rwave[2] == 0x7fffffff ? 0 : rwave[2];
+    for (int i = tid0; i < NP; i += (64 * W)) perm_out[i] = perm[i];
+    if (tid0 == 0 && info) *info = rwave[2] == 0x7fffffff ? 0 : rwave[2];
+}
+
+// The order in which a solve reads the tiles of a factor of NB block rows: per
+// block row of L (downwards), then of U (upwards), its tiles off the diagonal
+// from left to right, then the inverse of its diagonal block's triangle.
+template <int NB>
+struct SolveOrder {
+    static constexpr int total = NB * (NB + 1);
+    static constexpr bool up(int q) { return q >= total / 2; }
+    static constexpr int row(int q) {   // block rows done before tile q's
+        int e = q % (total / 2), m = 0;
+        while (e > m) e -= ++m;
+        return m;
+    }
+    static constexpr int ib(int q) { return up(q) ? NB - 1 - row(q) : row(q); }
+    static constexpr int jb(int q) {    // == ib: the diagonal block's inverse
+        const int e = q % (total / 2) - row(q) * (row(q) + 1) / 2;
+        return up(q) ? (e < row(q) ? ib(q) + 1 + e : ib(q)) : e;
+    }
+};
+
+template <typename F, int... I>
+__device__ __forceinline__ void static_for_each(F &&f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+// f(0), ..., f(N - 1), each index a constant
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F &&f) {
+    static_for_each(static_cast<F &&>(f), std::make_integer_sequence<int, N>{});
 }
 
 // Solves (P^T L U) z = b for one matrix factored by lu_factor_left, with the
-// NT threads of a per-cell workgroup.  Row r of the factors is storage row
-// rowmap[r] (identity if rowmap is null); y starts as b[bperm[.]] (both are
-// perm in the solver).  b[NP] (LDS, FP64) is read, the
-// solution is left in y[NP] (LDS); t is 64 doubles of LDS scratch.  Factor
-// entries are widened to FP64; the arithmetic is FP64.
-// N (even, N <= NP) is the order of the padded matrix: its rows and columns
-// from N on are the identity's, in the matrix and so in its factors (no
-// pivot is taken from them before column N), and b is zero there; the
+// NT threads of a workgroup.  Row r of the factors is storage row rowmap[r]
+// (identity if rowmap is null); y starts as b[bperm[.]] (both are perm in the
+// solver).  b[NP] (LDS, FP64) is read, the solution is left in y[NP] (LDS); t is
+// 64 doubles of LDS scratch.  Factor entries are widened to FP64; the
+// arithmetic is FP64.
+// N (even, 64 (NB - 1) < N <= NP) is the order of the padded matrix: its rows
+// and columns from N on are the identity's, in the matrix and so in its factors
+// (no pivot is taken from them before column N), and b is zero there; the
 // products then stop at N and y keeps its zeros past N.  N = NP for factors
 // of unknown padding.
-template <typename T, int NT>
-__device__ __forceinline__ void lu_solve_left(const T *__restrict__ A, const T *__restrict__ dinv, const int32_t *__restrict__ rowmap,
-                              const int32_t *__restrict__ bperm, int NP, int N, const double *b, double *y, double *t) {
-    const int tid = threadIdx.x;
-    const int lane16 = tid & 15, row16 = tid >> 4;   // 16 lanes per row
-    constexpr int RP = NT / 16, P = kLuW / RP;        // rows per pass, passes
-    constexpr int VW = 16 / int(sizeof(T));           // factor entries per 16-byte load
+//
+// The factor is read once as a stream of 64 x 64 tiles.  No tile's address
+// depends on a result, so each thread keeps its parts of the next kDepth tiles
+// in flight in registers while it works on the current one: one workgroup
+// alone must draw what its compute unit can (kDepth x 32 kB in FP64 against
+// some 2 us of latency), where loads issued block by block wait for every
+// block's reductions and barriers.  The stream is unrolled (NB is a constant):
+// a tile is then its loads at constant offsets from its rows' addresses, its
+// products with solution entries held in registers, and nothing else.  With the
+// position in the stream computed at run time the bookkeeping took longer
+// than the loads: 19.3 us a solve of 200 species against 12.7, 69 against 64 of
+// 500 with 256 cells at once; block by block it was 26.8 and 115 us.  What is
+// left is the chain of two reductions and two barriers a block row (some
+// 0.7 us) at 200 species, and at 500 the memory as well (2.3 MB a solve).
+// 16 lanes to a row, 16 bytes (VW entries) a load.
+template <typename T, int NT, int NB, int kDepth>
+__device__ __forceinline__ void lu_solve_left(const T *__restrict__ A, int lda, const T *__restrict__ dinv,
+                                              const int32_t *rowmap, const int32_t *bperm, int NP, int N,
+                                              const double *b, double *y, double *t) {
+    using Order = SolveOrder<NB>;
+    constexpr int VW = 16 / int(sizeof(T));          // factor entries per 16-byte load
+    constexpr int H = kLuW / (16 * VW);              // loads per row of a tile
+    constexpr int RP = NT / 16, P = kLuW / RP;       // rows per pass, rows per thread
+    const int tid = thread_id();
+    const int lane16 = tid & 15, row16 = tid >> 4;
+    const int Wl = N - kLuW * (NB - 1);              // rows of the last block
     for (int i = tid; i < NP; i += NT) y[i] = b[bperm[i]];
-    __syncthreads();
-    const int NB = (N + kLuW - 1) / kLuW;
-    // t[rr] = y[r0 + rr] - A_row(r0 + rr)[c_begin, c_end) . vec for rr < W (rows through
-    // rowmap); 16 lanes per row, each thread carries P rows, whose 16-byte
-    // loads are in flight together.
-    auto gemv_off = [&](int r0, int W, int c_begin, int c_end, const double *vec) {
-        // rows past W (last block) read row W - 1 again; their sums are not stored.
-        // No load sits behind a condition, so all of them are in flight together.
-        const T *rows[P];
+    // where this thread's rows of each block row begin, at its first column
+    // (rows past the end read the last one again)
+    uint32_t off[NB][P];
+#pragma unroll
+    for (int ib = 0; ib < NB; ++ib)
 #pragma unroll
         for (int p = 0; p < P; ++p) {
-            const int rr = min(row16 + RP * p, W - 1);
-            rows[p] = A + size_t(rowmap ? rowmap[r0 + rr] : r0 + rr) * NP;
+            const int rr = row16 + RP * p, r = ib * kLuW + (ib == NB - 1 ? min(rr, Wl - 1) : rr);
+            off[ib][p] = uint32_t(rowmap ? rowmap[r] : r) * uint32_t(lda) + VW * lane16;
         }
-        double acc[P] = {};
-        // VW entries (16 bytes) per lane and load: c_begin is a multiple of 64
-        // and rows are 64-byte aligned.  FP32 entries past c_end (at most
-        // three, within the row) meet zeros of vec.
-        for (int c = c_begin + VW * lane16; c < c_end; c += 16 * VW) {
-            double yv[VW];
+    T buf[kDepth][P][H][VW];
+    // The zero side of a triangle's inverse is not read: a column there loads the
+    // 16 bytes that hold the diagonal instead (a cache line the row needs
+    // anyway) and contributes nothing.
+    auto load = [&](auto qc) __attribute__((always_inline)) {
+        constexpr int q = decltype(qc)::value;
+        constexpr int ib = Order::ib(q), jb = Order::jb(q);
+        constexpr bool up = Order::up(q), last = ib == NB - 1;
+        T(&dst)[P][H][VW] = buf[q % kDepth];
 #pragma unroll
-            for (int k = 0; k < VW; ++k) yv[k] = vec[c + k];
-            T a[P][VW];
+        for (int p = 0; p < P; ++p)
 #pragma unroll
-            for (int p = 0; p < P; ++p) __builtin_memcpy(a[p], __builtin_assume_aligned(rows[p] + c, 16), 16);
-#pragma unroll
-            for (int p = 0; p < P; ++p) {
-                if constexpr (VW == 2)
-                    acc[p] += double(a[p][0]) * yv[0] + double(a[p][1]) * yv[1];
-                else
-                    acc[p] += (double(a[p][0]) * yv[0] + double(a[p][1]) * yv[1]) +
-                              (double(a[p][2]) * yv[2] + double(a[p][3]) * yv[3]);
-            }
-        }
-#pragma unroll
-        for (int p = 0; p < P; ++p) {
-            const double a = row_sum(acc[p]);
-            const int rr = row16 + RP * p;
-            if (lane16 == 0 && rr < W) t[rr] = y[r0 + rr] - a;
-        }
-    };
-    // D is the 64 x 64 inverse of the block's unit lower (lower) or upper
-    // triangle.  Its other triangle is zero and is not read: a column on that
-    // side of the diagonal loads the diagonal entry instead (a cache line the
-    // row needs anyway) and contributes nothing.  Rows past W read row W - 1
-    // again and are not stored.
-    auto gemv_diag = [&](int r0, int W, const T *D, bool lower) {
-        double acc[P] = {};
-        for (int c = VW * lane16; c < W; c += 16 * VW) {
-            double tv[VW];
-#pragma unroll
-            for (int k = 0; k < VW; ++k) tv[k] = c + k < W ? t[c + k] : 0.0;
-            // the 16 bytes holding the diagonal stand in for those on the zero side
-            T a[P][VW];
-#pragma unroll
-            for (int p = 0; p < P; ++p) {
-                const int rr = min(row16 + RP * p, W - 1), dq = rr & ~(VW - 1);
-                __builtin_memcpy(a[p], __builtin_assume_aligned(D + rr * kLuW + (lower ? min(c, dq) : max(c, dq)), 16),
-                                 16);
-            }
-#pragma unroll
-            for (int p = 0; p < P; ++p) {
-                const int rr = min(row16 + RP * p, W - 1);
-                double term[VW];
-#pragma unroll
-                for (int k = 0; k < VW; ++k) {
-                    const bool use = c + k < W && (lower ? c + k <= rr : c + k >= rr);
-                    term[k] = use ? double(a[p][k]) * tv[k] : 0.0;
+            for (int h = 0; h < H; ++h) {
+                const T *src;
+                if constexpr (jb == ib) {
+                    const int rr = last ? min(row16 + RP * p, Wl - 1) : row16 + RP * p;
+                    const int c = VW * lane16 + 16 * VW * h, dq = rr & ~(VW - 1);
+                    src = dinv + (ib * 2 + (up ? 1 : 0)) * (kLuW * kLuW) + uint32_t(rr * kLuW + (up ? max(c, dq) : min(c, dq)));
+                } else if constexpr (jb == NB - 1) {
+                    // the last block column may be narrower
+                    const int c = jb * kLuW + VW * lane16 + 16 * VW * h;
+                    src = A + (off[ib][p] - VW * lane16 + min(c, NP - VW));
+                } else {
+                    src = A + off[ib][p] + (jb * kLuW + 16 * VW * h);
                 }
-                if constexpr (VW == 2)
-                    acc[p] += term[0] + term[1];
-                else
-                    acc[p] += (term[0] + term[1]) + (term[2] + term[3]);
+                __builtin_memcpy(dst[p][h], __builtin_assume_aligned(src, 16), 16);
+            }
+    };
+    double yv[NB][H][VW];     // this lane's columns of the solution so far
+    double acc[P] = {};
+    auto use = [&](auto qc) __attribute__((always_inline)) {
+        // products and sums exactly as written
+#pragma clang fp contract(off)
+        constexpr int q = decltype(qc)::value;
+        constexpr int ib = Order::ib(q), jb = Order::jb(q), r0 = ib * kLuW;
+        constexpr bool up = Order::up(q), last = ib == NB - 1;
+        T(&a)[P][H][VW] = buf[q % kDepth];
+        if constexpr (jb != ib) {
+#pragma unroll
+            for (int h = 0; h < H; ++h) {
+                // FP32 entries past N (at most three, within the row) meet zeros of y
+                const bool in = jb < NB - 1 || VW * lane16 + 16 * VW * h < Wl;
+#pragma unroll
+                for (int p = 0; p < P; ++p) {
+                    double s;
+                    s = fma(double(a[p][h][0]), yv[jb][h][0], double(a[p][h][1]) * yv[jb][h][1]);
+                    if constexpr (VW == 4)
+                        s = s + fma(double(a[p][h][2]), yv[jb][h][2], double(a[p][h][3]) * yv[jb][h][3]);
+                    if (in) acc[p] += s;
+                }
+            }
+            return;
+        }
+        const int W = last ? Wl : kLuW;
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            const double s = row_sum(acc[p]);
+            acc[p] = 0.0;
+            const int r = row16 + RP * p;
+            if (lane16 == 0 && r < W) t[r] = y[r0 + r] - s;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int h = 0; h < H; ++h) {
+            const int c = VW * lane16 + 16 * VW * h;
+            if (c < W) {
+                double tv[VW];
+#pragma unroll
+                for (int k = 0; k < VW; ++k) tv[k] = c + k < W ? t[c + k] : 0.0;
+#pragma unroll
+                for (int p = 0; p < P; ++p) {
+                    const int r = min(row16 + RP * p, W - 1);
+                    double term[VW];
+#pragma unroll
+                    for (int k = 0; k < VW; ++k) {
+                        const bool in = c + k < W && (up ? c + k >= r : c + k <= r);
+                        term[k] = in ? double(a[p][h][k]) * tv[k] : 0.0;
+                    }
+                    if constexpr (VW == 2)
+                        acc[p] += term[0] + term[1];
+                    else
+                        acc[p] += (term[0] + term[1]) + (term[2] + term[3]);
+                }
             }
         }
 #pragma unroll
         for (int p = 0; p < P; ++p) {
-            const double a = row_sum(acc[p]);
-            const int rr = row16 + RP * p;
-            if (lane16 == 0 && rr < W) y[r0 + rr] = a;
+            const double s = row_sum(acc[p]);
+            acc[p] = 0.0;
+            const int r = row16 + RP * p;
+            if (lane16 == 0 && r < W) y[r0 + r] = s;
         }
+        __syncthreads();
+        // the block's entries for the block rows to come
+#pragma unroll
+        for (int h = 0; h < H; ++h)
+#pragma unroll
+            for (int k = 0; k < VW; ++k) {
+                const int c = VW * lane16 + 16 * VW * h + k;
+                yv[ib][h][k] = y[r0 + (last ? min(c, NP - r0 - 1) : c)];
+            }
     };
-    for (int ib = 0; ib < NB; ++ib) {
-        const int r0 = ib * kLuW, W = min(kLuW, N - r0);
-        gemv_off(r0, W, 0, r0, y);
-        __syncthreads();
-        gemv_diag(r0, W, dinv + size_t(ib) * 2 * kLuW * kLuW, true);
-        __syncthreads();
+    static_for<(kDepth < Order::total ? kDepth : Order::total)>([&](auto q) __attribute__((always_inline)) { load(q); });
+    __syncthreads();
+    static_for<Order::total>([&](auto qc) __attribute__((always_inline)) {
+        constexpr int q = decltype(qc)::value;
+        use(qc);
+        if constexpr (q + kDepth < Order::total) load(std::integral_constant<int, q + kDepth>{});
+        // the tiles in flight stay those named above
+        __builtin_amdgcn_sched_barrier(0);
+    });
+}
+
+// The same for any order: NB = ceil(N / 64).
+template <typename T, int NT, int kDepth>
+__device__ __forceinline__ void lu_solve_left(const T *__restrict__ A, int lda, const T *__restrict__ dinv,
+                                              const int32_t *rowmap, const int32_t *bperm, int NP, int N,
+                                              const double *b, double *y, double *t) {
+#define ABDF_SOLVE(NB) \
+    case NB: lu_solve_left<T, NT, NB, kDepth>(A, lda, dinv, rowmap, bperm, NP, N, b, y, t); break
+    switch ((N + kLuW - 1) / kLuW) {
+        ABDF_SOLVE(1);
+        ABDF_SOLVE(2);
+        ABDF_SOLVE(3);
+        ABDF_SOLVE(4);
+        ABDF_SOLVE(5);
+        ABDF_SOLVE(6);
+        ABDF_SOLVE(7);
+        default: lu_solve_left<T, NT, 8, kDepth>(A, lda, dinv, rowmap, bperm, NP, N, b, y, t); break;
     }
-    for (int ib = NB - 1; ib >= 0; --ib) {
-        const int r0 = ib * kLuW, W = min(kLuW, N - r0);
-        gemv_off(r0, W, r0 + W, N, y);
-        __syncthreads();
-        gemv_diag(r0, W, dinv + size_t(ib) * 2 * kLuW * kLuW + kLuW * kLuW, false);
-        __syncthreads();
-    }
+#undef ABDF_SOLVE
 }
 
 
@@ -946,22 +1049,22 @@ __device__ __forceinline__ void lu_solve_left(const T *__restrict__ A, const T *
 template <typename T, int W>
 __device__ __forceinline__ void lu_solve_left_T(const T *__restrict__ A, const int32_t *__restrict__ rowmap, int NP,
                                                 double *b, double *z, double *t, double *Db) {
-    const int tid = threadIdx.x;
-    const int col = tid & 63, grp = tid >> 6;
-    const int NB = (NP + kLuW - 1) / kLuW;
+    const int tid = thread_id();
+    const int col = tid & 63, grp = wave_of(tid);
+    const int NB = (NP + kLuW - 1) / kLuW, lda = lu_ld(NP);
     // t[col] = b[r0 + col] - sum_{r in [rb, re)} A_logical[r][r0 + col] vec[r]
     auto colgemv = [&](int r0, int Wb, int rb, int re, const double *vec) {
         double acc = 0.0;
         if (col < Wb) {
             int r = rb + grp;
             for (; r + 3 * W < re; r += 4 * W) {
-                const double a0 = double(A[size_t(rowmap[r]) * NP + r0 + col]);
-                const double a1 = double(A[size_t(rowmap[r + W]) * NP + r0 + col]);
-                const double a2 = double(A[size_t(rowmap[r + 2 * W]) * NP + r0 + col]);
-                const double a3 = double(A[size_t(rowmap[r + 3 * W]) * NP + r0 + col]);
+                const double a0 = double(A[size_t(rowmap[r]) * lda + r0 + col]);
+                const double a1 = double(A[size_t(rowmap[r + W]) * lda + r0 + col]);
+                const double a2 = double(A[size_t(rowmap[r + 2 * W]) * lda + r0 + col]);
+                const double a3 = double(A[size_t(rowmap[r + 3 * W]) * lda + r0 + col]);
                 acc += a0 * vec[r] + a1 * vec[r + W] + a2 * vec[r + 2 * W] + a3 * vec[r + 3 * W];
             }
-            for (; r < re; r += W) acc += double(A[size_t(rowmap[r]) * NP + r0 + col]) * vec[r];
+            for (; r < re; r += W) acc += double(A[size_t(rowmap[r]) * lda + r0 + col]) * vec[r];
         }
         t[kLuW + grp * kLuW + col] = acc;
         __syncthreads();
@@ -977,7 +1080,7 @@ __device__ __forceinline__ void lu_solve_left_T(const T *__restrict__ A, const i
     auto stage = [&](int r0, int Wb) {
         for (int e = tid; e < Wb * kLuW; e += 64 * W) {
             const int rr = e >> 6, cc = e & 63;
-            if (cc < Wb) Db[rr * kLdb + cc] = double(A[size_t(rowmap[r0 + rr]) * NP + r0 + cc]);
+            if (cc < Wb) Db[rr * kLdb + cc] = double(A[size_t(rowmap[r0 + rr]) * lda + r0 + cc]);
         }
         __syncthreads();
     };

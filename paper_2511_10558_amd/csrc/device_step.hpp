@@ -46,7 +46,7 @@ __device__ inline double growth(double err, int p) {
 // R(1)[m][j] in the order of the recurrence R[i][.] = R[i - 1][.] (i - 1 - rho .) / i,
 // then the sum over m in order.  Static loop bounds keep everything in registers.
 __device__ inline void interp_product(int q, double rho, double *RU) {
-    const int t = threadIdx.x;
+    const int t = thread_id();
     if (t >= 36) return;
     const int i = t / 6, j = t % 6;
     if (i > q || j > q) return;
@@ -134,7 +134,8 @@ __device__ __forceinline__ double wg_sum(double v, double *red) {
     v = wave_sum(v);
     if constexpr (W == 1) return v;
     __syncthreads();
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    const int t = thread_id();
+    if ((t & 63) == 0) red[t >> 6] = v;
     __syncthreads();
     double s = 0.0;
 #pragma unroll
@@ -148,7 +149,7 @@ __device__ __forceinline__ double wg_sum(double v, double *red) {
 // doubles of LDS (above 256 species), red: 4 N doubles.
 template <int W, int N>
 __device__ __forceinline__ void wg_squares(double (&v)[N], int S, double *fold, double *red) {
-    const int t = threadIdx.x;
+    const int t = thread_id();
     double a[N];
 #pragma unroll
     for (int k = 0; k < N; ++k) a[k] = v[k] * v[k];
@@ -212,14 +213,14 @@ struct SpeciesState {
 
 __device__ __forceinline__ void load_rows(const Slots &s, int slot, SpeciesState &y) {
     const double *D = s.D + size_t(slot) * kDRows * s.S;
-    const int i = threadIdx.x;
+    const int i = thread_id();
 #pragma unroll
     for (int j = 0; j < kDRows; ++j) y.v[j] = i < s.S ? D[j * s.S + i] : 0.0;
 }
 
 __device__ __forceinline__ void store_rows(const Slots &s, int slot, const SpeciesState &y) {
     double *D = s.D + size_t(slot) * kDRows * s.S;
-    const int i = threadIdx.x;
+    const int i = thread_id();
     if (i < s.S) {
 #pragma unroll
         for (int j = 0; j < kDRows; ++j) D[j * s.S + i] = y.v[j];
@@ -253,7 +254,7 @@ __device__ __forceinline__ void rescale_rows(SpeciesState &y, int q, double rho,
 template <int W>
 __device__ __forceinline__ void begin_attempt(const Slots &s, const DeviceNet &n, int slot, StepLds<W> &L,
                                               SpeciesState &y) {
-    const int i = threadIdx.x;
+    const int i = thread_id();
     const bool own = i < s.S;
     SlotCtl &cs = L.cs;
     if (threadIdx.x == 0) {
@@ -343,7 +344,7 @@ static __constant__ double kRkA[kRkStages][kRkStages] = {
 // corrector with c = h gamma.  Ends with a barrier.
 template <int W>
 __device__ __forceinline__ void begin_stage_rk(const Slots &s, int slot, StepLds<W> &L, SpeciesState &y) {
-    const int i = threadIdx.x;
+    const int i = thread_id();
     const bool own = i < s.S;
     SlotCtl &cs = L.cs;
     const int stage = cs.stage;
@@ -415,12 +416,13 @@ __device__ __forceinline__ void factor_slot(const Slots &s, const DeviceNet &n, 
     const int S = s.S, NP = s.NP;
     double *jv = s.jval + size_t(slot) * n.nnzJ;
     if (!cs.jv_valid) {
-        if (int(threadIdx.x) < S) smem[threadIdx.x] = s.xJ[size_t(slot) * S + threadIdx.x];
+        const int i = thread_id();
+        if (i < S) smem[i] = s.xJ[size_t(slot) * S + i];
         __syncthreads();
         jacobian_values<64 * W>(n, s.k + size_t(slot) * n.R, smem, jv);
         __syncthreads();
     }
-    NewtonMatrixSource<T> src{n.jmask, n.jbase, n.nbw, jv, cs.c};
+    NewtonMatrixSource<T> src{n.jmask, n.jbase, n.nbw, jv, uniform(cs.c)};
     lu_factor_left<T, W>(slot_lu<T>(s, slot), NP, s.perm + size_t(slot) * NP, slot_dinv<T>(s, slot), nullptr,
                          reinterpret_cast<unsigned char *>(smem), src);
     __syncthreads();
@@ -428,16 +430,19 @@ __device__ __forceinline__ void factor_slot(const Slots &s, const DeviceNet &n, 
 
 // ----------------------------------------------------------------- newton --
 
-// z = M^{-1} b with the slot's factors (b, z in LDS [NP]; scratch: NP row
-// indices and 64 doubles).  Ends with a barrier.
+// z = M^{-1} b with the slot's factors (b, z in LDS [NP]; scratch: 64 doubles and
+// NP row indices).  Ends with a barrier.
 template <typename T, int W>
 __device__ __forceinline__ void solve_slot(const Slots &s, int slot, const double *b, double *z, double *scratch) {
-    const int S = s.S, NP = s.NP;
+    const int S = s.S, NP = s.NP, tid = thread_id();
     int32_t *perm = reinterpret_cast<int32_t *>(scratch + kLuW);
-    if (int(threadIdx.x) < NP) perm[threadIdx.x] = s.perm[size_t(slot) * NP + threadIdx.x];
+    if (tid < NP) perm[tid] = s.perm[size_t(slot) * NP + tid];
     __syncthreads();
     const int N = min(NP, S + (S & 1));   // the padding past S is the identity's
-    lu_solve_left<T, 64 * W>(slot_lu<T>(s, slot), slot_dinv<T>(s, slot), perm, perm, NP, N, b, z, scratch);
+    // FP64: 6 tiles of 16 registers a thread in flight
+    constexpr int kDepth = sizeof(T) == sizeof(double) ? 6 : 8;
+    lu_solve_left<T, 64 * W, kDepth>(slot_lu<T>(s, slot), lu_ld(NP), slot_dinv<T>(s, slot), perm, perm, NP, N, b, z,
+                                     scratch);
 }
 
 // The convergence and divergence tests after Newton iteration m with correction
@@ -469,14 +474,14 @@ template <int W, bool kF32>
 __device__ __forceinline__ int newton_slot(const Slots &s, const DeviceNet &n, int slot, StepLds<W> &L,
                                            SpeciesState &y, double *smem, unsigned long long *t_rhs) {
     constexpr int NT = 64 * W;
-    const int S = s.S, NP = s.NP, i = threadIdx.x;
+    const int S = s.S, NP = s.NP, i = thread_id();
     const bool own = i < S;
     SlotCtl &cs = L.cs;
     double *b = smem, *z = b + NP, *z2 = z + NP;
     double *xs = kF32 ? z2 + NP : z2, *rate = xs + S;
     const double *k = s.k + size_t(slot) * n.R;
-    const double c = cs.c, c_lu = cs.c_lu, tol = cs.newton_tol;
-    const int mode = kF32 ? cs.lu_mode : kLu64;
+    const double c = uniform(cs.c), c_lu = uniform(cs.c_lu), tol = uniform(cs.newton_tol);
+    const int mode = kF32 ? __builtin_amdgcn_readfirstlane(cs.lu_mode) : kLu64;
     double eta_old = 0.0;
     int phase = kIter, m = 0;
     while (phase == kIter) {
@@ -543,7 +548,7 @@ __device__ __forceinline__ int newton_slot(const Slots &s, const DeviceNet &n, i
 template <int W>
 __device__ __forceinline__ void control_bdf(const Slots &s, int slot, StepLds<W> &L, SpeciesState &y, int phase,
                                             double *smem) {
-    const int i = threadIdx.x, S = s.S;
+    const int i = thread_id(), S = s.S;
     const bool own = i < S;
     SlotCtl &cs = L.cs;
     const int q = cs.q;
@@ -696,7 +701,7 @@ __device__ __forceinline__ void control_bdf(const Slots &s, int slot, StepLds<W>
 // error test Y_7 - Y_6 decides the step.  Ends with a barrier.
 template <int W>
 __device__ __forceinline__ void control_rk(const Slots &s, StepLds<W> &L, SpeciesState &y, int phase, double *smem) {
-    const int i = threadIdx.x, S = s.S;
+    const int i = thread_id(), S = s.S;
     const bool own = i < S;
     SlotCtl &cs = L.cs;
     const int stage = cs.stage;

@@ -62,7 +62,7 @@ __device__ __forceinline__ int take_slot(const Slots &s, const IntegrateArgs &a,
             __hip_atomic_store(&s.q->stop, a.launch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();
-    return L.slot;
+    return __builtin_amdgcn_readfirstlane(L.slot);   // a scalar: so are the slot's addresses
 }
 
 }  // namespace
@@ -251,7 +251,7 @@ template <int NT>
 __device__ __forceinline__ void rescale_adjoint(double *L, int S, int q, double rho, double *RU) {
     interp_product(q, rho, RU);
     __syncthreads();
-    for (int i = threadIdx.x; i < S; i += NT) {
+    for (int i = thread_id(); i < S; i += NT) {
         double v[kMaxOrder + 1], w[kMaxOrder + 1];
 #pragma unroll
         for (int j = 0; j <= kMaxOrder; ++j) v[j] = j <= q ? L[j * S + i] : 0.0;
@@ -276,9 +276,9 @@ __device__ __forceinline__ void rescale_adjoint(double *L, int S, int q, double 
 template <int NT>
 __device__ __forceinline__ void jac_transpose_apply(const DeviceNet &n, const double *k, const double *xs,
                                                     const double *v, double *w, double c, double *out, int S) {
-    for (int r = threadIdx.x; r < n.R; r += NT) w[r] = nu_dot(n, v, r);
+    for (int r = thread_id(); r < n.R; r += NT) w[r] = nu_dot(n, v, r);
     __syncthreads();
-    for (int j = threadIdx.x; j < S; j += NT) {
+    for (int j = thread_id(); j < S; j += NT) {
         double jt = 0.0;
         for (int e = n.dcol_ptr[j]; e < n.dcol_ptr[j + 1]; ++e) {
             const int ent = n.dcol_ent[e];
@@ -311,7 +311,7 @@ __device__ __forceinline__ void adj_begin(const Slots &s, const DeviceNet &n, in
     double *rb = s.rb + size_t(slot) * S, *xJ = s.xJ + size_t(slot) * S, *lam_d = s.psi + size_t(slot) * S;
     const double *xt = s.tape_x + te * S;
     double *xs = smem, *ls = xs + S, *w = ls + S;
-    for (int i = threadIdx.x; i < S; i += NT) {
+    for (int i = thread_id(); i < S; i += NT) {
         double v[kDRows];
         for (int j = 0; j <= q + 2; ++j) v[j] = L[j * S + i];
         for (int j = 0; j <= q; ++j) v[j + 1] = v[j + 1] + v[j];
@@ -350,18 +350,18 @@ __device__ __forceinline__ void adj_finish(const Slots &s, const DeviceNet &n, i
         const double *x0 = s.tape_x0 + size_t(cs.cell) * S;
         const double *k = s.k + size_t(slot) * R;
         double *g = s.g + size_t(slot) * R;
-        for (int i = threadIdx.x; i < S; i += NT) {
+        for (int i = thread_id(); i < S; i += NT) {
             xs[i] = x0[i];
             l1[i] = L[S + i];
         }
         __syncthreads();
-        for (int r = threadIdx.x; r < R; r += NT) g[r] += h0 * reactant_product(n, xs, r) * nu_dot(n, l1, r);
+        for (int r = thread_id(); r < R; r += NT) g[r] += h0 * reactant_product(n, xs, r) * nu_dot(n, l1, r);
         __syncthreads();
         // dL/dx0 = lambda_0 + h0 J(x0)^T lambda_1 (dx0 first holds the second term)
         jac_transpose_apply<NT>(n, k, xs, l1, w, h0, dx0, S);
-        for (int i = threadIdx.x; i < S; i += NT) dx0[i] = L[i] + dx0[i];
+        for (int i = thread_id(); i < S; i += NT) dx0[i] = L[i] + dx0[i];
     } else {
-        for (int i = threadIdx.x; i < S; i += NT) dx0[i] = L[i];
+        for (int i = thread_id(); i < S; i += NT) dx0[i] = L[i];
     }
     __syncthreads();
     finish_slot(s, slot, cs, cs.status == kRunning ? ABDF_CELL_OK : cs.status);
@@ -384,7 +384,7 @@ __device__ __forceinline__ void adj_step(const Slots &s, const DeviceNet &n, int
     double *xs = smem, *ms = xs + S;
     double gr[kMaxOrder + 1];
     for (int j = 1; j <= q; ++j) gr[j] = bdf_gamma(j) / gq;
-    for (int i = threadIdx.x; i < S; i += NT) {
+    for (int i = thread_id(); i < S; i += NT) {
         const double lxp = lxp_g[i];
         const double m = lam_d[i] + lxp;
         xs[i] = xJ[i];
@@ -394,7 +394,7 @@ __device__ __forceinline__ void adj_step(const Slots &s, const DeviceNet &n, int
     }
     __syncthreads();
     double *g = s.g + size_t(slot) * R;
-    for (int r = threadIdx.x; r < R; r += NT) g[r] += c * reactant_product(n, xs, r) * nu_dot(n, ms, r);
+    for (int r = thread_id(); r < R; r += NT) g[r] += c * reactant_product(n, xs, r) * nu_dot(n, ms, r);
     __syncthreads();
     const int m = cs.n_steps - 1;
     const int w0 = s.tape_w0 ? s.tape_w0[cs.cell] : 0;
@@ -448,14 +448,14 @@ __global__ void __launch_bounds__(kBlock) k_adj_admit(Slots s, DeviceNet n, AdjA
     if (ok && s.win_resume) {
         // the adjoint rows and dL/dk where the previous pass (the later window) left them
         const double *wl = s.win_lam + size_t(cell) * kDRows * S;
-        for (int i = threadIdx.x; i < kDRows * S; i += kBlock) L[i] = wl[i];
-        for (int r = threadIdx.x; r < R; r += kBlock) g[r] = s.win_g[size_t(cell) * R + r];
+        for (int i = thread_id(); i < kDRows * S; i += kBlock) L[i] = wl[i];
+        for (int r = thread_id(); r < R; r += kBlock) g[r] = s.win_g[size_t(cell) * R + r];
     } else {
-        for (int i = threadIdx.x; i < S; i += kBlock) {
+        for (int i = thread_id(); i < S; i += kBlock) {
             L[i] = ok ? a.dLdx[cell * S + i] : 0.0;
             for (int j = 1; j < kDRows; ++j) L[j * S + i] = 0.0;
         }
-        for (int r = threadIdx.x; r < R; r += kBlock) g[r] = 0.0;
+        for (int r = thread_id(); r < R; r += kBlock) g[r] = 0.0;
     }
     __syncthreads();
     cell_rates(n, phi, s.k + size_t(slot) * R);
@@ -500,11 +500,11 @@ k_reverse(Slots s, DeviceNet n, IntegrateArgs a) {
                 // lambda_xp = M^{-T} (c J^T lambda_d)
                 double *b = smem, *z = b + NP, *t = z + NP, *Db = t + (1 + W) * kLuW;
                 const double *rb = s.rb + size_t(slot) * S;
-                for (int i = threadIdx.x; i < NP; i += NT) b[i] = i < S ? rb[i] : 0.0;
+                for (int i = thread_id(); i < NP; i += NT) b[i] = i < S ? rb[i] : 0.0;
                 __syncthreads();
                 lu_solve_left_T<double, W>(slot_lu<double>(s, slot), s.perm + size_t(slot) * NP, NP, b, z, t, Db);
                 double *d = s.d + size_t(slot) * S;
-                for (int i = threadIdx.x; i < S; i += NT) d[i] = z[i];
+                for (int i = thread_id(); i < S; i += NT) d[i] = z[i];
                 __syncthreads();
             }
             clk.stop(&t_phase[kPhaseAdjSolve]);
@@ -525,8 +525,8 @@ k_reverse(Slots s, DeviceNet n, IntegrateArgs a) {
             // the window is swept: the earlier steps come in the next pass
             const double *lam = s.D + size_t(slot) * kDRows * S, *g = s.g + size_t(slot) * R;
             double *wl = s.win_lam + size_t(cs.cell) * kDRows * S;
-            for (int i = threadIdx.x; i < kDRows * S; i += NT) wl[i] = lam[i];
-            for (int r = threadIdx.x; r < R; r += NT) s.win_g[size_t(cs.cell) * R + r] = g[r];
+            for (int i = thread_id(); i < kDRows * S; i += NT) wl[i] = lam[i];
+            for (int r = thread_id(); r < R; r += NT) s.win_g[size_t(cs.cell) * R + r] = g[r];
             __syncthreads();
             finish_slot(s, slot, cs, kWindowDone);
             __syncthreads();

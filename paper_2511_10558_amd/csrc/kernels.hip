@@ -508,11 +508,11 @@ __global__ void __launch_bounds__(kAsmThreads) k_newton_matrix_only(DeviceNet n,
 // Copies an n x n matrix into the padded NP x NP work matrix (identity padding) and back.
 template <typename T>
 __global__ void k_pad_in(int n, int NP, const double *A, T *W) {
-    const long long b = blockIdx.y;
+    const long long b = blockIdx.y, ld = lu_ld(NP);
     for (long long e = blockIdx.x * blockDim.x + threadIdx.x; e < (long long)NP * NP; e += gridDim.x * blockDim.x) {
         const int i = int(e / NP), j = int(e % NP);
         double v = (i < n && j < n) ? A[(b * n + i) * n + j] : (i == j ? 1.0 : 0.0);
-        W[b * NP * NP + e] = T(v);
+        W[(b * NP + i) * ld + j] = T(v);
     }
 }
 
@@ -523,7 +523,7 @@ __global__ void k_pad_out(int n, int NP, const T *W, double *A, const int32_t *p
     const long long b = blockIdx.y;
     for (long long e = blockIdx.x * blockDim.x + threadIdx.x; e < (long long)n * n; e += gridDim.x * blockDim.x) {
         const int i = int(e / n), j = int(e % n);
-        A[(b * n + i) * n + j] = double(W[b * NP * NP + (long long)permW[b * NP + i] * NP + j]);
+        A[(b * n + i) * n + j] = double(W[(b * NP + permW[b * NP + i]) * (long long)lu_ld(NP) + j]);
     }
     if (blockIdx.x == 0)
         for (int i = threadIdx.x; i < n; i += blockDim.x) perm[b * n + i] = permW[b * NP + i];
@@ -538,7 +538,7 @@ template <typename T, int W>
 __global__ void __launch_bounds__(64 * W) k_lu_factor_only(int NP, T *A0, int32_t *permW, T *dinv, int32_t *info) {
     extern __shared__ double smem[];
     const long long b = blockIdx.x;
-    T *A = A0 + b * NP * NP;
+    T *A = A0 + b * NP * lu_ld(NP);
     lu_factor_left<T, W>(A, NP, permW + b * NP, dinv + b * lu2_dinv_elems<T>(NP), info ? info + b : nullptr,
                       reinterpret_cast<unsigned char *>(smem), DenseSource<T>{A, NP});
 }
@@ -553,7 +553,7 @@ __global__ void __launch_bounds__(kDinvThreads) k_dinv_only(int NP, const double
     for (int j = 0; j * kLuW < NP; ++j) {
         const int r0 = j * kLuW, Wj = min(kLuW, NP - r0);
         for (int e = threadIdx.x; e < Wj * Wj; e += kDinvThreads)
-            Cb[(e / Wj) * kLdb + e % Wj] = W[b * NP * NP + size_t(r0 + e / Wj) * NP + r0 + e % Wj];
+            Cb[(e / Wj) * kLdb + e % Wj] = W[(b * NP + r0 + e / Wj) * (long long)lu_ld(NP) + r0 + e % Wj];
         __syncthreads();
         diag_inverses<double, kDinvThreads / 64>(Cb, Wj, dinv + b * lu2_dinv_elems<double>(NP) + size_t(j) * 2 * kLuW * kLuW, Xb, Yb,
                               nullptr);
@@ -570,7 +570,8 @@ __global__ void __launch_bounds__(kBlock) k_lu_solve_only(int NP, int n, const d
     for (int i = threadIdx.x; i < NP; i += kBlock) b[i] = i < n ? bvec[bi * n + i] : 0.0;
     __syncthreads();
     // the padding past n is the identity's (k_pad_in, k_copy_perm)
-    lu_solve_left<double, kBlock>(W + bi * NP * NP, dinv + bi * lu2_dinv_elems<double>(NP), nullptr, permW + bi * NP, NP,
+    lu_solve_left<double, kBlock, 2>(W + bi * NP * lu_ld(NP), lu_ld(NP), dinv + bi * lu2_dinv_elems<double>(NP), nullptr,
+                                     permW + bi * NP, NP,
                           min(NP, n + (n & 1)), b, y, t);
     for (int i = threadIdx.x; i < n; i += kBlock) bvec[bi * n + i] = y[i];
 }
@@ -658,7 +659,7 @@ static bool rhs_stream_shape(const DeviceNet &n, int &ku, int &gpw) {
                  : (const void *)&K<12, 2>))
 
 size_t lu_bytes(int NP, int prec) {
-    return size_t(NP) * NP * (prec == ABDF_PREC_FP32_LU ? sizeof(float) : sizeof(double));
+    return size_t(NP) * lu_ld(NP) * (prec == ABDF_PREC_FP32_LU ? sizeof(float) : sizeof(double));
 }
 
 size_t dinv_bytes(int NP, int prec) {
