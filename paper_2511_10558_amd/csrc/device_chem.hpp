@@ -130,41 +130,64 @@ __device__ __forceinline__ void cell_jvp(const DeviceNet &n, const double *__res
 
 // The Jacobian nonzeros J_e(x) of one cell into jv[nnzJ] (global, written
 // coalesced): each nonzero's terms summed in the order of its term list.  x in
-// LDS, k in global memory.  Cooperative.
+// LDS; k in LDS or global memory.  Cooperative.
+//
+// A nonzero has 1.8 terms on average and is a chain of three loads (its list's
+// bounds, the terms, their coefficients), so a thread works on kU nonzeros at
+// once, two terms of each in flight together; longer lists finish one by one.
 template <int NT>
 __device__ __forceinline__ void jacobian_values(const DeviceNet &n, const double *__restrict__ k, const double *x,
                                                 double *jv) {
-    // a nonzero's terms are loaded four at a time before any is used; the sum
-    // still runs term by term in order
-    for (int e = thread_id(); e < n.nnzJ; e += NT) {
-        double v = 0.0;
-        const int t0 = n.jterm_ptr[e], t1 = n.jterm_ptr[e + 1];
-        for (int tb = t0; tb < t1; tb += 4) {
-            int w[4];
-            double cf[4];
+    constexpr int kU = 4, kT = 2;
+    auto term = [&](int w, double cf) {
+        const int other = (w & 0xffff) - 1;
+        double v = cf * k[w >> 16];
+        if (other >= 0) v *= x[other];
+        return v;
+    };
+    for (int e0 = thread_id(); e0 < n.nnzJ; e0 += kU * NT) {
+        int t0[kU], t1[kU];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const bool in = tb + u < t1;
-                w[u] = in ? n.jt_rx_other[tb + u] : 0;
-                cf[u] = in ? n.jt_coef[tb + u] : 0.0;
+        for (int u = 0; u < kU; ++u) {
+            const int e = min(e0 + u * NT, n.nnzJ - 1);
+            t0[u] = n.jterm_ptr[e];
+            t1[u] = n.jterm_ptr[e + 1];
+        }
+        int w[kU][kT];
+        double cf[kU][kT];
+#pragma unroll
+        for (int u = 0; u < kU; ++u)
+#pragma unroll
+            for (int t = 0; t < kT; ++t) {
+                const int at = min(t0[u] + t, t1[u] - 1);   // a nonzero has at least one term
+                w[u][t] = n.jt_rx_other[at];
+                cf[u][t] = n.jt_coef[at];
             }
-            double kv[4], xv[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int other = (w[u] & 0xffff) - 1;
-                kv[u] = k[w[u] >> 16];
-                xv[u] = x[other >= 0 ? other : 0];
+        for (int u = 0; u < kU; ++u) {
+            double v = 0.0;
+#pragma unroll
+            for (int t = 0; t < kT; ++t) {
+                const double p = term(w[u][t], cf[u][t]);
+                if (t0[u] + t < t1[u]) v += p;
             }
+            for (int tb = t0[u] + kT; tb < t1[u]; tb += 4) {
+                int wr[4];
+                double cr[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                if (tb + u < t1) {
-                    double term = cf[u] * kv[u];
-                    if ((w[u] & 0xffff) != 0) term *= xv[u];
-                    v += term;
+                for (int t = 0; t < 4; ++t) {
+                    const int at = min(tb + t, t1[u] - 1);
+                    wr[t] = n.jt_rx_other[at];
+                    cr[t] = n.jt_coef[at];
+                }
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const double p = term(wr[t], cr[t]);
+                    if (tb + t < t1[u]) v += p;
                 }
             }
+            if (e0 + u * NT < n.nnzJ) jv[e0 + u * NT] = v;
         }
-        jv[e] = v;
     }
 }
 

@@ -5,6 +5,8 @@
 
 #include <cstdint>
 #include <limits>
+#include <type_traits>
+#include <utility>
 
 namespace abdf {
 
@@ -205,6 +207,16 @@ __device__ __forceinline__ void wave_argmax_ballot(double &v, int &k) {
     v = m;
 }
 
+template <typename F, int... I>
+__device__ __forceinline__ void static_for_each(F &&f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+// f(0), ..., f(N - 1), each index a constant
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F &&f) {
+    static_for_each(static_cast<F &&>(f), std::make_integer_sequence<int, N>{});
+}
+
 // threadIdx.x, opaque to the compiler: what a phase of a persistent kernel
 // derives from it (addresses above all) is formed in that phase, instead of
 // being hoisted out of the loop over attempts into registers that the
@@ -230,6 +242,14 @@ __device__ __forceinline__ double row_rotate(double v) {
     const int lo = __double2loint(v), hi = __double2hiint(v);
     return __hiloint2double(__builtin_amdgcn_mov_dpp(hi, 0x120 + N, 0xf, 0xf, true),
                             __builtin_amdgcn_mov_dpp(lo, 0x120 + N, 0xf, 0xf, true));
+}
+
+// v of lane N of each row of 16, on all lanes of the row.
+template <int N>
+__device__ __forceinline__ double row_broadcast(double v) {
+    const int lo = __double2loint(v), hi = __double2hiint(v);
+    return __hiloint2double(__builtin_amdgcn_mov_dpp(hi, 0x150 + N, 0xf, 0xf, true),
+                            __builtin_amdgcn_mov_dpp(lo, 0x150 + N, 0xf, 0xf, true));
 }
 
 // Sum over each row of 16 lanes, on all of them: the pairwise sums of lanes 8,

@@ -39,9 +39,6 @@
 #include "device_common.hpp"
 #include "device_lu.hpp"
 
-#include <type_traits>
-#include <utility>
-
 namespace abdf {
 
 constexpr int kLuW = 64;          // block-column width
@@ -364,9 +361,25 @@ __device__ __forceinline__ void lu_factor_left(T *__restrict__ A, int NP, int32_
                     }
             }
         }
-        // 2. updates from the earlier block columns
+        // 2. updates from the earlier block columns.  What comes from memory is
+        //    asked for ahead of the barriers and the products it would
+        //    otherwise wait behind: the inverse of L_ii before C_i is staged,
+        //    this wave's first tile of L before U_ij is complete, each further
+        //    tile before the products with the one before it.
+#pragma unroll 1
         for (int i = 0; i < j; ++i) {
             const int r0 = i * kLuW;
+            const T *Li = dinv + size_t(i) * 2 * kLuW * kLuW;   // inverse of the unit-lower block i
+            // the 16 tiles of U_ij = inv(L_ii) C_i, spread over all waves (a
+            // workgroup of fewer than four waves has one block column)
+            constexpr int TPW = W >= 4 ? 16 / W : 1;
+            const int t0 = wave * TPW, tr = t0 >> 2;
+            v4 ia[4];
+            if constexpr (W >= 4) {
+#pragma unroll
+                for (int kk = 0; kk < 4; ++kk)
+                    ia[kk] = *reinterpret_cast<const v4 *>(Li + (16 * tr + lc) * kLuW + 16 * kk + 4 * g);
+            }
 #pragma unroll
             for (int s = 0; s < lu_slots<W>; ++s) {
                 const int rt = wave + W * s;
@@ -380,15 +393,19 @@ __device__ __forceinline__ void lu_factor_left(T *__restrict__ A, int NP, int32_
                 }
             }
             __syncthreads();
-            const T *Li = dinv + size_t(i) * 2 * kLuW * kLuW;   // inverse of the unit-lower block i
-            if constexpr (W >= 4) {
-                // the 16 tiles of U_ij = inv(L_ii) C_i, spread over all waves (one wave has one block column)
-                constexpr int TPW = 16 / W;
-                const int t0 = wave * TPW, tr = t0 >> 2;
-                v4 a[4];
+            // rows of the first tile below block i that this wave holds
+            v4 la[4];
+            auto load_tile = [&](int rt) {
+                const T *Lrow = A + size_t(perm[16 * rt + lc]) * lda + r0;
 #pragma unroll
-                for (int kk = 0; kk < 4; ++kk)
-                    a[kk] = *reinterpret_cast<const v4 *>(Li + (16 * tr + lc) * kLuW + 16 * kk + 4 * g);
+                for (int kk = 0; kk < 4; ++kk) la[kk] = *reinterpret_cast<const v4 *>(Lrow + 16 * kk + 4 * g);
+            };
+            {
+                const int below = 4 * (i + 1);
+                const int first = wave >= below ? wave : wave + (below - wave + W - 1) / W * W;
+                if (first < RT) load_tile(first);
+            }
+            if constexpr (W >= 4) {
 #pragma unroll
                 for (int k = 0; k < TPW; ++k) {
                     const int ct = (t0 + k) & 3;
@@ -398,7 +415,7 @@ __device__ __forceinline__ void lu_factor_left(T *__restrict__ A, int NP, int32_
                         for (int kk = 0; kk < 4; ++kk)
 #pragma unroll
                             for (int e = 0; e < 4; ++e)
-                                u = M::mma(a[kk][e], Cb[(16 * kk + 4 * g + e) * kLdb + 16 * ct + lc], u);
+                                u = M::mma(ia[kk][e], Cb[(16 * kk + 4 * g + e) * kLdb + 16 * ct + lc], u);
 #pragma unroll
                         for (int v = 0; v < 4; ++v) Ub[(16 * tr + M::row(lane, v)) * kLdb + 16 * ct + lc] = u[v];
                     }
@@ -419,27 +436,250 @@ __device__ __forceinline__ void lu_factor_left(T *__restrict__ A, int NP, int32_
                             for (int v = 0; v < 4; ++v) acc[s][ct][v] = Ub[(16 * tr + M::row(lane, v)) * kLdb + 16 * ct + lc];
                 }
                 if (rt >= 4 * (i + 1) && rt < RT) {
-                    const T *Lrow = A + size_t(perm[16 * rt + lc]) * lda + r0;
                     v4 a[4];
 #pragma unroll
-                    for (int kk = 0; kk < 4; ++kk) a[kk] = *reinterpret_cast<const v4 *>(Lrow + 16 * kk + 4 * g);
+                    for (int kk = 0; kk < 4; ++kk) a[kk] = la[kk];
+                    if (rt + W < RT) load_tile(rt + W);
+                    if (CTj == 4) {
 #pragma unroll
-                    for (int kk = 0; kk < 4; ++kk)
+                        for (int kk = 0; kk < 4; ++kk)
 #pragma unroll
-                        for (int e = 0; e < 4; ++e)
+                            for (int e = 0; e < 4; ++e)
 #pragma unroll
-                            for (int ct = 0; ct < 4; ++ct)
-                                if (ct < CTj)
+                                for (int ct = 0; ct < 4; ++ct)
                                     acc[s][ct] = M::mma(-a[kk][e], Ub[(16 * kk + 4 * g + e) * kLdb + 16 * ct + lc],
                                                         acc[s][ct]);
+                    } else {
+#pragma unroll
+                        for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                                for (int ct = 0; ct < 3; ++ct)
+                                    if (ct < CTj)
+                                        acc[s][ct] = M::mma(-a[kk][e], Ub[(16 * kk + 4 * g + e) * kLdb + 16 * ct + lc],
+                                                            acc[s][ct]);
+                    }
                 }
             }
             __syncthreads();
         }
         // 3. panel factorisation, 16-column sub-panels.  Rows stay at their
-        //    positions; pivoting assigns logical rows to positions.
+        //    positions; pivoting assigns logical rows to positions.  First on the
+        //    diagonal, as long as it is accepted: then no row has been exchanged
+        //    in this block column, position and logical row are the same, the
+        //    pivot rows of sub-panel sp are row tile 4 j + sp and the unused rows
+        //    the tiles below.  Unrolled, so that a sub-panel's column tile is a
+        //    constant of the accumulators.  The first sub-panel refused and those
+        //    after it go through the general loop below.  (12.9 us a sub-panel of
+        //    512 rows through the general loop alone, 9.5 this way.)
+        int from = CTj;      // the first sub-panel left to the general loop
+        static_for<4>([&](auto spc) __attribute__((always_inline)) {
+            constexpr int sp = decltype(spc)::value;
+            if (sp >= from) return;
+            const int tid = thread_id(), lane = tid & 63, wave = wave_of(tid);
+            const int g = lane >> 4, lc = lane & 15;
+            const int dt = 4 * j + sp, rb = 16 * dt;
+            // (a) the sub-panel's column tile to LDS, one row per position (the
+            //     accumulators keep it until (c))
+#pragma unroll
+            for (int s = 0; s < lu_slots<W>; ++s) {
+                const int rt = wave + W * s;
+                if (rt >= dt && rt < RT)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) P[(16 * rt + M::row(lane, v)) * kPanLd + lc] = acc[s][sp][v];
+            }
+            if (tid == 0) spec_bad[0] = 0;
+            __syncthreads();
+            // (b1) the diagonal block, rows rb .. rb + 15
+            if (wave == 0) {
+                // the 16 x 16 block in registers; column c: every entry below row
+                // c takes its multiplier or its update from row c, each lane
+                // reading what it needs from the lanes that hold it before it
+                // changes its own; the factored block then goes to Db.  A pivot
+                // below the smallest normal number refuses the diagonal (partial
+                // pivoting then forms such multipliers by division).
+                bool bad = false;
+                if constexpr (sizeof(T) == sizeof(float)) {
+                    // FP32: lane i < 16 holds row i; the pivot and the rest of
+                    // row c reach every lane by readlane
+                    T a[16];
+                    const bool row_lane = lane < 16;
+#pragma unroll
+                    for (int c = 0; c < 16; ++c) a[c] = P[(rb + (row_lane ? lane : 0)) * kPanLd + c];
+                    T uii = T(1);
+#pragma unroll
+                    for (int c = 0; c < 16; ++c) {
+                        const T piv = lane_value(a[c], c);
+                        const bool normal = fabs(piv) >= std::numeric_limits<T>::min();
+                        const T rinv = T(1) / (normal ? piv : T(1));
+                        if (lane == c) uii = a[c];
+                        const bool below = row_lane && lane > c;
+                        const T l = a[c] * rinv;
+                        bad |= !normal;
+                        bad |= below && !(fabs(l) <= T(kPivotThreshold));
+#pragma unroll
+                        for (int j = c + 1; j < 16; ++j) {
+                            const T ucj = lane_value(a[j], c);
+                            if (below) a[j] = a[j] - l * ucj;
+                        }
+                        if (below) a[c] = l;
+                    }
+                    if (row_lane) {
+#pragma unroll
+                        for (int c = 0; c < 16; ++c) Db[lane * kCrowLd + c] = a[c];
+                        Db[lane * kCrowLd + 16] = T(1) / uii;   // used only when every pivot is normal
+                    }
+                } else {
+                    // FP64 (fewer registers): lane l holds the entries of rows
+                    // i = 4 t + l / 16 (t = 0..3) in column j = l % 16.  A column
+                    // is a chain of its pivot (readlane), its reciprocal and the
+                    // multipliers (a row broadcast each); the pivot row's entries
+                    // come by LDS permutes meanwhile.
+                    const int jj = lane & 15, gg = lane >> 4;
+                    T a[4];
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) a[t] = P[(rb + 4 * t + gg) * kPanLd + jj];
+                    static_for<16>([&](auto cc) __attribute__((always_inline)) {
+                        constexpr int c = decltype(cc)::value, tc = c >> 2, gc = c & 3;
+                        const T ucj = __shfl(a[tc], 16 * gc + jj);
+                        const T piv = lane_value(a[tc], 16 * gc + c);
+                        const bool normal = fabs(piv) >= std::numeric_limits<T>::min();
+                        const T rinv = T(1) / (normal ? piv : T(1));
+                        T l[4];
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) l[t] = row_broadcast<c>(a[t]) * rinv;
+                        bad |= !normal;
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) {
+                            const int i = 4 * t + gg;
+                            if (4 * t + 3 > c) {
+                                const bool below = i > c;
+                                bad |= below && jj == c && !(fabs(l[t]) <= T(kPivotThreshold));
+                                const T upd = a[t] - l[t] * ucj;
+                                a[t] = below && jj == c ? l[t] : (below && jj > c ? upd : a[t]);
+                            }
+                        }
+                    });
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) Db[(4 * t + gg) * kCrowLd + jj] = a[t];
+                    wave_lds_order();
+                    if (lane < 16) Db[lane * kCrowLd + 16] = T(1) / Db[lane * kCrowLd + lane];   // used only when every pivot is normal
+                }
+                if (__ballot(bad) != 0 && lane == 0) spec_bad[0] = 1;
+            }
+            __syncthreads();
+            // (b2) every row below, one thread each, against the diagonal block's
+            //      U rows (no exchange between waves), the result written over
+            //      the row in LDS.  A U row is read once per wave, an entry a
+            //      lane, and its entries handed round as scalars: read from LDS
+            //      by every lane they took its whole rate.
+            const int q = tid;
+            const bool row = q >= rb + 16 && q < NP;
+            {
+                bool bad = false;
+                if (64 * wave + 63 >= rb + 16 && 64 * wave < NP) {
+                    T x[16];
+                    const int qr = row ? q : rb;      // idle lanes work on a row of the panel for nothing
+#pragma unroll
+                    for (int c = 0; c < 16; ++c) x[c] = P[qr * kPanLd + c];
+                    T un = Db[lane < 17 ? lane : 0];
+#pragma unroll
+                    for (int c = 0; c < 16; ++c) {
+                        const T u = un;
+                        if (c < 15) un = Db[(c + 1) * kCrowLd + (lane < 17 ? lane : 0)];
+                        const T l = x[c] * lane_value(u, 16);
+                        bad |= !(fabs(l) <= T(kPivotThreshold));
+                        x[c] = l;
+#pragma unroll
+                        for (int cb = c + 1; cb < 16; ++cb) x[cb] -= l * lane_value(u, cb);
+                    }
+                    if (row) {
+#pragma unroll
+                        for (int c = 0; c < 16; ++c) P[q * kPanLd + c] = x[c];
+                    }
+                }
+                if (__ballot(bad && row) != 0 && lane == 0) spec_bad[0] = 1;
+            }
+            __syncthreads();
+            if (__builtin_amdgcn_readfirstlane(spec_bad[0]) != 0) {
+                from = sp;
+                return;
+            }
+            // accepted: the diagonal rows are the pivots, labels unchanged
+            if (q >= rb && q < rb + 16) {
+                pidx[q] = 16 * sp + (q - rb);
+                piv_pos[16 * sp + (q - rb)] = q;
+            }
+            // (c) back to the accumulators; (d) the pivot rows of the remaining
+            //     column tiles of the block to LDS
+            const int nct = CTj - sp - 1;
+#pragma unroll
+            for (int s = 0; s < lu_slots<W>; ++s) {
+                const int rt = wave + W * s;
+                if (rt >= dt && rt < RT) {
+                    const T *src = rt == dt ? Db : P + 16 * rt * kPanLd;
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) acc[s][sp][v] = src[M::row(lane, v) * kPanLd + lc];
+                    if (rt == dt) {
+#pragma unroll
+                        for (int ct = sp + 1; ct < 4; ++ct)
+                            if (ct < CTj)
+#pragma unroll
+                                for (int v = 0; v < 4; ++v)
+                                    U12[M::row(lane, v) * kU12Ld + 16 * (ct - sp - 1) + lc] = acc[s][ct][v];
+                    }
+                }
+            }
+            if constexpr (sp < 3) {
+                if (nct == 0) return;
+                __syncthreads();
+                // U12 of the pivot rows, a column a thread
+                if (tid < 16 * nct) {
+                    T u[16];
+#pragma unroll
+                    for (int i2 = 0; i2 < 16; ++i2) u[i2] = U12[i2 * kU12Ld + tid];
+#pragma unroll
+                    for (int i2 = 1; i2 < 16; ++i2) {
+#pragma unroll
+                        for (int m = 0; m < i2; ++m) u[i2] -= Db[i2 * kCrowLd + m] * u[m];
+                    }
+#pragma unroll
+                    for (int i2 = 0; i2 < 16; ++i2) U12[i2 * kU12Ld + tid] = u[i2];
+                }
+                __syncthreads();
+                // the rows below
+#pragma unroll
+                for (int s = 0; s < lu_slots<W>; ++s) {
+                    const int rt = wave + W * s;
+                    if (rt > dt && rt < RT) {
+                        T a[4];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) a[e] = -P[(16 * rt + lc) * kPanLd + 4 * e + g];
+#pragma unroll
+                        for (int ct = sp + 1; ct < 4; ++ct)
+                            if (ct < CTj)
+#pragma unroll
+                                for (int e = 0; e < 4; ++e)
+                                    acc[s][ct] = M::mma(a[e], U12[(4 * e + g) * kU12Ld + 16 * (ct - sp - 1) + lc],
+                                                        acc[s][ct]);
+                    }
+                    if (rt == dt) {
+#pragma unroll
+                        for (int ct = sp + 1; ct < 4; ++ct)
+                            if (ct < CTj)
+#pragma unroll
+                                for (int v = 0; v < 4; ++v)
+                                    acc[s][ct][v] = U12[M::row(lane, v) * kU12Ld + 16 * (ct - sp - 1) + lc];
+                    }
+                }
+                __syncthreads();
+            }
+        });
+        __syncthreads();
+        // the general loop, from the first sub-panel whose diagonal was refused
 #pragma unroll 1
-        for (int sp = 0; sp < CTj; ++sp) {
+        for (int sp = from; sp < CTj; ++sp) {
             // (a) the sub-panel's column tile to LDS, one row per position (the
             //     accumulators keep it until (c), so it can be written again)
             auto panel_to_lds = [&]() {
@@ -843,16 +1083,6 @@ struct SolveOrder {
         return up(q) ? (e < row(q) ? ib(q) + 1 + e : ib(q)) : e;
     }
 };
-
-template <typename F, int... I>
-__device__ __forceinline__ void static_for_each(F &&f, std::integer_sequence<int, I...>) {
-    (f(std::integral_constant<int, I>{}), ...);
-}
-// f(0), ..., f(N - 1), each index a constant
-template <int N, typename F>
-__device__ __forceinline__ void static_for(F &&f) {
-    static_for_each(static_cast<F &&>(f), std::make_integer_sequence<int, N>{});
-}
 
 // Solves (P^T L U) z = b for one matrix factored by lu_factor_left, with the
 // NT threads of a workgroup.  Row r of the factors is storage row rowmap[r]

@@ -416,10 +416,13 @@ __device__ __forceinline__ void factor_slot(const Slots &s, const DeviceNet &n, 
     const int S = s.S, NP = s.NP;
     double *jv = s.jval + size_t(slot) * n.nnzJ;
     if (!cs.jv_valid) {
+        // x_J and the rate coefficients, which the terms read at random, in LDS
+        const double *k = s.k + size_t(slot) * n.R;
         const int i = thread_id();
         if (i < S) smem[i] = s.xJ[size_t(slot) * S + i];
+        for (int r = i; r < n.R; r += 64 * W) smem[S + r] = k[r];
         __syncthreads();
-        jacobian_values<64 * W>(n, s.k + size_t(slot) * n.R, smem, jv);
+        jacobian_values<64 * W>(n, smem + S, smem, jv);
         __syncthreads();
     }
     NewtonMatrixSource<T> src{n.jmask, n.jbase, n.nbw, jv, uniform(cs.c)};

@@ -1,0 +1,81 @@
+// The persistent integration of cells of at most 64 species.
+#include "device_tiny.hpp"
+#include "integrate_kernels.hpp"
+
+namespace abdf {
+
+// Integrates queued cells of at most 64 species, one wave per cell (TinyCell).
+template <typename T>
+__global__ void __launch_bounds__(64) k_integrate_tiny(Slots s, DeviceNet n, IntegrateArgs a) {
+    extern __shared__ double smem[];
+    __shared__ StepLds<1> L;
+    __shared__ unsigned long long t_phase[kPhases];
+    const unsigned long long t0 = wall_clock64();
+    if (threadIdx.x < kPhases) t_phase[threadIdx.x] = 0;
+    const bool rk = s.method == ABDF_METHOD_ESDIRK5;
+    PhaseClock clk{a.prof && threadIdx.x == 0, 0};
+    TinyCell<T> cell(n, reinterpret_cast<unsigned char *>(smem));
+    while (true) {
+        const int slot = take_slot<1>(s, a, L);
+        if (slot < 0) break;
+        const double *kg = s.k + size_t(slot) * n.R;
+        SpeciesState y;
+        load_rows(s, slot, y);
+        cell.load_rates(kg);
+        if (L.cs.jv_valid) cell.restore(s, n, slot);
+        bool up = false;
+        while (true) {
+            clk.start();
+            if (rk)
+                begin_stage_rk<1>(s, slot, L, y);
+            else
+                begin_attempt<1>(s, n, slot, L, y);
+            if (L.cs.status != kRunning) break;
+            if (s.tvar && L.cs.tc > 0.0) cell.load_rates(kg);
+            clk.stop(&t_phase[kPhaseControl]);
+            if (!L.cs.lu_valid) {
+                if (!L.cs.jv_valid)
+                    cell.jacobian(n, s.xJ + size_t(slot) * s.S, s.jval + size_t(slot) * n.nnzJ);
+                cell.factor(s, slot, L.cs.c);
+                if (threadIdx.x == 0) {
+                    L.cs.c_lu = L.cs.c;
+                    L.cs.lu_valid = 1;
+                    L.cs.jv_valid = 1;
+                    L.cs.n_lu += 1;
+                }
+                __syncthreads();
+                clk.stop(&t_phase[kPhaseFactor]);
+            }
+            const int phase = newton_tiny<T>(s, slot, L, y, cell, clk.on ? &t_phase[kPhaseRhs] : nullptr);
+            clk.stop(&t_phase[kPhaseNewton]);
+            if (rk)
+                control_rk<1>(s, L, y, phase, nullptr);
+            else
+                control_bdf<1>(s, slot, L, y, phase, nullptr);
+            if (L.cs.status != kRunning) break;
+            up = time_up<1>(s, a, t0, L);
+            clk.stop(&t_phase[kPhaseControl]);
+            if (up) break;
+        }
+        store_rows(s, slot, y);
+        if (!up) finish_slot(s, slot, L.cs, L.cs.status);
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            s.ctl[slot] = L.cs;
+            if (up) hold_slot(s, slot);
+        }
+        if (up) break;
+    }
+    __syncthreads();
+    if (a.prof && threadIdx.x < kPhases)
+        atomicAdd(&s.q->ticks[threadIdx.x],
+                  t_phase[threadIdx.x] - (threadIdx.x == kPhaseNewton ? t_phase[kPhaseRhs] : 0ull));
+}
+
+Persistent integrate_tiny(const DeviceNet &n, int prec) {
+    return prec == ABDF_PREC_FP32_LU
+               ? Persistent{(const void *)&k_integrate_tiny<float>, 64, TinyLayout<float>(n).total}
+               : Persistent{(const void *)&k_integrate_tiny<double>, 64, TinyLayout<double>(n).total};
+}
+
+}  // namespace abdf

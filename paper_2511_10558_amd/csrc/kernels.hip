@@ -742,23 +742,21 @@ hipError_t launch_newton_matrix(const DeviceNet &n, long long cells, const doubl
     return LAUNCH_CHECK();
 }
 
-// Waves of the standalone factorisation.  FP64: 8 waves of 256 VGPRs, each wave
-// holding four row tiles of the block column.  FP32: 16 waves of 128 VGPRs with
-// two row tiles each (its accumulators are half the size), twice the waves to
-// hide latency with.
-constexpr int kLuWaves64 = 8, kLuWaves32 = 16;
+// Waves of the standalone factorisation: of 256 VGPRs, each holding four row
+// tiles of the block column.
+constexpr int kLuWaves = 8;
 
 hipError_t launch_lu_factor(int n, int NP, long long batch, double *A, void *W, int32_t *permW, int32_t *perm,
                             void *dinv, int32_t *info, int prec, hipStream_t st) {
     dim3 g(std::max(1, std::min(64, (NP * NP + 255) / 256)), unsigned(batch));
     if (prec == ABDF_PREC_FP32_LU) {
         hipLaunchKernelGGL(k_pad_in<float>, g, dim3(256), 0, st, n, NP, A, (float *)W);
-        hipLaunchKernelGGL((k_lu_factor_only<float, kLuWaves32>), dim3(batch), dim3(64 * kLuWaves32), (lu2_lds_bytes<float, kLuWaves32>(NP)), st, NP,
+        hipLaunchKernelGGL((k_lu_factor_only<float, kLuWaves>), dim3(batch), dim3(64 * kLuWaves), (lu2_lds_bytes<float, kLuWaves>(NP)), st, NP,
                            (float *)W, permW, (float *)dinv, info);
         hipLaunchKernelGGL(k_pad_out<float>, g, dim3(256), 0, st, n, NP, (const float *)W, A, permW, perm);
     } else {
         hipLaunchKernelGGL(k_pad_in<double>, g, dim3(256), 0, st, n, NP, A, (double *)W);
-        hipLaunchKernelGGL((k_lu_factor_only<double, kLuWaves64>), dim3(batch), dim3(64 * kLuWaves64), (lu2_lds_bytes<double, kLuWaves64>(NP)), st,
+        hipLaunchKernelGGL((k_lu_factor_only<double, kLuWaves>), dim3(batch), dim3(64 * kLuWaves), (lu2_lds_bytes<double, kLuWaves>(NP)), st,
                            NP, (double *)W, permW, (double *)dinv, info);
         hipLaunchKernelGGL(k_pad_out<double>, g, dim3(256), 0, st, n, NP, (const double *)W, A, permW, perm);
     }

@@ -34,6 +34,9 @@ KERNEL_SOURCES = ["paper_2511_10558_amd/csrc/device_lu2.hpp", "paper_2511_10558_
                   "paper_2511_10558_amd/csrc/device_chem.hpp", "paper_2511_10558_amd/csrc/kernels.hip",
                   "paper_2511_10558_amd/csrc/integrate.hip", "paper_2511_10558_amd/csrc/device_step.hpp",
                   "paper_2511_10558_amd/csrc/device_tiny.hpp",
+                  "paper_2511_10558_amd/csrc/integrate_kernels.hpp",
+                  "paper_2511_10558_amd/csrc/integrate_fp32.hip", "paper_2511_10558_amd/csrc/integrate_tiny.hip",
+                  "paper_2511_10558_amd/csrc/reverse.hip",
                   "paper_2511_10558_amd/csrc/device_common.hpp"]
 COPY_BYTES = 256 * 1024 * 1024
 
