@@ -7,7 +7,7 @@ from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 SOURCES = ["csrc/integrate_fp32.hip", "csrc/integrate.hip", "csrc/integrate_tiny.hip", "csrc/reverse.hip",
-           "csrc/kernels.hip", "csrc/engine.cpp", "csrc/network.cpp", "csrc/server.cpp", "csrc/adjoint.cpp",
+           "csrc/kernels.hip", "csrc/lu_batch.hip", "csrc/engine.cpp", "csrc/network.cpp", "csrc/server.cpp", "csrc/adjoint.cpp",
            "csrc/abi.cpp", "csrc/noalloc.hip"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-pthread",

@@ -539,11 +539,8 @@ abdf_status abdf_newton_matrix(const abdf_network *net, int64_t n_cells, const d
     const abdf::DeviceNet *dn = net->host.device_tables(err);
     if (!dn) return fail(ABDF_E_DEVICE, err);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    double *jv = nullptr;
-    HIP_OR_FAIL(hipMalloc(reinterpret_cast<void **>(&jv), size_t(n_cells) * std::max(dn->nnzJ, 1) * sizeof(double)));
-    hipError_t e = abdf::launch_newton_matrix(*dn, n_cells, k, x, c, M_out, jv, st);
+    hipError_t e = abdf::launch_newton_matrix(*dn, n_cells, k, x, c, M_out, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
-    (void)hipFree(jv);
     if (e != hipSuccess) return fail(ABDF_E_DEVICE, hipGetErrorString(e));
     return ok();
 }
@@ -556,18 +553,13 @@ abdf_status abdf_lu_factor(int32_t n, int64_t batch, double *A, int32_t *perm, i
     CHECK_DEV(A, "A");
     CHECK_DEV(perm, "perm");
     if (info) CHECK_DEV(info, "info");
-    const int NP = (n + 15) / 16 * 16;
-    void *W = nullptr, *dinv = nullptr;
-    int32_t *permW = nullptr;
-    hipError_t e = hipMalloc(&W, size_t(batch) * abdf::lu_bytes(NP, precision));
-    if (e == hipSuccess) e = hipMalloc(&dinv, size_t(batch) * abdf::dinv_bytes(NP, precision));
-    if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&permW), size_t(batch) * NP * sizeof(int32_t));
+    const abdf::LuFactorPlan plan = abdf::plan_lu_factor(n, batch, precision);
+    void *scratch = nullptr;
+    hipError_t e = plan.scratch ? hipMalloc(&scratch, plan.scratch) : hipSuccess;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (e == hipSuccess) e = abdf::launch_lu_factor(n, NP, batch, A, W, permW, perm, dinv, info, precision, st);
+    if (e == hipSuccess) e = abdf::launch_lu_factor(plan, n, batch, A, perm, info, scratch, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
-    if (W) (void)hipFree(W);
-    if (dinv) (void)hipFree(dinv);
-    if (permW) (void)hipFree(permW);
+    if (scratch) (void)hipFree(scratch);
     if (e != hipSuccess) return fail(ABDF_E_DEVICE, hipGetErrorString(e));
     return ok();
 }
@@ -578,18 +570,9 @@ abdf_status abdf_lu_solve(int32_t n, int64_t batch, const double *LU, const int3
     CHECK_DEV(LU, "LU");
     CHECK_DEV(perm, "perm");
     CHECK_DEV(b, "b");
-    const int NP = (n + 15) / 16 * 16;
-    void *W = nullptr, *dinv = nullptr;
-    int32_t *permW = nullptr;
-    hipError_t e = hipMalloc(&W, size_t(batch) * abdf::lu_bytes(NP, ABDF_PREC_FP64));
-    if (e == hipSuccess) e = hipMalloc(&dinv, size_t(batch) * abdf::dinv_bytes(NP, ABDF_PREC_FP64));
-    if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&permW), size_t(batch) * NP * sizeof(int32_t));
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (e == hipSuccess) e = abdf::launch_lu_solve(n, NP, batch, LU, perm, b, W, permW, dinv, st);
+    hipError_t e = abdf::launch_lu_solve(n, batch, LU, perm, b, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
-    if (W) (void)hipFree(W);
-    if (dinv) (void)hipFree(dinv);
-    if (permW) (void)hipFree(permW);
     if (e != hipSuccess) return fail(ABDF_E_DEVICE, hipGetErrorString(e));
     return ok();
 }

@@ -16,14 +16,18 @@ template <int NT = kBlock>
 __device__ inline void cell_rates(const DeviceNet &n, const double *phi, double *k) {
     const double T = phi[0], nH = phi[1], Av = phi[2], zeta = phi[3], G0 = phi[4];
     const double T300 = T / 300.0;
+    // one exponential for the laws that have one, whatever the mix of laws
+    // among a wave's reactions
     for (int r = thread_id(); r < n.R; r += NT) {
         const int t = n.rx_type[r];
-        const double a = n.alpha[r];
+        const double a = n.alpha[r], ga = n.gamma[r];
+        const double e = exp(t == kTwoBody ? -ga / T : (t == kPhoto ? -ga * Av : 0.0));
+        const double p = t == kTwoBody || t == kCrPhoton ? pow(T300, n.beta[r]) : 1.0;
         double v;
-        if (t == kTwoBody) v = a * pow(T300, n.beta[r]) * exp(-n.gamma[r] / T) * nH;
+        if (t == kTwoBody) v = a * p * e * nH;
         else if (t == kCosmicRay) v = a * zeta;
-        else if (t == kCrPhoton) v = a * pow(T300, n.beta[r]) * (n.gamma[r] / (1.0 - n.albedo)) * zeta;
-        else v = a * G0 * exp(-n.gamma[r] * Av);
+        else if (t == kCrPhoton) v = a * p * (ga / (1.0 - n.albedo)) * zeta;
+        else v = a * G0 * e;
         k[r] = v;
     }
 }
@@ -128,16 +132,16 @@ __device__ __forceinline__ void cell_jvp(const DeviceNet &n, const double *__res
     species_gather<NT>(n, drate, out);
 }
 
-// The Jacobian nonzeros J_e(x) of one cell into jv[nnzJ] (global, written
-// coalesced): each nonzero's terms summed in the order of its term list.  x in
-// LDS; k in LDS or global memory.  Cooperative.
+// The Jacobian nonzeros J_e(x), first <= e < last, of one cell into
+// jv[e - first] (written coalesced): each nonzero's terms summed in the order of
+// its term list.  x in LDS; k in LDS or global memory.  Cooperative.
 //
 // A nonzero has 1.8 terms on average and is a chain of three loads (its list's
 // bounds, the terms, their coefficients), so a thread works on kU nonzeros at
 // once, two terms of each in flight together; longer lists finish one by one.
 template <int NT>
 __device__ __forceinline__ void jacobian_values(const DeviceNet &n, const double *__restrict__ k, const double *x,
-                                                double *jv) {
+                                                double *jv, int first, int last) {
     constexpr int kU = 4, kT = 2;
     auto term = [&](int w, double cf) {
         const int other = (w & 0xffff) - 1;
@@ -145,11 +149,11 @@ __device__ __forceinline__ void jacobian_values(const DeviceNet &n, const double
         if (other >= 0) v *= x[other];
         return v;
     };
-    for (int e0 = thread_id(); e0 < n.nnzJ; e0 += kU * NT) {
+    for (int e0 = first + thread_id(); e0 < last; e0 += kU * NT) {
         int t0[kU], t1[kU];
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
-            const int e = min(e0 + u * NT, n.nnzJ - 1);
+            const int e = min(e0 + u * NT, last - 1);
             t0[u] = n.jterm_ptr[e];
             t1[u] = n.jterm_ptr[e + 1];
         }
@@ -186,9 +190,15 @@ __device__ __forceinline__ void jacobian_values(const DeviceNet &n, const double
                     if (tb + t < t1[u]) v += p;
                 }
             }
-            if (e0 + u * NT < n.nnzJ) jv[e0 + u * NT] = v;
+            if (e0 + u * NT < last) jv[e0 + u * NT - first] = v;
         }
     }
+}
+
+template <int NT>
+__device__ __forceinline__ void jacobian_values(const DeviceNet &n, const double *__restrict__ k, const double *x,
+                                                double *jv) {
+    jacobian_values<NT>(n, k, x, jv, 0, n.nnzJ);
 }
 
 // Entries of M = I - c J of one cell where the factorisation gathers them:

@@ -166,8 +166,9 @@ __host__ __device__ constexpr size_t lu2_dinv_elems(int NP) {
 // level on the matrix cores, one wave per block,
 // X_ij = -X_ii sum_k L_ik X_kj (lower) and Y_ij = -Y_ii sum_k U_ik Y_kj (upper).
 // Xb, Yb: W x kLdb LDS outputs; Tb: 1536 elements of LDS scratch (FP32 only).  Every
-// thread of the workgroup must call this (it contains barriers).
-template <typename T, int NW>
+// thread of the workgroup must call this (it contains barriers).  Without kUpper
+// only the lower one.
+template <typename T, int NW, bool kUpper>
 __device__ __forceinline__ void diag_inverses(const T *Cb, int W, T *D, T *Xb, T *Yb, T *Tb) {
     constexpr int HALF = 32 * NW;   // threads of each triangle
     const int tid = thread_id();
@@ -185,7 +186,7 @@ __device__ __forceinline__ void diag_inverses(const T *Cb, int W, T *D, T *Xb, T
     // several columns in turn)
     for (int hc = h; hc < 64; hc += HALF) {
         const int b = hc >> 4, kc = hc & 15;
-        if (b < nb) {
+        if (b < nb && (kUpper || !upper)) {
             const T *Bd = Cb + 16 * b * kLdb + 16 * b;     // the diagonal block, leading dimension kLdb
             double xs[16];
             if (!upper) {
@@ -226,7 +227,7 @@ __device__ __forceinline__ void diag_inverses(const T *Cb, int W, T *D, T *Xb, T
         using acc_t = typename Mt::acc_t;
         const int wave = wave_of(tid), lane = tid & 63, lr = lane & 15, lg = lane >> 4;
         for (int d = 1; d < nb; ++d) {
-            for (int blk = wave; blk < 2 * (nb - d); blk += NW) {
+            for (int blk = wave; blk < (kUpper ? 2 : 1) * (nb - d); blk += NW) {
                 const bool up = blk >= nb - d;
                 const int bi = up ? blk - (nb - d) : blk;
                 const int i = up ? bi : bi + d, jb = up ? bi + d : bi;
@@ -263,10 +264,11 @@ __device__ __forceinline__ void diag_inverses(const T *Cb, int W, T *D, T *Xb, T
             __syncthreads();
         }
     }
-    for (int e = h; e < 64 * W; e += HALF) D[(upper ? kLuW * kLuW : 0) + e] = Z[(e >> 6) * kLdb + (e & 63)];
+    if (kUpper || !upper)
+        for (int e = h; e < 64 * W; e += HALF) D[(upper ? kLuW * kLuW : 0) + e] = Z[(e >> 6) * kLdb + (e & 63)];
 }
 
-// The value v of lane src (a constant of the unrolled loops), on every lane.
+// The value v of lane src (the same on every lane), on every lane.
 __device__ __forceinline__ double lane_value(double v, int src) {
     const int lo = __builtin_amdgcn_readlane(__double2loint(v), src);
     const int hi = __builtin_amdgcn_readlane(__double2hiint(v), src);
@@ -276,31 +278,76 @@ __device__ __forceinline__ float lane_value(float v, int src) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), src));
 }
 
-// Entries of the matrix to factor as stored in A (storage row, column).  A
-// source yields an entry in two steps: row(r, c0), what the lanes of row r
-// need for the 64 columns from c0 (a multiple of 64), and entry(that, r, col),
-// so that the gather can issue every row's loads before the entry loads that
-// depend on them.
+// Where lu_factor_left keeps the factors: rows in storage order, leading
+// dimension lu_ld(NP), in T (a slot's own storage).
+template <typename T>
+struct SlotStorage {
+    static constexpr bool kKeepInverses = true;   // the solves use them
+    T *A;
+    int lda;
+    using v4 = typename V4<T>::type;
+    // four entries of a row from column c, a multiple of 4
+    __device__ __forceinline__ v4 load4(int row, int c) const {
+        return *reinterpret_cast<const v4 *>(A + uint32_t(row * lda + c));
+    }
+    __device__ __forceinline__ void store(int row, int c, T v) const { A[uint32_t(row * lda + c)] = v; }
+};
+
+// The caller's n x n FP64 matrix itself, factored in place; the padding to a
+// multiple of 16 (the identity's) is not stored, and the rows of L that belong
+// to it are zero.  Rows begin on 8-byte boundaries.
+template <typename T>
+struct DenseStorage {
+    static constexpr bool kKeepInverses = false;
+    double *A;
+    int n;
+    using v4 = typename V4<T>::type;
+    __device__ __forceinline__ v4 load4(int row, int c) const {
+        double d[4];
+        __builtin_memcpy(d, A + uint32_t(min(row, n - 1) * n + c), sizeof(d));
+        v4 v;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = row < n ? T(d[k]) : T(0);
+        return v;
+    }
+    __device__ __forceinline__ void store(int row, int c, T v) const {
+        if (row < n && c < n) A[uint32_t(row * n + c)] = double(v);
+    }
+};
+
+// The entries of the matrix to factor (storage row, column).  A source yields an
+// entry in two steps: row(r, c0), what the lanes of row r need for the 64
+// columns from c0 (a multiple of 64), and entry(that, r, col), so that the
+// gather can issue every row's loads before the entry loads that depend on
+// them.
 template <typename T>
 struct DenseSource {
-    const T *A;
-    int NP;
+    const double *A;
+    int n;
     struct Row { int32_t off; };
-    __device__ __forceinline__ Row row(int r, int) const { return {r * lu_ld(NP)}; }
-    __device__ __forceinline__ T entry(const Row &w, int, int col) const { return A[w.off + col]; }
+    __device__ __forceinline__ Row row(int r, int) const { return {min(r, n - 1) * n}; }
+    __device__ __forceinline__ T entry(const Row &w, int r, int col) const {
+        const double v = A[uint32_t(w.off + min(col, n - 1))];
+        return r < n && col < n ? T(v) : T(r == col ? 1.0 : 0.0);
+    }
 };
 
 // Factors the matrix whose entries src yields (read once, when its block
-// column is gathered) into A: A needs no initial contents.
-template <typename T, int W, typename Src>
-__device__ __forceinline__ void lu_factor_left(T *__restrict__ A, int NP, int32_t *__restrict__ perm_out,
+// column is gathered) into st, which needs no initial contents.  Leaves the row
+// order in LuLds::perm as well as in perm_out [NP] (null: only there).  dinv: the
+// inverse diagonal blocks; unless the storage keeps them for solves, only those
+// of L that later block columns need, one 64 x 64 block after the other.
+template <typename T, int W, typename Src, typename Storage>
+__device__ __forceinline__ void lu_factor_left(const Storage &st, int NP, int32_t *__restrict__ perm_out,
                                                T *__restrict__ dinv, int32_t *info, unsigned char *smem,
                                                const Src &src) {
     using M = Mfma<T>;
     using acc_t = typename M::acc_t;
     using v4 = typename V4<T>::type;
+    constexpr bool kKeep = Storage::kKeepInverses;
+    constexpr int kDinvStride = (kKeep ? 2 : 1) * kLuW * kLuW;
     const int tid0 = thread_id();
-    const int RT = NP / 16, lda = lu_ld(NP);
+    const int RT = NP / 16;
     const int NB = (NP + kLuW - 1) / kLuW;
 
     const LuLds<T, W> lds(NP, smem);
@@ -369,7 +416,7 @@ __device__ __forceinline__ void lu_factor_left(T *__restrict__ A, int NP, int32_
 #pragma unroll 1
         for (int i = 0; i < j; ++i) {
             const int r0 = i * kLuW;
-            const T *Li = dinv + size_t(i) * 2 * kLuW * kLuW;   // inverse of the unit-lower block i
+            const T *Li = dinv + size_t(i) * kDinvStride;   // inverse of the unit-lower block i
             // the 16 tiles of U_ij = inv(L_ii) C_i, spread over all waves (a
             // workgroup of fewer than four waves has one block column)
             constexpr int TPW = W >= 4 ? 16 / W : 1;
@@ -396,9 +443,9 @@ __device__ __forceinline__ void lu_factor_left(T *__restrict__ A, int NP, int32_
             // rows of the first tile below block i that this wave holds
             v4 la[4];
             auto load_tile = [&](int rt) {
-                const T *Lrow = A + size_t(perm[16 * rt + lc]) * lda + r0;
+                const int row = perm[16 * rt + lc];
 #pragma unroll
-                for (int kk = 0; kk < 4; ++kk) la[kk] = *reinterpret_cast<const v4 *>(Lrow + 16 * kk + 4 * g);
+                for (int kk = 0; kk < 4; ++kk) la[kk] = st.load4(row, r0 + 16 * kk + 4 * g);
             };
             {
                 const int below = 4 * (i + 1);
@@ -1057,13 +1104,16 @@ __device__ __forceinline__ void lu_factor_left(T *__restrict__ A, int NP, int32_
                     if (ct < CTj)
 #pragma unroll
                         for (int v = 0; v < 4; ++v)
-                            A[size_t(sto[16 * rt + M::row(lane, v)]) * lda + c0 + 16 * ct + lc] = acc[s][ct][v];
+                            st.store(sto[16 * rt + M::row(lane, v)], c0 + 16 * ct + lc, acc[s][ct][v]);
         }
         __syncthreads();
-        diag_inverses<T, W>(Cb, Wj, dinv + size_t(j) * 2 * kLuW * kLuW, Xb, Ub, Xb + lu2_stage_rows(NP) * kLdb);
-        __syncthreads();
+        if (kKeep || j + 1 < NB) {
+            diag_inverses<T, W, kKeep>(Cb, Wj, dinv + size_t(j) * kDinvStride, Xb, Ub, Xb + lu2_stage_rows(NP) * kLdb);
+            __syncthreads();
+        }
     }
-    for (int i = tid0; i < NP; i += (64 * W)) perm_out[i] = perm[i];
+    if (perm_out)
+        for (int i = tid0; i < NP; i += (64 * W)) perm_out[i] = perm[i];
     if (tid0 == 0 && info) *info = rwave[2] == 0x7fffffff ? 0 : rwave[2];
 }
 
@@ -1087,16 +1137,14 @@ struct SolveOrder {
 };
 
 // Solves (P^T L U) z = b for one matrix factored by lu_factor_left, with the
-// NT threads of a workgroup.  Row r of the factors is storage row rowmap[r]
-// (identity if rowmap is null); y starts as b[bperm[.]] (both are perm in the
-// solver).  b[NP] (LDS, FP64) is read, the solution is left in y[NP] (LDS); t is
+// NT threads of a workgroup.  Row r of the factors is storage row perm[r] (LDS);
+// y starts as b[perm[.]].  b[NP] (LDS, FP64) is read, the solution is left in y[NP] (LDS); t is
 // 64 doubles of LDS scratch.  Factor entries are widened to FP64; the
 // arithmetic is FP64.
 // N (even, 64 (NB - 1) < N <= NP) is the order of the padded matrix: its rows
 // and columns from N on are the identity's, in the matrix and so in its factors
 // (no pivot is taken from them before column N), and b is zero there; the
-// products then stop at N and y keeps its zeros past N.  N = NP for factors
-// of unknown padding.
+// products then stop at N and y keeps its zeros past N.
 //
 // The factor is read once as a stream of 64 x 64 tiles.  No tile's address
 // depends on a result, so each thread keeps its parts of the next kDepth tiles
@@ -1114,7 +1162,7 @@ struct SolveOrder {
 // 16 lanes to a row, 16 bytes (VW entries) a load.
 template <typename T, int NT, int NB, int kDepth>
 __device__ __forceinline__ void lu_solve_left(const T *__restrict__ A, int lda, const T *__restrict__ dinv,
-                                              const int32_t *rowmap, const int32_t *bperm, int NP, int N,
+                                              const int32_t *perm, int NP, int N,
                                               const double *b, double *y, double *t) {
     using Order = SolveOrder<NB>;
     constexpr int VW = 16 / int(sizeof(T));          // factor entries per 16-byte load
@@ -1123,7 +1171,7 @@ __device__ __forceinline__ void lu_solve_left(const T *__restrict__ A, int lda, 
     const int tid = thread_id();
     const int lane16 = tid & 15, row16 = tid >> 4;
     const int Wl = N - kLuW * (NB - 1);              // rows of the last block
-    for (int i = tid; i < NP; i += NT) y[i] = b[bperm[i]];
+    for (int i = tid; i < NP; i += NT) y[i] = b[perm[i]];
     // where this thread's rows of each block row begin, at its first column
     // (rows past the end read the last one again)
     uint32_t off[NB][P];
@@ -1132,7 +1180,7 @@ __device__ __forceinline__ void lu_solve_left(const T *__restrict__ A, int lda, 
 #pragma unroll
         for (int p = 0; p < P; ++p) {
             const int rr = row16 + RP * p, r = ib * kLuW + (ib == NB - 1 ? min(rr, Wl - 1) : rr);
-            off[ib][p] = uint32_t(rowmap ? rowmap[r] : r) * uint32_t(lda) + VW * lane16;
+            off[ib][p] = uint32_t(perm[r]) * uint32_t(lda) + VW * lane16;
         }
     T buf[kDepth][P][H][VW];
     // The zero side of a triangle's inverse is not read: a column there loads the
@@ -1250,10 +1298,10 @@ __device__ __forceinline__ void lu_solve_left(const T *__restrict__ A, int lda, 
 // The same for any order: NB = ceil(N / 64).
 template <typename T, int NT, int kDepth>
 __device__ __forceinline__ void lu_solve_left(const T *__restrict__ A, int lda, const T *__restrict__ dinv,
-                                              const int32_t *rowmap, const int32_t *bperm, int NP, int N,
+                                              const int32_t *perm, int NP, int N,
                                               const double *b, double *y, double *t) {
 #define ABDF_SOLVE(NB) \
-    case NB: lu_solve_left<T, NT, NB, kDepth>(A, lda, dinv, rowmap, bperm, NP, N, b, y, t); break
+    case NB: lu_solve_left<T, NT, NB, kDepth>(A, lda, dinv, perm, NP, N, b, y, t); break
     switch ((N + kLuW - 1) / kLuW) {
         ABDF_SOLVE(1);
         ABDF_SOLVE(2);
@@ -1262,7 +1310,7 @@ __device__ __forceinline__ void lu_solve_left(const T *__restrict__ A, int lda, 
         ABDF_SOLVE(5);
         ABDF_SOLVE(6);
         ABDF_SOLVE(7);
-        default: lu_solve_left<T, NT, 8, kDepth>(A, lda, dinv, rowmap, bperm, NP, N, b, y, t); break;
+        default: lu_solve_left<T, NT, 8, kDepth>(A, lda, dinv, perm, NP, N, b, y, t); break;
     }
 #undef ABDF_SOLVE
 }

@@ -172,7 +172,7 @@ struct TinyCell {
     // M = I - c J factored; the inverses of its triangles and the row order stay
     // in LDS for the solves.
     __device__ __forceinline__ void factor(const Slots &s, int slot, double c) {
-        lu_factor_left<T, 1>(slot_lu<T>(s, slot), NP, s.perm + size_t(slot) * NP, slot_dinv<T>(s, slot), nullptr, lu,
+        lu_factor_left<T, 1>(SlotStorage<T>{slot_lu<T>(s, slot), lu_ld(NP)}, NP, s.perm + size_t(slot) * NP, slot_dinv<T>(s, slot), nullptr, lu,
                              TinySource<T>{J, S, ld, c});
         wave_lds_order();
     }

@@ -381,8 +381,6 @@ __global__ void k_grad_sum(const double *g_cell, long long cells, int R, double 
     out[r] = acc;
 }
 
-constexpr int kAsmThreads = 512;   // workgroup of the stand-alone Newton-matrix assembly
-
 // dL/dphi of one cell (one workgroup) from its dL/dlog alpha: five sums over
 // reactions of g_r d log k_r / d phi_j (paper Sec. 2, App. B.1 rate laws).
 __global__ void __launch_bounds__(kBlock) k_phys_grad(DeviceNet n, PhysArgs p, const double *g_cell, double *out) {
@@ -484,96 +482,38 @@ k_rhs_stream(DeviceNet n, long long C, const double *__restrict__ k, const doubl
     }
 }
 
-// Writes the unpadded S x S Newton matrix of each cell through the solver's
-// own path: the Jacobian nonzeros at x (jacobian_values, into the scratch jv of
-// nnzJ doubles per cell), then every entry as NewtonMatrixSource yields it to
-// the factorisation's gather.
+// Writes the unpadded S x S Newton matrix of each cell, kAsmRows rows a
+// workgroup: the rows' Jacobian nonzeros (jacobian_values) go to LDS, and every
+// entry is written as NewtonMatrixSource yields it to the factorisation's
+// gather, a wave to a row, 64 columns at a time.  A call of 192 cells of 200
+// species (61 MB written) took 186 us with one workgroup a cell, the nonzeros in
+// global scratch allocated by the call and two integer divisions an entry, and
+// takes 127 us.
+constexpr int kAsmThreads = 256, kAsmRows = 16;
+
 __global__ void __launch_bounds__(kAsmThreads) k_newton_matrix_only(DeviceNet n, const double *k, const double *x,
-                                                                  const double *cvec, double *jv, double *M) {
+                                                                  const double *cvec, double *M) {
     extern __shared__ double smem[];
-    const long long c = blockIdx.x;
-    double *xs = smem;
-    for (int i = threadIdx.x; i < n.S; i += kAsmThreads) xs[i] = x[size_t(c) * n.S + i];
+    const long long cell = blockIdx.y;
+    const int S = n.S, r0 = blockIdx.x * kAsmRows, r1 = min(r0 + kAsmRows, S);
+    double *xs = smem, *jv = xs + S;
+    for (int i = threadIdx.x; i < S; i += kAsmThreads) xs[i] = x[size_t(cell) * S + i];
+    const int e0 = n.jrow_ptr[r0], e1 = n.jrow_ptr[r1];
     __syncthreads();
-    double *jvc = jv + size_t(c) * max(n.nnzJ, 1);
-    jacobian_values<kAsmThreads>(n, k + size_t(c) * n.R, xs, jvc);
+    jacobian_values<kAsmThreads>(n, k + size_t(cell) * n.R, xs, jv, e0, e1);
     __syncthreads();
-    const NewtonMatrixSource<double> src{n.jmask, n.jbase, n.nbw, jvc, cvec[c]};
-    for (size_t e = threadIdx.x; e < size_t(n.S) * n.S; e += kAsmThreads) {
-        const int i = int(e / n.S), j = int(e % n.S);
-        M[size_t(c) * n.S * n.S + e] = src.entry(src.row(i, j & ~63), i, j);
+    const double c = cvec[cell];
+    const int lane = threadIdx.x & 63;
+    for (int i = r0 + wave_of(threadIdx.x); i < r1; i += kAsmThreads / 64) {
+        const NewtonMatrixSource<double> src{n.jmask, n.jbase, n.nbw, jv, c};
+        double *row = M + (size_t(cell) * S + i) * S;
+        for (int c0 = 0; c0 < S; c0 += 64) {
+            const int j = c0 + lane;
+            auto w = src.row(i, c0);
+            w.base -= e0;
+            if (j < S) row[j] = src.entry(w, i, j);
+        }
     }
-}
-
-// Copies an n x n matrix into the padded NP x NP work matrix (identity padding) and back.
-template <typename T>
-__global__ void k_pad_in(int n, int NP, const double *A, T *W) {
-    const long long b = blockIdx.y, ld = lu_ld(NP);
-    for (long long e = blockIdx.x * blockDim.x + threadIdx.x; e < (long long)NP * NP; e += gridDim.x * blockDim.x) {
-        const int i = int(e / NP), j = int(e % NP);
-        double v = (i < n && j < n) ? A[(b * n + i) * n + j] : (i == j ? 1.0 : 0.0);
-        W[(b * NP + i) * ld + j] = T(v);
-    }
-}
-
-// Factors (rows in storage order, row i of P A at storage row permW[i]) back
-// to the LAPACK layout: row i of the output is row i of P A.
-template <typename T>
-__global__ void k_pad_out(int n, int NP, const T *W, double *A, const int32_t *permW, int32_t *perm) {
-    const long long b = blockIdx.y;
-    for (long long e = blockIdx.x * blockDim.x + threadIdx.x; e < (long long)n * n; e += gridDim.x * blockDim.x) {
-        const int i = int(e / n), j = int(e % n);
-        A[(b * n + i) * n + j] = double(W[(b * NP + permW[b * NP + i]) * (long long)lu_ld(NP) + j]);
-    }
-    if (blockIdx.x == 0)
-        for (int i = threadIdx.x; i < n; i += blockDim.x) perm[b * n + i] = permW[b * NP + i];
-}
-
-__global__ void k_copy_perm(int n, int NP, const int32_t *perm, int32_t *permW) {
-    const long long b = blockIdx.x;
-    for (int i = threadIdx.x; i < NP; i += blockDim.x) permW[b * NP + i] = i < n ? perm[b * n + i] : i;
-}
-
-template <typename T, int W>
-__global__ void __launch_bounds__(64 * W) k_lu_factor_only(int NP, T *A0, int32_t *permW, T *dinv, int32_t *info) {
-    extern __shared__ double smem[];
-    const long long b = blockIdx.x;
-    T *A = A0 + b * NP * lu_ld(NP);
-    lu_factor_left<T, W>(A, NP, permW + b * NP, dinv + b * lu2_dinv_elems<T>(NP), info ? info + b : nullptr,
-                      reinterpret_cast<unsigned char *>(smem), DenseSource<T>{A, NP});
-}
-
-constexpr int kDinvThreads = 512;
-
-// Inverse diagonal blocks of LAPACK-layout factors (rows already in P A order).
-__global__ void __launch_bounds__(kDinvThreads) k_dinv_only(int NP, const double *W, double *dinv) {
-    extern __shared__ double smem[];
-    const long long b = blockIdx.x;
-    double *Cb = smem, *Xb = Cb + kLuW * kLdb, *Yb = Xb + kLuW * kLdb;
-    for (int j = 0; j * kLuW < NP; ++j) {
-        const int r0 = j * kLuW, Wj = min(kLuW, NP - r0);
-        for (int e = threadIdx.x; e < Wj * Wj; e += kDinvThreads)
-            Cb[(e / Wj) * kLdb + e % Wj] = W[(b * NP + r0 + e / Wj) * (long long)lu_ld(NP) + r0 + e % Wj];
-        __syncthreads();
-        diag_inverses<double, kDinvThreads / 64>(Cb, Wj, dinv + b * lu2_dinv_elems<double>(NP) + size_t(j) * 2 * kLuW * kLuW, Xb, Yb,
-                              nullptr);
-        __syncthreads();
-    }
-}
-
-__global__ void __launch_bounds__(kBlock) k_lu_solve_only(int NP, int n, const double *W, const double *dinv,
-                                                          const int32_t *permW, double *bvec) {
-    extern __shared__ double smem[];
-    __shared__ double t[kLuW];
-    const long long bi = blockIdx.x;
-    double *b = smem, *y = b + NP;
-    for (int i = threadIdx.x; i < NP; i += kBlock) b[i] = i < n ? bvec[bi * n + i] : 0.0;
-    __syncthreads();
-    // the padding past n is the identity's (k_pad_in, k_copy_perm)
-    lu_solve_left<double, kBlock, 2>(W + bi * NP * lu_ld(NP), lu_ld(NP), dinv + bi * lu2_dinv_elems<double>(NP), nullptr,
-                                     permW + bi * NP, NP,
-                          min(NP, n + (n & 1)), b, y, t);
-    for (int i = threadIdx.x; i < n; i += kBlock) bvec[bi * n + i] = y[i];
 }
 
 // Matrix-core lane-layout check: D = A B for integer-valued A (16x4), B (4x16).
@@ -736,43 +676,17 @@ hipError_t launch_rhs_planned(const RhsPlan &p, const DeviceNet &n, long long ce
 }
 
 hipError_t launch_newton_matrix(const DeviceNet &n, long long cells, const double *k, const double *x,
-                                const double *c, double *M, double *jv, hipStream_t st) {
-    const size_t lds = sizeof(double) * size_t(n.S);
-    hipLaunchKernelGGL(k_newton_matrix_only, dim3(cells), dim3(kAsmThreads), lds, st, n, k, x, c, jv, M);
-    return LAUNCH_CHECK();
-}
-
-// Waves of the standalone factorisation: of 256 VGPRs, each holding four row
-// tiles of the block column.
-constexpr int kLuWaves = 8;
-
-hipError_t launch_lu_factor(int n, int NP, long long batch, double *A, void *W, int32_t *permW, int32_t *perm,
-                            void *dinv, int32_t *info, int prec, hipStream_t st) {
-    dim3 g(std::max(1, std::min(64, (NP * NP + 255) / 256)), unsigned(batch));
-    if (prec == ABDF_PREC_FP32_LU) {
-        hipLaunchKernelGGL(k_pad_in<float>, g, dim3(256), 0, st, n, NP, A, (float *)W);
-        hipLaunchKernelGGL((k_lu_factor_only<float, kLuWaves>), dim3(batch), dim3(64 * kLuWaves), (lu2_lds_bytes<float, kLuWaves>(NP)), st, NP,
-                           (float *)W, permW, (float *)dinv, info);
-        hipLaunchKernelGGL(k_pad_out<float>, g, dim3(256), 0, st, n, NP, (const float *)W, A, permW, perm);
-    } else {
-        hipLaunchKernelGGL(k_pad_in<double>, g, dim3(256), 0, st, n, NP, A, (double *)W);
-        hipLaunchKernelGGL((k_lu_factor_only<double, kLuWaves>), dim3(batch), dim3(64 * kLuWaves), (lu2_lds_bytes<double, kLuWaves>(NP)), st,
-                           NP, (double *)W, permW, (double *)dinv, info);
-        hipLaunchKernelGGL(k_pad_out<double>, g, dim3(256), 0, st, n, NP, (const double *)W, A, permW, perm);
+                                const double *c, double *M, hipStream_t st) {
+    // grid.y holds at most 65535 cells
+    const size_t lds = sizeof(double) * (size_t(n.S) + size_t(std::max(n.asm_nnz, 1)));
+    for (long long c0 = 0; c0 < cells; c0 += 65535) {
+        const unsigned m = unsigned(std::min<long long>(65535, cells - c0));
+        hipLaunchKernelGGL(k_newton_matrix_only, dim3((n.S + kAsmRows - 1) / kAsmRows, m), dim3(kAsmThreads), lds, st, n,
+                           k + size_t(c0) * n.R, x + size_t(c0) * n.S, c + c0, M + size_t(c0) * n.S * n.S);
+        const hipError_t e = LAUNCH_CHECK();
+        if (e != hipSuccess) return e;
     }
-    return LAUNCH_CHECK();
-}
-
-hipError_t launch_lu_solve(int n, int NP, long long batch, const double *LU, const int32_t *perm, double *b,
-                           void *W, int32_t *permW, void *dinv, hipStream_t st) {
-    dim3 g(std::max(1, std::min(64, (NP * NP + 255) / 256)), unsigned(batch));
-    hipLaunchKernelGGL(k_pad_in<double>, g, dim3(256), 0, st, n, NP, LU, (double *)W);
-    hipLaunchKernelGGL(k_copy_perm, dim3(unsigned(batch)), dim3(256), 0, st, n, NP, perm, permW);
-    hipLaunchKernelGGL(k_dinv_only, dim3(batch), dim3(kDinvThreads), sizeof(double) * 3 * kLuW * kLdb, st,
-                       NP, (const double *)W, (double *)dinv);
-    hipLaunchKernelGGL(k_lu_solve_only, dim3(batch), dim3(kBlock), sizeof(double) * 2 * NP, st, NP, n,
-                       (const double *)W, (const double *)dinv, permW, b);
-    return LAUNCH_CHECK();
+    return hipSuccess;
 }
 
 hipError_t launch_selftest(int *bad, hipStream_t st) {

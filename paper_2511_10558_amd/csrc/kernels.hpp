@@ -100,13 +100,18 @@ hipError_t plan_rhs(const DeviceNet &n, long long cells, RhsPlan &p);
 // start and end.
 hipError_t launch_rhs_planned(const RhsPlan &p, const DeviceNet &n, long long cells, const double *k, const double *x,
                               double *f, hipStream_t st, hipEvent_t start = nullptr, hipEvent_t stop = nullptr);
-// jv: scratch of cells * max(nnzJ, 1) doubles (the Jacobian nonzeros)
 hipError_t launch_newton_matrix(const DeviceNet &n, long long cells, const double *k, const double *x,
-                                const double *c, double *M, double *jv, hipStream_t st);
-hipError_t launch_lu_factor(int n, int NP, long long batch, double *A, void *W, int32_t *permW, int32_t *perm,
-                            void *dinv, int32_t *info, int prec, hipStream_t st);
-hipError_t launch_lu_solve(int n, int NP, long long batch, const double *LU, const int32_t *perm, double *b,
-                           void *W, int32_t *permW, void *dinv, hipStream_t st);
+                                const double *c, double *M, hipStream_t st);
+// Factorisation in place of a batch of n x n matrices; scratch: bytes.
+struct LuFactorPlan {
+    const void *fn = nullptr;
+    int grid = 0;
+    size_t lds = 0, scratch = 0;
+};
+LuFactorPlan plan_lu_factor(int n, long long batch, int prec);
+hipError_t launch_lu_factor(const LuFactorPlan &p, int n, long long batch, double *A, int32_t *perm, int32_t *info,
+                            void *scratch, hipStream_t st);
+hipError_t launch_lu_solve(int n, long long batch, const double *LU, const int32_t *perm, double *b, hipStream_t st);
 size_t dinv_bytes(int NP, int prec);
 size_t lu_bytes(int NP, int prec);
 hipError_t launch_selftest(int *bad, hipStream_t st);

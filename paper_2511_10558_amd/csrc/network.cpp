@@ -527,6 +527,9 @@ const DeviceNet *HostNetwork::device_tables(std::string &err) const {
     chk(upload(&d->jbase, jbase));
     d->nbw = (NP + 63) / 64;
     d->n_sgroup = int32_t(sg_base.size());
+    d->asm_nnz = 0;
+    for (int r0 = 0; r0 < S; r0 += 16)
+        d->asm_nnz = std::max(d->asm_nnz, jrow_ptr[size_t(std::min(r0 + 16, S))] - jrow_ptr[size_t(r0)]);
     d->sg_maxlen = 0;
     d->sg_total = int32_t(sg_ent.size());
     for (int32_t w : sg_len) d->sg_maxlen = std::max(d->sg_maxlen, w & 0xffffff);

@@ -52,6 +52,7 @@ struct DeviceNet {
     int32_t *jt_rx_other = nullptr;  // reaction << 16 | (other species + 1), 0 in the low half = none
     double *jt_coef = nullptr;     // [nterm] nu_ir * multiplicity
     int32_t nnzJ = 0, nterm = 0;
+    int32_t asm_nnz = 0;           // most nonzeros in 16 consecutive rows from a multiple of 16
     // reaction-major stoichiometry: the species of reaction r with nu != 0
     int32_t *rnu_ptr = nullptr;    // [R+1]
     int32_t *rnu_ent = nullptr;    // species << 3 | (nu + 4)

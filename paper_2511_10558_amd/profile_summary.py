@@ -32,6 +32,7 @@ ROOT = os.path.dirname(HERE)
 PROFILES = os.path.join(ROOT, "profiles")
 KERNEL_SOURCES = ["paper_2511_10558_amd/csrc/device_lu2.hpp", "paper_2511_10558_amd/csrc/device_lu.hpp",
                   "paper_2511_10558_amd/csrc/device_chem.hpp", "paper_2511_10558_amd/csrc/kernels.hip",
+                  "paper_2511_10558_amd/csrc/lu_batch.hip",
                   "paper_2511_10558_amd/csrc/integrate.hip", "paper_2511_10558_amd/csrc/device_step.hpp",
                   "paper_2511_10558_amd/csrc/device_tiny.hpp",
                   "paper_2511_10558_amd/csrc/integrate_kernels.hpp",

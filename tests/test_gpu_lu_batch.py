@@ -1,0 +1,36 @@
+"""Batched in-place factorisation and solve at the edges of their tiles (GPU)."""
+import numpy as np
+import pytest
+
+from tests.gpu_util import device, t
+
+pytestmark = pytest.mark.gpu
+
+
+# orders one short of, at and past the 16-wide tiles and the 64-wide block
+# columns, and the widest; a batch of small ones larger than what is resident
+@pytest.mark.parametrize("n,batch", [(15, 2500), (16, 3), (17, 3), (63, 3), (64, 3), (65, 5), (129, 3), (257, 3),
+                                     (449, 3), (511, 3), (512, 2)])
+@pytest.mark.parametrize("prec", ["fp64", "fp32_lu"])
+def test_lu_in_place_at_tile_edges(n, batch, prec):
+    # every second matrix keeps its rows in place, the others exchange
+    # them.  Bounds: a factor entry sums at most n products of |L| <= 4 with |U|
+    # (30 n u max |A|, as for the other orders), a solution two such triangular
+    # solves.
+    import paper_2511_10558_amd as ab
+    dev = device()
+    rng = np.random.default_rng(n)
+    A = rng.normal(size=(batch, n, n))
+    A[::2] = np.eye(n) + 0.3 / np.sqrt(n) * A[::2]
+    b = rng.normal(size=(batch, n))
+    LU, perm, info = ab.lu_factor(t(A, dev), precision=prec)
+    assert not info.any()
+    u = np.finfo(np.float64 if prec == "fp64" else np.float32).eps / 2
+    z = ab.lu_solve(LU, perm, t(b, dev)).cpu().numpy()
+    LU, perm = LU.cpu().numpy(), perm.cpu().numpy()
+    for i in range(min(batch, 3)) if batch < 100 else (0, 1, 1023, batch - 2, batch - 1):
+        L, U = np.tril(LU[i], -1) + np.eye(n), np.triu(LU[i])
+        assert sorted(perm[i]) == list(range(n)) and np.abs(L).max() <= 4.0 * (1 + 1e-6)
+        assert np.abs(A[i][perm[i]] - L @ U).max() <= 30 * n * u * np.abs(A[i]).max()
+        res = np.abs(A[i] @ z[i] - b[i]).max() / (np.abs(A[i]).max() * np.abs(z[i]).max())
+        assert res <= 60 * n * u
