@@ -53,7 +53,7 @@ constexpr double kPivotThreshold = 4.0;
 // panel); each wave holds row tiles w, w + W, ... of the block column in at most
 // lu_slots accumulator tiles.
 template <int W>
-constexpr int lu_slots = W >= 8 ? kLuMaxNP / 16 / W : 4;
+constexpr int lu_slots = kLuMaxNP / 16 / (W >= 8 ? W : 8);
 constexpr int lu_wave_bits(int w) { return w <= 1 ? 0 : 1 + lu_wave_bits(w / 2); }
 constexpr int kLdb = 65;          // LDS leading dimension of 64-wide staging buffers
 
@@ -336,8 +336,9 @@ struct DenseSource {
 // column is gathered) into st, which needs no initial contents.  Leaves the row
 // order in LuLds::perm as well as in perm_out [NP] (null: only there).  dinv: the
 // inverse diagonal blocks; unless the storage keeps them for solves, only those
-// of L that later block columns need, one 64 x 64 block after the other.
-template <typename T, int W, typename Src, typename Storage>
+// of L that later block columns need, one 64 x 64 block after the other.  A single
+// wave (W = 1) holds kTiles x kTiles tiles, NP <= 16 kTiles.
+template <typename T, int W, int kTiles, typename Src, typename Storage>
 __device__ __forceinline__ void lu_factor_left(const Storage &st, int NP, int32_t *__restrict__ perm_out,
                                                T *__restrict__ dinv, int32_t *info, unsigned char *smem,
                                                const Src &src) {
@@ -345,6 +346,7 @@ __device__ __forceinline__ void lu_factor_left(const Storage &st, int NP, int32_
     using acc_t = typename M::acc_t;
     using v4 = typename V4<T>::type;
     constexpr bool kKeep = Storage::kKeepInverses;
+    constexpr int kSlots = W == 1 ? kTiles : lu_slots<W>, kCT = W == 1 ? kTiles : 4;
     constexpr int kDinvStride = (kKeep ? 2 : 1) * kLuW * kLuW;
     const int tid0 = thread_id();
     const int RT = NP / 16;
@@ -377,30 +379,30 @@ __device__ __forceinline__ void lu_factor_left(const Storage &st, int NP, int32_
             log_pos[q] = q;
             pidx[q] = -1;
         }
-        acc_t acc[lu_slots<W>][4];
+        acc_t acc[kSlots][kCT];
         // 1. gather the block column (positions = logical rows at this point):
         //    what each of the lane's rows needs first, then every entry, so
         //    that each lane has all its row loads in flight together and then
         //    all its entry loads (the accumulators are not live yet).  Tiles
         //    outside the matrix read column c0 + lc of row 0 and are zeroed.
         {
-            typename Src::Row rw[lu_slots<W>][4];
-            int srow[lu_slots<W>][4];
+            typename Src::Row rw[kSlots][4];
+            int srow[kSlots][4];
 #pragma unroll
-            for (int s = 0; s < lu_slots<W>; ++s) {
+            for (int s = 0; s < kSlots; ++s) {
                 const int rt = wave + W * s;
 #pragma unroll
                 for (int v = 0; v < 4; ++v) srow[s][v] = rt < RT ? perm[16 * rt + M::row(lane, v)] : 0;
             }
 #pragma unroll
-            for (int s = 0; s < lu_slots<W>; ++s)
+            for (int s = 0; s < kSlots; ++s)
 #pragma unroll
                 for (int v = 0; v < 4; ++v) rw[s][v] = src.row(srow[s][v], c0);
 #pragma unroll
-            for (int s = 0; s < lu_slots<W>; ++s) {
+            for (int s = 0; s < kSlots; ++s) {
                 const int rt = wave + W * s;
 #pragma unroll
-                for (int ct = 0; ct < 4; ++ct)
+                for (int ct = 0; ct < kCT; ++ct)
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
                         const T val = src.entry(rw[s][v], srow[s][v], c0 + 16 * (ct < CTj ? ct : 0) + lc);
@@ -428,11 +430,11 @@ __device__ __forceinline__ void lu_factor_left(const Storage &st, int NP, int32_
                     ia[kk] = *reinterpret_cast<const v4 *>(Li + (16 * tr + lc) * kLuW + 16 * kk + 4 * g);
             }
 #pragma unroll
-            for (int s = 0; s < lu_slots<W>; ++s) {
+            for (int s = 0; s < kSlots; ++s) {
                 const int rt = wave + W * s;
                 if (rt >= 4 * i && rt < 4 * i + 4) {
 #pragma unroll
-                    for (int ct = 0; ct < 4; ++ct)
+                    for (int ct = 0; ct < kCT; ++ct)
                         if (ct < CTj)
 #pragma unroll
                             for (int v = 0; v < 4; ++v)
@@ -472,12 +474,12 @@ __device__ __forceinline__ void lu_factor_left(const Storage &st, int NP, int32_
             // the rows of block i take their tiles of U_ij; the rows below are
             // updated C -= L_{:,i} U_ij
 #pragma unroll
-            for (int s = 0; s < lu_slots<W>; ++s) {
+            for (int s = 0; s < kSlots; ++s) {
                 const int rt = wave + W * s;
                 if (rt >= 4 * i && rt < 4 * i + 4) {
                     const int tr = rt - 4 * i;
 #pragma unroll
-                    for (int ct = 0; ct < 4; ++ct)
+                    for (int ct = 0; ct < kCT; ++ct)
                         if (ct < CTj)
 #pragma unroll
                             for (int v = 0; v < 4; ++v) acc[s][ct][v] = Ub[(16 * tr + M::row(lane, v)) * kLdb + 16 * ct + lc];
@@ -493,7 +495,7 @@ __device__ __forceinline__ void lu_factor_left(const Storage &st, int NP, int32_
 #pragma unroll
                             for (int e = 0; e < 4; ++e)
 #pragma unroll
-                                for (int ct = 0; ct < 4; ++ct)
+                                for (int ct = 0; ct < kCT; ++ct)
                                     acc[s][ct] = M::mma(-a[kk][e], Ub[(16 * kk + 4 * g + e) * kLdb + 16 * ct + lc],
                                                         acc[s][ct]);
                     } else {
@@ -502,7 +504,7 @@ __device__ __forceinline__ void lu_factor_left(const Storage &st, int NP, int32_
 #pragma unroll
                             for (int e = 0; e < 4; ++e)
 #pragma unroll
-                                for (int ct = 0; ct < 3; ++ct)
+                                for (int ct = 0; ct < (kCT < 3 ? kCT : 3); ++ct)
                                     if (ct < CTj)
                                         acc[s][ct] = M::mma(-a[kk][e], Ub[(16 * kk + 4 * g + e) * kLdb + 16 * ct + lc],
                                                             acc[s][ct]);
@@ -523,7 +525,7 @@ __device__ __forceinline__ void lu_factor_left(const Storage &st, int NP, int32_
         //    general loop alone, timed over a batch of 256 matrices; 9.7 this
         //    way, timed inside a solve of 512 cells.)
         int from = CTj;      // the first sub-panel left to the general loop
-        static_for<4>([&](auto spc) __attribute__((always_inline)) {
+        static_for<kCT>([&](auto spc) __attribute__((always_inline)) {
             constexpr int sp = decltype(spc)::value;
             if (sp >= from) return;
             const int tid = thread_id(), lane = tid & 63, wave = wave_of(tid);
@@ -532,7 +534,7 @@ __device__ __forceinline__ void lu_factor_left(const Storage &st, int NP, int32_
             // (a) the sub-panel's column tile to LDS, one row per position (the
             //     accumulators keep it until (c))
 #pragma unroll
-            for (int s = 0; s < lu_slots<W>; ++s) {
+            for (int s = 0; s < kSlots; ++s) {
                 const int rt = wave + W * s;
                 if (rt >= dt && rt < RT)
 #pragma unroll
@@ -664,7 +666,7 @@ __device__ __forceinline__ void lu_factor_left(const Storage &st, int NP, int32_
             //     column tiles of the block to LDS
             const int nct = CTj - sp - 1;
 #pragma unroll
-            for (int s = 0; s < lu_slots<W>; ++s) {
+            for (int s = 0; s < kSlots; ++s) {
                 const int rt = wave + W * s;
                 if (rt >= dt && rt < RT) {
                     const T *src = rt == dt ? Db : P + 16 * rt * kPanLd;
@@ -672,7 +674,7 @@ __device__ __forceinline__ void lu_factor_left(const Storage &st, int NP, int32_
                     for (int v = 0; v < 4; ++v) acc[s][sp][v] = src[M::row(lane, v) * kPanLd + lc];
                     if (rt == dt) {
 #pragma unroll
-                        for (int ct = sp + 1; ct < 4; ++ct)
+                        for (int ct = sp + 1; ct < kCT; ++ct)
                             if (ct < CTj)
 #pragma unroll
                                 for (int v = 0; v < 4; ++v)
@@ -699,14 +701,14 @@ __device__ __forceinline__ void lu_factor_left(const Storage &st, int NP, int32_
                 __syncthreads();
                 // the rows below
 #pragma unroll
-                for (int s = 0; s < lu_slots<W>; ++s) {
+                for (int s = 0; s < kSlots; ++s) {
                     const int rt = wave + W * s;
                     if (rt > dt && rt < RT) {
                         T a[4];
 #pragma unroll
                         for (int e = 0; e < 4; ++e) a[e] = -P[(16 * rt + lc) * kPanLd + 4 * e + g];
 #pragma unroll
-                        for (int ct = sp + 1; ct < 4; ++ct)
+                        for (int ct = sp + 1; ct < kCT; ++ct)
                             if (ct < CTj)
 #pragma unroll
                                 for (int e = 0; e < 4; ++e)
@@ -715,7 +717,7 @@ __device__ __forceinline__ void lu_factor_left(const Storage &st, int NP, int32_
                     }
                     if (rt == dt) {
 #pragma unroll
-                        for (int ct = sp + 1; ct < 4; ++ct)
+                        for (int ct = sp + 1; ct < kCT; ++ct)
                             if (ct < CTj)
 #pragma unroll
                                 for (int v = 0; v < 4; ++v)
@@ -733,14 +735,14 @@ __device__ __forceinline__ void lu_factor_left(const Storage &st, int NP, int32_
             //     accumulators keep it until (c), so it can be written again)
             auto panel_to_lds = [&]() {
 #pragma unroll
-                for (int s = 0; s < lu_slots<W>; ++s) {
+                for (int s = 0; s < kSlots; ++s) {
                     const int rt = wave + W * s;
                     if (rt >= 4 * j && rt < RT)
 #pragma unroll
                         for (int v = 0; v < 4; ++v) {
                             T val = acc[s][0][v];
 #pragma unroll
-                            for (int ct = 1; ct < 4; ++ct)
+                            for (int ct = 1; ct < kCT; ++ct)
                                 if (ct == sp) val = acc[s][ct][v];
                             P[(16 * rt + M::row(lane, v)) * kPanLd + lc] = val;
                         }
@@ -1002,14 +1004,14 @@ __device__ __forceinline__ void lu_factor_left(const Storage &st, int NP, int32_
             }   // partial pivoting
             // (c) back to the accumulators
 #pragma unroll
-            for (int s = 0; s < lu_slots<W>; ++s) {
+            for (int s = 0; s < kSlots; ++s) {
                 const int rt = wave + W * s;
                 if (rt >= 4 * j && rt < RT)
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
                         const T val = P[(16 * rt + M::row(lane, v)) * kPanLd + lc];
 #pragma unroll
-                        for (int ct = 0; ct < 4; ++ct)
+                        for (int ct = 0; ct < kCT; ++ct)
                             if (ct == sp) acc[s][ct][v] = val;
                     }
             }
@@ -1018,11 +1020,11 @@ __device__ __forceinline__ void lu_factor_left(const Storage &st, int NP, int32_
             if (sp + 1 < CTj) {
                 const int nct = CTj - sp - 1;
 #pragma unroll
-                for (int s = 0; s < lu_slots<W>; ++s) {
+                for (int s = 0; s < kSlots; ++s) {
                     const int rt = wave + W * s;
                     if (rt >= 4 * j && rt < RT)
 #pragma unroll
-                        for (int ct = 1; ct < 4; ++ct)
+                        for (int ct = 1; ct < kCT; ++ct)
                             if (ct > sp && ct < CTj)
 #pragma unroll
                                 for (int v = 0; v < 4; ++v) {
@@ -1047,7 +1049,7 @@ __device__ __forceinline__ void lu_factor_left(const Storage &st, int NP, int32_
                 }
                 __syncthreads();
 #pragma unroll
-                for (int s = 0; s < lu_slots<W>; ++s) {
+                for (int s = 0; s < kSlots; ++s) {
                     const int rt = wave + W * s;
                     if (rt >= 4 * j && rt < RT) {
                         const bool unused = pidx[16 * rt + lc] < 0;
@@ -1055,7 +1057,7 @@ __device__ __forceinline__ void lu_factor_left(const Storage &st, int NP, int32_
 #pragma unroll
                         for (int e = 0; e < 4; ++e) a[e] = unused ? -P[(16 * rt + lc) * kPanLd + 4 * e + g] : T(0);
 #pragma unroll
-                        for (int ct = 1; ct < 4; ++ct) {
+                        for (int ct = 1; ct < kCT; ++ct) {
                             if (ct > sp && ct < CTj) {
 #pragma unroll
                                 for (int e = 0; e < 4; ++e)
@@ -1081,11 +1083,11 @@ __device__ __forceinline__ void lu_factor_left(const Storage &st, int NP, int32_
         // 4. diagonal block (logical rows c0 .. c0 + Wj - 1) to LDS, its
         //    triangles' inverses, and the block column back to its storage rows
 #pragma unroll
-        for (int s = 0; s < lu_slots<W>; ++s) {
+        for (int s = 0; s < kSlots; ++s) {
             const int rt = wave + W * s;
             if (rt >= 4 * j && rt < RT)
 #pragma unroll
-                for (int ct = 0; ct < 4; ++ct)
+                for (int ct = 0; ct < kCT; ++ct)
                     if (ct < CTj)
 #pragma unroll
                         for (int v = 0; v < 4; ++v) {
@@ -1096,11 +1098,11 @@ __device__ __forceinline__ void lu_factor_left(const Storage &st, int NP, int32_
         // the block column goes back first, so that the accumulators are free
         // while the inverses are formed
 #pragma unroll
-        for (int s = 0; s < lu_slots<W>; ++s) {
+        for (int s = 0; s < kSlots; ++s) {
             const int rt = wave + W * s;
             if (rt < RT)
 #pragma unroll
-                for (int ct = 0; ct < 4; ++ct)
+                for (int ct = 0; ct < kCT; ++ct)
                     if (ct < CTj)
 #pragma unroll
                         for (int v = 0; v < 4; ++v)

@@ -426,7 +426,7 @@ __device__ __forceinline__ void factor_slot(const Slots &s, const DeviceNet &n, 
         __syncthreads();
     }
     NewtonMatrixSource<T> src{n.jmask, n.jbase, n.nbw, jv, uniform(cs.c)};
-    lu_factor_left<T, W>(SlotStorage<T>{slot_lu<T>(s, slot), lu_ld(NP)}, NP, s.perm + size_t(slot) * NP, slot_dinv<T>(s, slot), nullptr,
+    lu_factor_left<T, W, 4>(SlotStorage<T>{slot_lu<T>(s, slot), lu_ld(NP)}, NP, s.perm + size_t(slot) * NP, slot_dinv<T>(s, slot), nullptr,
                          reinterpret_cast<unsigned char *>(smem), src);
     __syncthreads();
 }

@@ -62,7 +62,7 @@ struct TinySource {
     }
 };
 
-template <typename T>
+template <typename T, int kTiles>
 struct TinyCell {
     int S, R, NP, ld, ng;
     unsigned char *lu;       // lu_factor_left's LDS block
@@ -158,7 +158,7 @@ struct TinyCell {
     __device__ __forceinline__ void jacobian(const DeviceNet &n, const double *xJ, double *jv) {
         if (int(threadIdx.x) < S) xs[threadIdx.x] = xJ[threadIdx.x];
         wave_lds_order();
-        jacobian_values<64>(n, k, xs, jv);
+        jacobian_values<64, 2, 4>(n, k, xs, jv);
         scatter(n, jv);
     }
     // each lane scatters the nonzeros it wrote
@@ -172,7 +172,7 @@ struct TinyCell {
     // M = I - c J factored; the inverses of its triangles and the row order stay
     // in LDS for the solves.
     __device__ __forceinline__ void factor(const Slots &s, int slot, double c) {
-        lu_factor_left<T, 1>(SlotStorage<T>{slot_lu<T>(s, slot), lu_ld(NP)}, NP, s.perm + size_t(slot) * NP, slot_dinv<T>(s, slot), nullptr, lu,
+        lu_factor_left<T, 1, kTiles>(SlotStorage<T>{slot_lu<T>(s, slot), lu_ld(NP)}, NP, s.perm + size_t(slot) * NP, slot_dinv<T>(s, slot), nullptr, lu,
                              TinySource<T>{J, S, ld, c});
         wave_lds_order();
     }
@@ -270,8 +270,8 @@ struct TinyCell {
 };
 
 // The corrector of one attempt (newton_slot for a tiny cell).
-template <typename T>
-__device__ __forceinline__ int newton_tiny(const Slots &s, int slot, StepLds<1> &L, SpeciesState &y, TinyCell<T> &cell,
+template <typename T, int kTiles>
+__device__ __forceinline__ int newton_tiny(const Slots &s, int slot, StepLds<1> &L, SpeciesState &y, TinyCell<T, kTiles> &cell,
                                            unsigned long long *t_rhs) {
     const int S = s.S, i = threadIdx.x;
     const bool own = i < S;

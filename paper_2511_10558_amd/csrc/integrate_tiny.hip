@@ -4,8 +4,9 @@
 
 namespace abdf {
 
-// Integrates queued cells of at most 64 species, one wave per cell (TinyCell).
-template <typename T>
+// Integrates queued cells of at most 16 kTiles species, one wave per cell
+// (TinyCell).
+template <typename T, int kTiles>
 __global__ void __launch_bounds__(64) k_integrate_tiny(Slots s, DeviceNet n, IntegrateArgs a) {
     extern __shared__ double smem[];
     __shared__ StepLds<1> L;
@@ -14,7 +15,7 @@ __global__ void __launch_bounds__(64) k_integrate_tiny(Slots s, DeviceNet n, Int
     if (threadIdx.x < kPhases) t_phase[threadIdx.x] = 0;
     const bool rk = s.method == ABDF_METHOD_ESDIRK5;
     PhaseClock clk{a.prof && threadIdx.x == 0, 0};
-    TinyCell<T> cell(n, reinterpret_cast<unsigned char *>(smem));
+    TinyCell<T, kTiles> cell(n, reinterpret_cast<unsigned char *>(smem));
     while (true) {
         const int slot = take_slot<1>(s, a, L);
         if (slot < 0) break;
@@ -46,7 +47,7 @@ __global__ void __launch_bounds__(64) k_integrate_tiny(Slots s, DeviceNet n, Int
                 __syncthreads();
                 clk.stop(&t_phase[kPhaseFactor]);
             }
-            const int phase = newton_tiny<T>(s, slot, L, y, cell, clk.on ? &t_phase[kPhaseRhs] : nullptr);
+            const int phase = newton_tiny<T, kTiles>(s, slot, L, y, cell, clk.on ? &t_phase[kPhaseRhs] : nullptr);
             clk.stop(&t_phase[kPhaseNewton]);
             if (rk)
                 control_rk<1>(s, L, y, phase, nullptr);
@@ -72,10 +73,20 @@ __global__ void __launch_bounds__(64) k_integrate_tiny(Slots s, DeviceNet n, Int
                   t_phase[threadIdx.x] - (threadIdx.x == kPhaseNewton ? t_phase[kPhaseRhs] : 0ull));
 }
 
+// The narrowest of three widths: the factorisation's accumulators (kTiles^2 tiles
+// of 16 x 16) and its unrolled panels decide the kernel's registers; of 4 x 4
+// tiles they spill beside the rest, of 2 x 2 they don't.  A solve of one cell of
+// 12 species took 13.3 ms with 4 x 4 tiles for every size and takes 11.9 ms.
+template <typename T>
+static Persistent pick(const DeviceNet &n) {
+    const void *fn = n.NP <= 16   ? (const void *)&k_integrate_tiny<T, 1>
+                     : n.NP <= 32 ? (const void *)&k_integrate_tiny<T, 2>
+                                  : (const void *)&k_integrate_tiny<T, 4>;
+    return {fn, 64, TinyLayout<T>(n).total};
+}
+
 Persistent integrate_tiny(const DeviceNet &n, int prec) {
-    return prec == ABDF_PREC_FP32_LU
-               ? Persistent{(const void *)&k_integrate_tiny<float>, 64, TinyLayout<float>(n).total}
-               : Persistent{(const void *)&k_integrate_tiny<double>, 64, TinyLayout<double>(n).total};
+    return prec == ABDF_PREC_FP32_LU ? pick<float>(n) : pick<double>(n);
 }
 
 }  // namespace abdf

@@ -486,10 +486,10 @@ k_rhs_stream(DeviceNet n, long long C, const double *__restrict__ k, const doubl
 // workgroup: the rows' Jacobian nonzeros (jacobian_values) go to LDS, and every
 // entry is written as NewtonMatrixSource yields it to the factorisation's
 // gather, a wave to a row, 64 columns at a time.  A call of 192 cells of 200
-// species (61 MB written) took 186 us with one workgroup a cell, the nonzeros in
+// species (61 MB written) took 194 us with one workgroup a cell, the nonzeros in
 // global scratch allocated by the call and two integer divisions an entry, and
-// takes 127 us.
-constexpr int kAsmThreads = 256, kAsmRows = 16;
+// takes 82 us.
+constexpr int kAsmThreads = 256, kAsmRows = 16;   // rows: the blocks of jlong16
 
 __global__ void __launch_bounds__(kAsmThreads) k_newton_matrix_only(DeviceNet n, const double *k, const double *x,
                                                                   const double *cvec, double *M) {
@@ -500,7 +500,8 @@ __global__ void __launch_bounds__(kAsmThreads) k_newton_matrix_only(DeviceNet n,
     for (int i = threadIdx.x; i < S; i += kAsmThreads) xs[i] = x[size_t(cell) * S + i];
     const int e0 = n.jrow_ptr[r0], e1 = n.jrow_ptr[r1];
     __syncthreads();
-    jacobian_values<kAsmThreads>(n, k + size_t(cell) * n.R, xs, jv, e0, e1);
+    const int l0 = n.jlong16_ptr[blockIdx.x], l1 = n.jlong16_ptr[blockIdx.x + 1];
+    jacobian_values<kAsmThreads>(n, k + size_t(cell) * n.R, xs, jv, e0, e1, n.jlong16 + l0, l1 - l0);
     __syncthreads();
     const double c = cvec[cell];
     const int lane = threadIdx.x & 63;

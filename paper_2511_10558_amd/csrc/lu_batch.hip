@@ -60,7 +60,7 @@ __global__ void __launch_bounds__(64 * kLuWaves) k_lu_factor(int n, int batch, d
     T *dinv = scratch + blockIdx.x * lu_scratch_elems<T>(NP);
     for (int m = blockIdx.x; m < batch; m += gridDim.x) {
         double *A = A0 + size_t(m) * n * n;
-        lu_factor_left<T, kLuWaves>(DenseStorage<T>{A, n}, NP, nullptr, dinv, info ? info + m : nullptr, lds,
+        lu_factor_left<T, kLuWaves, 4>(DenseStorage<T>{A, n}, NP, nullptr, dinv, info ? info + m : nullptr, lds,
                                     DenseSource<T>{A, n});
         __syncthreads();
         for (int i = thread_id(); i < n; i += 64 * kLuWaves) perm_out[size_t(m) * n + i] = perm[i];

@@ -133,6 +133,7 @@ HostNetwork::~HostNetwork() {
         if (hipGetDevice(&prev) == hipSuccess && hipSetDevice(d->device) == hipSuccess) {
             void *ptrs[] = {d->rx_ab, d->rx_type, d->alpha, d->beta, d->gamma, d->sg_base, d->sg_len,
                             d->sg_lane, d->sg_red, d->sg_ent, d->jrow_ptr, d->jcol, d->jrow, d->jterm_ptr, d->jt_rx_other, d->jt_coef,
+                            d->jlong, d->jlong16, d->jlong16_ptr,
                             d->rnu_ptr, d->rnu_ent, d->dcol_ptr, d->dcol_ent, d->dcol_coef, d->jidx,
                             d->jmask, d->jbase};
             for (void *p : ptrs)
@@ -517,6 +518,22 @@ const DeviceNet *HostNetwork::device_tables(std::string &err) const {
     chk(upload(&d->jterm_ptr, jterm_ptr));
     chk(upload(&d->jt_rx_other, jt_rx_other));
     chk(upload(&d->jt_coef, jt_coef));
+    const auto terms = [&](int32_t nz) { return jterm_ptr[size_t(nz) + 1] - jterm_ptr[size_t(nz)]; };
+    const auto longer = [&](int32_t a, int32_t b) { return terms(a) > terms(b); };
+    std::vector<int32_t> jlong, jlong16, jlong16_ptr(1, 0);
+    for (int32_t nz = 0; nz < int32_t(jcol.size()); ++nz)
+        if (terms(nz) > kJacShort) jlong.push_back(nz);
+    jlong16 = jlong;
+    for (int32_t r0 = 0; r0 < S; r0 += 16) {
+        const auto end = std::lower_bound(jlong.begin(), jlong.end(), jrow_ptr[size_t(std::min(r0 + 16, S))]);
+        jlong16_ptr.push_back(int32_t(end - jlong.begin()));
+        std::stable_sort(jlong16.begin() + jlong16_ptr[jlong16_ptr.size() - 2], jlong16.begin() + jlong16_ptr.back(), longer);
+    }
+    std::stable_sort(jlong.begin(), jlong.end(), longer);
+    d->n_jlong = int32_t(jlong.size());
+    chk(upload(&d->jlong, jlong));
+    chk(upload(&d->jlong16, jlong16));
+    chk(upload(&d->jlong16_ptr, jlong16_ptr));
     chk(upload(&d->rnu_ptr, rnu_ptr));
     chk(upload(&d->rnu_ent, rnu_ent));
     chk(upload(&d->dcol_ptr, dcol_ptr));

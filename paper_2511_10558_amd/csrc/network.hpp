@@ -18,6 +18,9 @@ constexpr int kRhsResidentGroups = 16;   // lane groups the streaming right-hand
 constexpr int kRhsResidentLen = 40;      // the longest lane it holds
 
 // Device copies of the network tables (one per HIP device).
+// Terms of a Jacobian nonzero that jacobian_values sums in its first pass.
+constexpr int kJacShort = 2;
+
 struct DeviceNet {
     int device = -1;
     int S = 0, R = 0, NP = 0;
@@ -51,7 +54,12 @@ struct DeviceNet {
     int32_t *jterm_ptr = nullptr;  // [nnzJ+1]
     int32_t *jt_rx_other = nullptr;  // reaction << 16 | (other species + 1), 0 in the low half = none
     double *jt_coef = nullptr;     // [nterm] nu_ir * multiplicity
-    int32_t nnzJ = 0, nterm = 0;
+    // the nonzeros of more than kJacShort terms, longest first: all of them, and
+    // by blocks of 16 rows
+    int32_t *jlong = nullptr;      // [n_jlong]
+    int32_t *jlong16 = nullptr;    // [n_jlong]
+    int32_t *jlong16_ptr = nullptr;  // [ceil(S / 16) + 1]
+    int32_t nnzJ = 0, nterm = 0, n_jlong = 0;
     int32_t asm_nnz = 0;           // most nonzeros in 16 consecutive rows from a multiple of 16
     // reaction-major stoichiometry: the species of reaction r with nu != 0
     int32_t *rnu_ptr = nullptr;    // [R+1]

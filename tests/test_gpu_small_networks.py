@@ -1,0 +1,42 @@
+"""Whole solves at the sizes where the integration kernel changes form (GPU)."""
+import numpy as np
+import pytest
+
+import synth
+from oracle import bdf, chem
+from tests.gpu_util import device, rel_err_above, solve_cells
+
+pytestmark = pytest.mark.gpu
+
+
+def first_species(full, n):
+    """The reactions of a network among n of its species: the elements' own, then
+    by first appearance in a reaction."""
+    order = [full.index(a) for a in ("e-", "H", "He", "C", "N", "O", "S")]
+    sides = np.concatenate([full.reactants, full.products], axis=1)
+    order += [int(i) for i in dict.fromkeys(sides.ravel().tolist()) if i >= 0 and i not in order]
+    keep = sorted(order[:n])
+    new = np.full(full.n_species + 1, -1, np.int32)   # the last entry: no species
+    new[keep] = np.arange(n)
+    inside = ((sides < 0) | (new[sides] >= 0)).all(axis=1)
+    return synth.Network(f"{full.name}-{n}", [full.species[i] for i in keep], full.comp[keep], full.charge[keep],
+                         full.rtype[inside], new[full.reactants[inside]], new[full.products[inside]],
+                         full.alpha[inside], full.beta[inside], full.gamma[inside], full.albedo)
+
+
+# one wave a cell with 1, 2 or 4 tiles of 16 to a side up to 64 species, eight waves
+# from 65 on
+@pytest.mark.parametrize("n", [16, 17, 32, 33, 63, 64, 65])
+@pytest.mark.parametrize("precision", ["fp64", "fp32_lu"])
+def test_solve_at_kernel_edges_matches_oracle(n, precision):
+    import paper_2511_10558_amd as ab
+    net = first_species(synth.network_for_config("net200"), n)
+    g = ab.Network.from_text(net.to_text())
+    cells = synth.sample_cells(net, 3, seed=n)
+    cells.t_end[:] = 1e2 * 3.15576e7
+    x, status, _ = solve_cells(ab, g, cells, device(), precision=precision)
+    for c in range(cells.n):
+        ref = bdf.solve(chem.cell_chemistry(net, cells.cell(c)), cells.x0[c], cells.t_end[c], 1e-6, 1e-20)
+        assert status[c] == 0 and ref.status == bdf.OK
+        # the tolerance of whole solves at rtol 1e-6 against the oracle
+        assert rel_err_above(x[c], ref.x) <= 1e-4
