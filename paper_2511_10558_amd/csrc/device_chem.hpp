@@ -104,6 +104,96 @@ __device__ __forceinline__ void cell_rhs(const DeviceNet &n, const double *__res
     species_gather<NT>(n, rate, f);
 }
 
+// cell_rhs for a workgroup alone on its compute unit: the same values, with what
+// the species sums need from memory asked for ahead.  A group's sums are its
+// header, then its entries, then the rates they point to; the headers of a wave's
+// first two groups and all entries of the first are on their way while the
+// rates are formed, and each batch of entries used makes room for the same
+// batch of the next group.  (A residual of 500 species 11.0 us a cell before, 8.9
+// now with 96 cells in the FP32-LU form; 13.8 and 11.7 with 256 in FP64, where
+// the solves beside it draw all the memory gives; of 200 species 5.3 and 5.0.)
+template <int NT>
+__device__ __forceinline__ void cell_rhs_ahead(const DeviceNet &n, const double *__restrict__ k, const double *x,
+                                               double *rate, double *f) {
+    constexpr int kU = 6, kB = 8, kM = kRhsResidentLen / kB, NW = NT / 64;
+    static_assert(kRhsResidentLen % kB == 0 && kRhsSegment <= kRhsResidentLen, "a lane's entries in whole batches");
+    const int tid = thread_id(), lane = tid & 63;
+    struct Head { int mine, red, lw, base; };
+    auto header = [&](int g) __attribute__((always_inline)) {
+        const int gc = min(g, n.n_sgroup - 1);   // a network has at least one species, so one group
+        Head h{n.sg_lane[gc * 64 + lane], n.sg_red[gc * 64 + lane], n.sg_len[gc], n.sg_base[gc]};
+        return h;
+    };
+    int w[kM][kB];
+    // entries past the group's longest lane are its last row's again, and not used
+    auto entries = [&](const Head &h, int b) __attribute__((always_inline)) {
+        const int L = h.lw & 0xffffff;
+        if (b * kB < L) {
+            const int32_t *e = n.sg_ent + h.base + lane;
+#pragma unroll
+            for (int u = 0; u < kB; ++u) w[b][u] = e[min(b * kB + u, L - 1) * 64];
+        }
+    };
+    int g = wave_of(tid);
+    Head h = header(g), hn = header(g + NW);
+    for (int first = 0; first < n.R; first += kU * NT) {   // whole waves: every lane has entries to load
+        const int r0 = first + tid;
+        int ab[kU];
+        double kr[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const int r = min(r0 + u * NT, n.R - 1);
+            ab[u] = n.rx_ab[r];
+            kr[u] = k[r];
+        }
+        if (first == 0) {
+#pragma unroll
+            for (int b = 0; b < kM; ++b) entries(h, b);
+        }
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const int r = r0 + u * NT;
+            const int p = ab[u] & 0xffff, q = (ab[u] >> 16) & 0xffff;
+            double v = kr[u] * x[p];
+            if (q != 0xffff) v *= x[q];
+            if (r < n.R) rate[r] = v;
+        }
+    }
+    __syncthreads();
+    for (; g < n.n_sgroup; g += NW) {
+        const Head hnn = header(g + 2 * NW);
+        const int L = h.lw & 0xffffff, steps = h.lw >> 24;
+        double acc = 0.0;
+#pragma unroll
+        for (int b = 0; b < kM; ++b) {
+            if (b * kB < L) {
+                double vv[kB];
+#pragma unroll
+                for (int u = 0; u < kB; ++u) vv[u] = rate[w[b][u] >> 3];
+#pragma unroll
+                for (int u = 0; u < kB; ++u)
+                    if (b * kB + u < h.mine) acc += double((w[b][u] & 7) - 4) * vv[u];
+            }
+            if (g + NW < n.n_sgroup) entries(hn, b);
+        }
+        // a species of more than 64 lanes' entries (the lanes are then longer)
+        for (int j = kM * kB; j < L; ++j) {
+            const int wj = n.sg_ent[h.base + min(j, L - 1) * 64 + lane];
+            if (j < h.mine) acc += double((wj & 7) - 4) * rate[wj >> 3];
+        }
+        const int q = h.red < 0 ? 0 : (h.red >> 7) & 127, m = h.red < 0 ? 1 : h.red & 127;
+        for (int t = 0; t < steps; ++t) {
+            const int off = 1 << t;
+            const double o = __shfl_down(acc, off);
+            if ((q & (2 * off - 1)) == 0 && q + off < m) acc += o;
+        }
+        if (h.red >= 0 && q == 0) f[h.red >> 14] = acc;
+        h = hn;
+        hn = hnn;
+    }
+    __syncthreads();
+}
+
 // J(x) y = nu . (d rate / dx) y for one cell: per reaction
 // k_r (y_a x_b + x_a y_b) (k_r y_a for one reactant; the same expression gives
 // 2 k_r x_a y_a for A + A), then the species sums of cell_rhs.  x, y in LDS;

@@ -493,7 +493,7 @@ __device__ __forceinline__ int newton_slot(const Slots &s, const DeviceNet &n, i
         if (own) xs[i] = y.x;
         if (i == 0) L.bad = 0;
         __syncthreads();
-        cell_rhs<NT, true>(n, k, xs, rate, b);
+        cell_rhs_ahead<NT>(n, k, xs, rate, b);
         double r = 0.0;
         if (own) {
             const double f = b[i];
