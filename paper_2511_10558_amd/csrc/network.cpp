@@ -133,7 +133,7 @@ HostNetwork::~HostNetwork() {
         if (hipGetDevice(&prev) == hipSuccess && hipSetDevice(d->device) == hipSuccess) {
             void *ptrs[] = {d->rx_ab, d->rx_type, d->alpha, d->beta, d->gamma, d->sg_base, d->sg_len,
                             d->sg_lane, d->sg_red, d->sg_ent, d->jrow_ptr, d->jcol, d->jrow, d->jterm_ptr, d->jt_rx_other, d->jt_coef,
-                            d->jlong, d->jlong16, d->jlong16_ptr,
+                            d->jlong,
                             d->rnu_ptr, d->rnu_ent, d->dcol_ptr, d->dcol_ent, d->dcol_coef, d->jidx,
                             d->jmask, d->jbase};
             for (void *p : ptrs)
@@ -531,9 +531,11 @@ const DeviceNet *HostNetwork::device_tables(std::string &err) const {
     }
     std::stable_sort(jlong.begin(), jlong.end(), longer);
     d->n_jlong = int32_t(jlong.size());
-    chk(upload(&d->jlong, jlong));
-    chk(upload(&d->jlong16, jlong16));
-    chk(upload(&d->jlong16_ptr, jlong16_ptr));
+    jlong.insert(jlong.end(), jlong16.begin(), jlong16.end());
+    jlong.insert(jlong.end(), jlong16_ptr.begin(), jlong16_ptr.end());
+    chk(upload(&d->jlong, jlong));   // the three in one allocation
+    d->jlong16 = d->jlong + d->n_jlong;
+    d->jlong16_ptr = d->jlong16 + d->n_jlong;
     chk(upload(&d->rnu_ptr, rnu_ptr));
     chk(upload(&d->rnu_ent, rnu_ent));
     chk(upload(&d->dcol_ptr, dcol_ptr));
