@@ -540,29 +540,27 @@ def main():
     if dom == "factor":
         peak = FP64_MFMA_PEAK_TFLOPS if args.precision == "fp64" else FP32_MFMA_PEAK_TFLOPS
         ach = n_lu * lu_flop / (prof["factor"][1] * 1e-3) / 1e12
-        roof = {"kernel": "k_factor", "bound": "mfma", "achieved": round(ach, 3), "peak": peak, "unit": "TFLOP/s",
+        roof = {"kernel": "k_integrate (factorisation phase)", "bound": "mfma", "achieved": round(ach, 3), "peak": peak, "unit": "TFLOP/s",
                 "frac": round(ach / peak, 4), "traffic": None}
     elif dom == "newton":
         ach = n_newton * newton_bytes / (prof["newton"][1] * 1e-3) / 1e9
-        roof = {"kernel": "k_newton_solve", "bound": "hbm", "achieved": round(ach, 1), "peak": HBM_PEAK_GBS,
+        roof = {"kernel": "k_integrate (triangular-solve phase)", "bound": "hbm", "achieved": round(ach, 1), "peak": HBM_PEAK_GBS,
                 "unit": "GB/s", "frac": round(ach / HBM_PEAK_GBS, 4), "traffic": None}
     elif dom == "rhs":
         ach = n_newton * rhs_bytes / (prof["rhs"][1] * 1e-3) / 1e9
-        roof = {"kernel": "k_newton_rhs", "bound": "hbm", "achieved": round(ach, 1), "peak": HBM_PEAK_GBS,
+        roof = {"kernel": "k_integrate (residual phase)", "bound": "hbm", "achieved": round(ach, 1), "peak": HBM_PEAK_GBS,
                 "unit": "GB/s", "frac": round(ach / HBM_PEAK_GBS, 4), "traffic": None}
     else:
         ach = n_att * control_bytes / (prof["control"][1] * 1e-3) / 1e9
-        roof = {"kernel": "k_control", "bound": "hbm", "achieved": round(ach, 1), "peak": HBM_PEAK_GBS,
+        roof = {"kernel": "k_integrate (control phase)", "bound": "hbm", "achieved": round(ach, 1), "peak": HBM_PEAK_GBS,
                 "unit": "GB/s", "frac": round(ach / HBM_PEAK_GBS, 4), "traffic": None}
     rec = recorded_traffic()
     # the counters were taken on one network in FP64; other workloads report none
     if rec is not None and args.precision == "fp64" and rec.get("network") == args.network:
-        if roof["kernel"] == "k_factor":
-            roof["traffic"] = round(rec["k_factor_bytes_per_lu"] * n_lu / max(1, prof["factor"][0]))
-        elif roof["kernel"] == "k_newton_solve":
-            roof["traffic"] = round(rec["k_newton_solve_bytes_per_iteration"] * n_newton / max(1, prof["newton"][0]))
-        roof["traffic_unit"] = "bytes per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE, copy-calibrated)"
-    # secondary figures for the other two hot kernels
+        # of the whole kernel: a persistent launch runs every phase
+        roof["traffic"] = round(rec["k_integrate_bytes_per_iteration"] * n_newton / max(1, prof["newton"][0]))
+        roof["traffic_unit"] = "bytes per launch, all phases (rocprofv3 FETCH_SIZE + WRITE_SIZE, copy-calibrated)"
+    # the factorisations' rate whichever phase leads
     if prof["factor"][1] > 0:
         kern["factor"]["tflops"] = round(n_lu * lu_flop / (prof["factor"][1] * 1e-3) / 1e12, 3)
     # the phases' times are means over the workgroups of the persistent launches

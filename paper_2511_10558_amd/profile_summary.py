@@ -117,12 +117,12 @@ def mfma(mdir, mlog, command):
         out.append(f"| {k} | {calls.get(k, 0)} | {d.get('SQ_INSTS_VALU_MFMA_MOPS_F64', 0):.4g} | "
                    f"{d.get('SQ_VALU_MFMA_BUSY_CYCLES', 0):.4g} | {d.get('SQ_BUSY_CU_CYCLES', 0):.4g} | "
                    f"{d.get('SQ_WAVE_CYCLES', 0):.4g} |")
-    f = agg.get("k_factor<double>", {})
+    f = agg.get("k_integrate<8, false>", {})
     executed = f.get("SQ_INSTS_VALU_MFMA_MOPS_F64", 0.0) * 512 / max(1, n_lu)
-    out += ["", f"k_factor<double>: {n_lu} factorisations; MFMA work executed per factorisation "
+    out += ["", f"k_integrate<8, false>: {n_lu} factorisations; MFMA work executed per factorisation "
                 f"{executed:.4g} flop (MOPS x 512) against the algorithmic 2/3 n^3 = {2 / 3 * S ** 3:.4g} "
                 f"({executed / (2 / 3 * S ** 3):.3f}x: the padding to 512 rows and the diagonal-block inverses).",
-            f"MFMA busy / CU busy cycles: {f.get('SQ_VALU_MFMA_BUSY_CYCLES', 0) / max(1, f.get('SQ_BUSY_CU_CYCLES', 1)):.3f}"
+            f"MFMA busy / CU busy cycles, all phases: {f.get('SQ_VALU_MFMA_BUSY_CYCLES', 0) / max(1, f.get('SQ_BUSY_CU_CYCLES', 1)):.3f}"
             " (both summed over the device as the counters report them)."]
     open(os.path.join(PROFILES, "mfma_net500.md"), "w").write("\n".join(out) + "\n")
     print("\n".join(out))
@@ -171,18 +171,15 @@ def main():
             continue
         out.append(f"| {short(r['Name'])} | {r['Calls']} | {float(r['TotalDurationNs'])/1e6:.1f} | "
                    f"{float(r['AverageNs'])/1e3:.1f} | {float(r['Percentage']):.2f} |")
-    # per hardware queue: the solver's stream and the side stream of the
-    # Newton iterations that run beside the factorisation
     trace_rows = list(csv.DictReader(open(os.path.join(trace, "run_kernel_trace.csv"))))
-    perq = {}
+    perk = {}
     spans = []
     for r in trace_rows:
         k = short(r["Kernel_Name"])
         t0, t1 = int(r["Start_Timestamp"]), int(r["End_Timestamp"])
         spans.append((t0, t1))
-        key = (k, r["Queue_Id"])
-        n, tot = perq.get(key, (0, 0))
-        perq[key] = (n + 1, tot + (t1 - t0))
+        n, tot = perk.get(k, (0, 0))
+        perk[k] = (n + 1, tot + (t1 - t0))
     spans.sort()
     busy, cs, ce = 0, None, None
     for a, b in spans:
@@ -194,25 +191,17 @@ def main():
             ce = max(ce, b)
     if ce is not None:
         busy += ce - cs
-    out += ["", "Per hardware queue (kernel trace).  Kernels on the second queue are the Newton "
-            "iterations of cells whose factorisation is current; they are launched beside k_factor "
-            "and their spans include the time their workgroups wait for compute units that "
-            "k_factor holds, so their totals overlap the factorisation's.", "",
-            "| kernel | queue | calls | total ms | average us |", "|---|---|---|---|---|"]
-    for (k, q), (n, tot) in sorted(perq.items(), key=lambda kv: -kv[1][1]):
-        if tot < 1e6:
-            continue
-        out.append(f"| {k} | {q} | {n} | {tot / 1e6:.1f} | {tot / n / 1e3:.1f} |")
-    out += ["", f"GPU busy (union of all kernel spans): {busy / 1e6:.1f} ms, of which k_factor "
-                f"{sum(t for (k, q), (n, t) in perq.items() if k.startswith('k_factor')) / 1e6:.1f} ms."]
+    out += ["", f"GPU busy (union of all kernel spans): {busy / 1e6:.1f} ms."]
     if len(sys.argv) > 5:
         tl = json.loads([l for l in open(sys.argv[5]) if l.startswith("{")][-1])
         out += ["", f"Bench line of the traced run: {tl['value']} {tl['unit']}, {tl['ms_per_step']} ms per solve, "
-                    f"work {json.dumps(tl['work'])}."]
+                    f"work {json.dumps(tl['work'])}.",
+                "Phases of the integration kernel, mean ms over its workgroups: " +
+                ", ".join(f"{k} {v['ms']}" for k, v in tl["kernels"].items() if v["ms"] > 0) + "."]
         if "roofline_rhs" in tl:
             rr = tl["roofline_rhs"]
             name = rr["kernel"].split()[0]
-            runs = [(n, t) for (k, q), (n, t) in perq.items() if k.startswith(name)]
+            runs = [v for k, v in perk.items() if k.startswith(name)]
             n_rhs, t_rhs = (sum(n for n, t in runs), sum(t for n, t in runs)) if runs else (0, 0)
             per_cell = float(rr["work"].split("=")[1].split("B")[0])
             if n_rhs:
@@ -242,13 +231,9 @@ def main():
         wb = w.get(k, (0, 0.0))[1] * 1024 * cw
         out.append(f"| {k} | {f.get(k, (0, 0))[0]} | {fb/2**20:.1f} | {wb/2**20:.1f} |")
         traffic[k] = fb + wb
-    per_lu = traffic.get("k_factor<double>", 0.0) / max(1, work["factorisations"])
-    per_it = sum(v for k, v in traffic.items() if k.startswith("k_newton_solve<double")) / \
-        max(1, work["newton_iterations"])
-    out += ["", f"Per factorisation (k_factor, assembly + LU): {per_lu/2**20:.2f} MiB of HBM traffic; "
-                f"per Newton solve (k_newton_solve): {per_it/2**20:.3f} MiB."]
-    rec = {"source_hash": source_hash(), "network": "net500", "k_factor_bytes_per_lu": per_lu,
-           "k_newton_solve_bytes_per_iteration": per_it}
+    per_it = traffic.get("k_integrate<8, false>", 0.0) / max(1, work["newton_iterations"])
+    out += ["", f"k_integrate, all phases: {per_it/2**20:.3f} MiB of HBM traffic per Newton iteration."]
+    rec = {"source_hash": source_hash(), "network": "net500", "k_integrate_bytes_per_iteration": per_it}
     # the standalone right-hand side: its launches cover the run's whole batch
     cells = json.loads(line)["config"]["cells"]
     rhs = [(k, n) for k, (n, _) in f.items() if k.startswith("k_rhs_stream") or k.startswith("k_rhs_only")]
