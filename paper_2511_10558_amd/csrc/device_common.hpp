@@ -59,6 +59,8 @@ struct SlotQueue {
     unsigned long long ticks[kPhases];        // 100 MHz ticks summed over workgroups, per phase (timers on)
     int32_t nfin;                             // finished slots since the last harvest (Slots::fin)
     int32_t stop;                             // the last launch in which a workgroup found the queue empty
+    int32_t n64;                              // one-wave FP32-LU kernel: running cells on FP64 factors
+    int32_t pad;
 };
 constexpr int kQueueInts = sizeof(SlotQueue) / sizeof(int32_t);
 

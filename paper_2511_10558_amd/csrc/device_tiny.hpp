@@ -14,8 +14,8 @@
 namespace abdf {
 
 // LDS layout of a network's tiny-cell kernel (offsets in bytes): the
-// factorisation's own block, then the rest.
-template <typename T>
+// factorisation's own block (in T, or in T and FP64 in turn), then the rest.
+template <typename T, bool kFp64Too>
 struct TinyLayout {
     int S, R, NP, ld, ng, nent;
     size_t J, k, rate, xs, f, ab, ent, lane, red, len, base, total;
@@ -26,7 +26,9 @@ struct TinyLayout {
         ng = n.n_sgroup;
         nent = n.sg_total;
         ld = S | 1;   // odd: a column's rows lie in different banks
-        size_t o = (lu2_lds_bytes<T, 1>(NP) + 15) / 16 * 16;
+        size_t o = lu2_lds_bytes<T, 1>(NP);
+        if (kFp64Too && lu2_lds_bytes<double, 1>(NP) > o) o = lu2_lds_bytes<double, 1>(NP);
+        o = (o + 15) / 16 * 16;
         auto part = [&o](size_t bytes) {
             const size_t at = o;
             o += (bytes + 7) / 8 * 8;
@@ -62,7 +64,9 @@ struct TinySource {
     }
 };
 
-template <typename T, int kTiles>
+// kFp64Too (T = float): the cell's factors may also be FP64.  What concerns the
+// factors is a template of their type U.
+template <typename T, int kTiles, bool kFp64Too>
 struct TinyCell {
     int S, R, NP, ld, ng;
     unsigned char *lu;       // lu_factor_left's LDS block
@@ -70,7 +74,7 @@ struct TinyCell {
     int32_t *ab, *ent, *lane, *red, *len, *base;
 
     __device__ __forceinline__ TinyCell(const DeviceNet &n, unsigned char *smem) {
-        const TinyLayout<T> l(n);
+        const TinyLayout<T, kFp64Too> l(n);
         S = l.S;
         R = l.R;
         NP = l.NP;
@@ -171,9 +175,10 @@ struct TinyCell {
 
     // M = I - c J factored; the inverses of its triangles and the row order stay
     // in LDS for the solves.
+    template <typename U>
     __device__ __forceinline__ void factor(const Slots &s, int slot, double c) {
-        lu_factor_left<T, 1, kTiles>(SlotStorage<T>{slot_lu<T>(s, slot), lu_ld(NP)}, NP, s.perm + size_t(slot) * NP, slot_dinv<T>(s, slot), nullptr, lu,
-                             TinySource<T>{J, S, ld, c});
+        lu_factor_left<U, 1, kTiles>(SlotStorage<U>{slot_lu<U>(s, slot), lu_ld(NP)}, NP, s.perm + size_t(slot) * NP,
+                                     slot_dinv<U>(s, slot), nullptr, lu, TinySource<U>{J, S, ld, c});
         wave_lds_order();
     }
 
@@ -182,8 +187,9 @@ struct TinyCell {
     // lu_solve_left's diagonal blocks.  b, y in LDS.  A lane group reads the
     // entries of P rows (all of them up to 32 species) before it uses any: rows
     // two at a time, a solve of 12 species took 2.5 us, and takes 1.9.
-    __device__ __forceinline__ void triangle(const T *D, bool lower, const double *b, double *y) const {
-        constexpr int VW = 16 / int(sizeof(T)), H = (16 * kTiles + 16 * VW - 1) / (16 * VW);
+    template <typename U>
+    __device__ __forceinline__ void triangle(const U *D, bool lower, const double *b, double *y) const {
+        constexpr int VW = 16 / int(sizeof(U)), H = (16 * kTiles + 16 * VW - 1) / (16 * VW);
         constexpr int P = kTiles == 2 ? 8 : 4;
         const int N = min(NP, S + (S & 1));
         const int lane16 = threadIdx.x & 15, row4 = threadIdx.x >> 4;
@@ -196,7 +202,7 @@ struct TinyCell {
                 tv[h][q] = c < N ? b[c] : 0.0;
             }
         for (int r0 = 0; r0 < N; r0 += 4 * P) {
-            T a[P][H][VW];
+            U a[P][H][VW];
 #pragma unroll
             for (int p = 0; p < P; ++p)
 #pragma unroll
@@ -233,15 +239,16 @@ struct TinyCell {
     }
 
     // This lane's entry of M^{-1} b, b given by lane.
+    template <typename U>
     __device__ __forceinline__ double solve(double b) {
         const int t = threadIdx.x;
-        const LuLds<T, 1> l(NP, lu);
+        const LuLds<U, 1> l(NP, lu);
         f[t] = t < S ? b : 0.0;
         wave_lds_order();
         xs[t] = t < NP ? f[l.perm[t]] : 0.0;
         wave_lds_order();
-        triangle(l.Xb, true, xs, f);
-        triangle(l.Ub, false, f, xs);
+        triangle<U>(l.Xb, true, xs, f);
+        triangle<U>(l.Ub, false, f, xs);
         return t < S ? xs[t] : 0.0;
     }
 
@@ -261,12 +268,12 @@ struct TinyCell {
         return sums();
     }
 
-    // An interrupted cell's matrices: the factorisation left its inverses and row
-    // order in the slot's storage; the Jacobian nonzeros are there as well.
-    __device__ __forceinline__ void restore(const Slots &s, const DeviceNet &n, int slot) {
-        scatter(n, s.jval + size_t(slot) * n.nnzJ);
-        const T *di = slot_dinv<T>(s, slot);
-        const LuLds<T, 1> l(NP, lu);
+    // An interrupted cell's factors: the factorisation left its inverses and row
+    // order in the slot's storage.
+    template <typename U>
+    __device__ __forceinline__ void restore(const Slots &s, int slot) {
+        const U *di = slot_dinv<U>(s, slot);
+        const LuLds<U, 1> l(NP, lu);
         for (int e = threadIdx.x; e < 64 * NP; e += 64) {
             l.Xb[(e >> 6) * kLdb + (e & 63)] = di[e];
             l.Ub[(e >> 6) * kLdb + (e & 63)] = di[kLuW * kLuW + e];
@@ -277,14 +284,15 @@ struct TinyCell {
 };
 
 // The corrector of one attempt (newton_slot for a tiny cell).
-template <typename T, int kTiles>
-__device__ __forceinline__ int newton_tiny(const Slots &s, int slot, StepLds<1> &L, SpeciesState &y, TinyCell<T, kTiles> &cell,
-                                           unsigned long long *t_rhs) {
+template <typename T, int kTiles, bool kFp64Too>
+__device__ __forceinline__ int newton_tiny(const Slots &s, int slot, StepLds<1> &L, SpeciesState &y,
+                                           TinyCell<T, kTiles, kFp64Too> &cell, unsigned long long *t_rhs) {
     const int S = s.S, i = threadIdx.x;
     const bool own = i < S;
     SlotCtl &cs = L.cs;
     const double c = cs.c, c_lu = cs.c_lu, tol = cs.newton_tol;
     const bool refine = sizeof(T) == sizeof(float) && cs.lu_mode == kLuRefined32;
+    const bool fp64 = kFp64Too && cs.lu_mode == kLu64;
     double eta_old = 0.0;
     int phase = kIter, m = 0;
     while (phase == kIter) {
@@ -297,10 +305,10 @@ __device__ __forceinline__ int newton_tiny(const Slots &s, int slot, StepLds<1> 
             phase = kFailed;
             break;
         }
-        double delta = cell.solve(r);
+        double delta = fp64 ? cell.template solve<double>(r) : cell.template solve<T>(r);
         if (refine) {
             const double jd = cell.jvp(s.xJ + size_t(slot) * S, delta);
-            delta = delta + cell.solve(own ? r - (delta - c_lu * jd) : 0.0);
+            delta = delta + cell.template solve<T>(own ? r - (delta - c_lu * jd) : 0.0);
         }
         if (c != c_lu) delta = delta * (2.0 / (1.0 + c / c_lu));
         const double eta = sqrt(wg_square<1>(delta / y.scl, S, nullptr, L.red) / S);

@@ -251,7 +251,7 @@ int Engine::layout(int nslots, void *base, std::string &err) {
         s_.atol_sp = static_cast<const double *>(part[19]);
     }
     lds_admit_ = admit_lds(dn_);
-    if (dn_.NP > 512 || lds_admit_ > kMaxLds || integrate_lds(dn_, prec_) > kMaxLds) {
+    if (dn_.NP > 512 || lds_admit_ > kMaxLds || integrate_lds(dn_, prec_, true) > kMaxLds) {
         err = "network too large for one workgroup's LDS";
         return ABDF_E_ARG;
     }
@@ -259,7 +259,8 @@ int Engine::layout(int nslots, void *base, std::string &err) {
     hipDeviceProp_t prop;
     if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess && prop.multiProcessorCount > 0)
         cus = prop.multiProcessorCount;
-    grid_max_ = cus * integrate_resident_per_cu(dn_, prec_);
+    grid_max_ = cus * integrate_resident_per_cu(dn_, prec_, false);
+    grid_fp64_max_ = cus * integrate_resident_per_cu(dn_, prec_, true);
     grid_reverse_max_ = cus * reverse_resident_per_cu(dn_);
     n_free_ = 0;
     for (int i = nslots - 1; i >= 0; --i) free_[n_free_++] = i;
@@ -312,6 +313,8 @@ int Engine::init_external(int nslots, void *base, size_t bytes, const HostBuffer
 int Engine::reset_counts(hipStream_t st, std::string &err) {
     HIP_TRY(launch_fill_i32(reinterpret_cast<int32_t *>(s_.q), 0, kQueueInts, st));
     held_seen_ = 0;
+    n64_seen_ = 0;
+    fp64_too_ = false;
     for (unsigned long long &t : ticks_seen_) t = 0;
     launch_ = 0;
     bound_ = 0;
@@ -376,8 +379,13 @@ IntegrateArgs Engine::next_launch(double ms, bool stop_on_idle) {
 int Engine::integrate(double ms, bool stop_on_idle, hipStream_t st, std::string &err) {
     if (bound_ <= 0) return ABDF_OK;
     TraceRange tr("abdf integrate");
-    grid_ = std::min(bound_, grid_max_);
-    HIP_TRY(launch_integrate(s_, dn_, next_launch(ms, stop_on_idle), grid_, st));
+    // while cells of the one-wave FP32-LU kernel are on FP64 factors, its form that
+    // holds those runs in every other launch (all cells advance in it, fewer at once)
+    fp64_too_ = n64_seen_ > 0 && !fp64_too_;
+    grid_ = std::min(bound_, fp64_too_ ? grid_fp64_max_ : grid_max_);
+    IntegrateArgs a = next_launch(ms, stop_on_idle);
+    a.fp64_too = fp64_too_;
+    HIP_TRY(launch_integrate(s_, dn_, a, grid_, st));
     return ABDF_OK;
 }
 
@@ -388,6 +396,7 @@ int Engine::sync_counts(hipStream_t st, int &nfin, std::string &err) {
     flush_timers();
     nfin = h_q_->nfin;
     held_seen_ = h_q_->held_tail;
+    n64_seen_ = h_q_->n64;
     // a phase's time: the mean over the launch's workgroups
     static const int kind[kPhases] = {ABDF_PROF_CONTROL, ABDF_PROF_FACTOR,    ABDF_PROF_RHS,
                                       ABDF_PROF_NEWTON,  ABDF_PROF_ADJ_SOLVE, ABDF_PROF_ADJ_STEP};

@@ -154,6 +154,8 @@ class Engine {
     SlotQueue *h_q_ = nullptr;          // pinned copy of the device's queue counters
     unsigned long long held_seen_ = 0, ticks_seen_[kPhases] = {};
     int32_t launch_ = 0;                // launches since the counters were reset
+    int32_t n64_seen_ = 0;              // SlotQueue::n64 as last read
+    bool fp64_too_ = false;             // the last launch's form (IntegrateArgs::fp64_too)
     int32_t *h_fin_ = nullptr;          // pinned [nslots]
     int32_t *h_admit_slots_ = nullptr;  // pinned [nslots]
     long long *h_admit_cells_ = nullptr;
@@ -163,7 +165,7 @@ class Engine {
     int bound_ = 0;
     size_t lds_admit_ = 0;
     int grid_ = 0;                      // workgroups of the last launch
-    int grid_max_ = 256, grid_reverse_max_ = 256;
+    int grid_max_ = 256, grid_fp64_max_ = 256, grid_reverse_max_ = 256;
     // kernel timers of launches not yet read back
     struct Pending { int kind; hipEvent_t a, b; };
     std::vector<Pending> pending_;

@@ -19,16 +19,14 @@ namespace abdf {
 Persistent integrate_wide_fp64(const DeviceNet &n) { return integrate_wide<false>(n); }
 
 // The tiny-cell kernel serves networks of at most 64 species whose tables fit
-// in the LDS beside the matrices.
-static Persistent integrate_kernel(const DeviceNet &n, int prec) {
-    if (n.S <= 64) {
-        const Persistent p = integrate_tiny(n, prec);
-        if (p.lds <= kMaxLds) return p;
-    }
+// in the LDS beside the matrices (in the FP32-LU form, beside FP64 ones: its
+// cells may come to need them).
+static Persistent integrate_kernel(const DeviceNet &n, int prec, bool fp64_too) {
+    if (n.S <= 64 && integrate_tiny(n, prec, true).lds <= kMaxLds) return integrate_tiny(n, prec, fp64_too);
     return prec == ABDF_PREC_FP32_LU ? integrate_wide_fp32(n) : integrate_wide_fp64(n);
 }
 
-size_t integrate_lds(const DeviceNet &n, int prec) { return integrate_kernel(n, prec).lds; }
+size_t integrate_lds(const DeviceNet &n, int prec, bool fp64_too) { return integrate_kernel(n, prec, fp64_too).lds; }
 size_t reverse_lds(const DeviceNet &n) { return reverse_kernel(n).lds; }
 
 static int resident_per_cu(const Persistent &p) {
@@ -37,7 +35,9 @@ static int resident_per_cu(const Persistent &p) {
     return (e == hipSuccess && nb > 0) ? nb : 1;
 }
 
-int integrate_resident_per_cu(const DeviceNet &n, int prec) { return resident_per_cu(integrate_kernel(n, prec)); }
+int integrate_resident_per_cu(const DeviceNet &n, int prec, bool fp64_too) {
+    return resident_per_cu(integrate_kernel(n, prec, fp64_too));
+}
 int reverse_resident_per_cu(const DeviceNet &n) { return resident_per_cu(reverse_kernel(n)); }
 
 static hipError_t launch_persistent(const Persistent &p, const Slots &s, const DeviceNet &n, const IntegrateArgs &a,
@@ -46,12 +46,13 @@ static hipError_t launch_persistent(const Persistent &p, const Slots &s, const D
     Slots ss = s;
     DeviceNet nn = n;
     IntegrateArgs aa = a;
+    aa.defer = p.defers;
     void *args[] = {&ss, &nn, &aa};
     return hipLaunchKernel(p.fn, dim3(unsigned(grid)), dim3(p.threads), args, p.lds, st);
 }
 
 hipError_t launch_integrate(const Slots &s, const DeviceNet &n, const IntegrateArgs &a, int grid, hipStream_t st) {
-    return launch_persistent(integrate_kernel(n, s.prec), s, n, a, grid, st);
+    return launch_persistent(integrate_kernel(n, s.prec, a.fp64_too), s, n, a, grid, st);
 }
 
 hipError_t launch_reverse(const Slots &s, const DeviceNet &n, const IntegrateArgs &a, int grid, hipStream_t st) {

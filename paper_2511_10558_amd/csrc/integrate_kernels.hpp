@@ -12,11 +12,13 @@ struct Persistent {
     const void *fn;
     int threads;
     size_t lds;
+    bool defers = false;   // puts cells on FP64 factors back (IntegrateArgs::defer)
 };
 Persistent integrate_wide_fp64(const DeviceNet &n);
 Persistent integrate_wide_fp32(const DeviceNet &n);
-// for networks of at most 64 species
-Persistent integrate_tiny(const DeviceNet &n, int prec);
+// for networks of at most 64 species; fp64_too: the FP32-LU form whose LDS also
+// holds FP64 factors
+Persistent integrate_tiny(const DeviceNet &n, int prec, bool fp64_too);
 Persistent reverse_kernel(const DeviceNet &n);
 
 // Eight waves to a workgroup: one thread per species up to 512.
@@ -39,14 +41,14 @@ struct PhaseClock {
 };
 
 // Whether this workgroup puts its cell back and ends: the launch's time is up,
-// or (when cells wait on the host for slots) another workgroup found the queue
-// empty.  Uniform; contains a barrier.
+// or (when cells wait on the host for slots, or for the form that holds FP64
+// factors) another workgroup found the queue empty.  Uniform; contains a barrier.
 template <int W>
 __device__ __forceinline__ bool time_up(const Slots &s, const IntegrateArgs &a, unsigned long long t0,
                                         StepLds<W> &L) {
     if (threadIdx.x == 0) {
         bool up = wall_clock64() - t0 > a.ticks;
-        if (a.stop_on_idle)
+        if (a.stop_on_idle || (a.defer && (L.cs.n_attempts & 7) == 0))   // not a load of every short attempt
             up |= __hip_atomic_load(&s.q->stop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == a.launch;
         L.flag = up;
     }
@@ -63,7 +65,8 @@ __device__ __forceinline__ int take_slot(const Slots &s, const IntegrateArgs &a,
         L.slot = slot;
         if (slot >= 0)
             L.cs = s.ctl[slot];
-        else if (a.stop_on_idle)
+        else if (a.stop_on_idle ||
+                 (a.defer && __hip_atomic_load(&s.q->n64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > 0))
             __hip_atomic_store(&s.q->stop, a.launch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();

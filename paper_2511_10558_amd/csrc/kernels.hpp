@@ -62,11 +62,13 @@ struct IntegrateArgs {
     int32_t launch;                  // number of this launch (> 0)
     int32_t stop_on_idle;            // cells wait on the host: end as soon as a workgroup finds the queue empty
     int32_t prof;                    // accumulate SlotQueue::ticks
+    int32_t fp64_too;                // one-wave FP32-LU kernel: the form that also holds FP64 factors
+    int32_t defer;                   // (set by the launcher) the form that does not: it puts cells on FP64 factors back
 };
 
 // LDS bytes per kernel for a network
 inline size_t admit_lds(const DeviceNet &n) { return sizeof(double) * (4 * size_t(n.S) + n.R); }
-size_t integrate_lds(const DeviceNet &n, int prec);
+size_t integrate_lds(const DeviceNet &n, int prec, bool fp64_too);
 size_t reverse_lds(const DeviceNet &n);
 
 hipError_t launch_admit(const Slots &s, const DeviceNet &n, const AdmitArgs &a, size_t lds, hipStream_t st);
@@ -74,7 +76,7 @@ hipError_t launch_admit(const Slots &s, const DeviceNet &n, const AdmitArgs &a, 
 hipError_t launch_integrate(const Slots &s, const DeviceNet &n, const IntegrateArgs &a, int grid, hipStream_t st);
 hipError_t launch_reverse(const Slots &s, const DeviceNet &n, const IntegrateArgs &a, int grid, hipStream_t st);
 // Their workgroups resident per CU.
-int integrate_resident_per_cu(const DeviceNet &n, int prec);
+int integrate_resident_per_cu(const DeviceNet &n, int prec, bool fp64_too);
 int reverse_resident_per_cu(const DeviceNet &n);
 hipError_t launch_harvest(const Slots &s, const HarvestArgs &h, hipStream_t st);
 

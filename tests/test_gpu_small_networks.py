@@ -40,3 +40,38 @@ def test_solve_at_kernel_edges_matches_oracle(n, precision):
         assert status[c] == 0 and ref.status == bdf.OK
         # the tolerance of whole solves at rtol 1e-6 against the oracle
         assert rel_err_above(x[c], ref.x) <= 1e-4
+
+
+# at these sizes and horizons some of the 40 cells' correctors fail with FP32
+# factors, plain and refined (96 species: the eight-wave kernel)
+@pytest.mark.parametrize("n,years", [(16, 1e3), (17, 1e3), (33, 1e6), (64, 1e6), (96, 1e6)])
+def test_fp32_cells_fall_back_to_fp64_factors(n, years):
+    import paper_2511_10558_amd as ab
+    net = first_species(synth.network_for_config("net200"), n)
+    g = ab.Network.from_text(net.to_text())
+    cells = synth.sample_cells(net, 40, seed=77, t_end_yr=years)
+    x, status, stats = solve_cells(ab, g, cells, device(), precision="fp32_lu", lu_reuse=0.3)
+    assert (status == 0).all()
+    fell = np.nonzero(stats["n_lu_fp64"])[0]
+    assert len(fell) > 0 and (stats["n_lu_fp64"] <= stats["n_lu"]).all()
+    for c in fell[:2]:
+        ref = bdf.solve(chem.cell_chemistry(net, cells.cell(c)), cells.x0[c], cells.t_end[c], 1e-6, 1e-20)
+        assert ref.status == bdf.OK and rel_err_above(x[c], ref.x) <= 1e-4
+
+
+# cells interrupted (fewer slots than cells: a launch ends when a workgroup runs
+# idle) and resumed, those on FP64 factors among them
+@pytest.mark.parametrize("n,years", [(16, 1e3), (31, 1e4), (64, 1e4), (65, 1e4)])
+@pytest.mark.parametrize("precision", ["fp64", "fp32_lu"])
+@pytest.mark.parametrize("method", ["bdf", "esdirk5"])
+def test_interrupted_cells_give_the_same_bits(n, years, precision, method):
+    import paper_2511_10558_amd as ab
+    net = first_species(synth.network_for_config("net200"), n)
+    g = ab.Network.from_text(net.to_text())
+    cells = synth.sample_cells(net, 40, seed=77, t_end_yr=years)
+    kw = dict(precision=precision, method=method, max_steps=3000)
+    x, status, stats = solve_cells(ab, g, cells, device(), **kw)
+    budget = 9 * (8 * (net.n_species * net.n_species * 6 + net.n_reactions) + 80000)   # 10 to 30 slots
+    xf, sf, stf = solve_cells(ab, g, cells, device(), hbm_budget_bytes=budget, **kw)
+    assert np.array_equal(sf, status) and np.array_equal(xf, x)
+    assert np.array_equal(stf, stats)
