@@ -251,7 +251,7 @@ int Engine::layout(int nslots, void *base, std::string &err) {
         s_.atol_sp = static_cast<const double *>(part[19]);
     }
     lds_admit_ = admit_lds(dn_);
-    if (dn_.NP > 512 || lds_admit_ > kMaxLds || integrate_lds(dn_, prec_, true) > kMaxLds) {
+    if (dn_.NP > 512 || lds_admit_ + kAdmitFixedLds > kMaxLds || integrate_lds(dn_, prec_, true) > kMaxLds) {
         err = "network too large for one workgroup's LDS";
         return ABDF_E_ARG;
     }
@@ -262,6 +262,10 @@ int Engine::layout(int nslots, void *base, std::string &err) {
     grid_max_ = cus * integrate_resident_per_cu(dn_, prec_, false);
     grid_fp64_max_ = cus * integrate_resident_per_cu(dn_, prec_, true);
     grid_reverse_max_ = cus * reverse_resident_per_cu(dn_);
+    if (grid_max_ == 0 || grid_fp64_max_ == 0) {
+        err = "network too large for one compute unit";
+        return ABDF_E_ARG;
+    }
     n_free_ = 0;
     for (int i = nslots - 1; i >= 0; --i) free_[n_free_++] = i;
     (void)n;
@@ -466,7 +470,7 @@ int Engine::reverse(const AdjIO &io, hipStream_t st, std::string &err) {
         if (rc0 != ABDF_OK) return rc0;
     }
     const size_t lds_adj = adj_lds(dn_);
-    if (lds_adj > kMaxLds || reverse_lds(dn_) > kMaxLds) {
+    if (lds_adj > kMaxLds || reverse_lds(dn_) > kMaxLds || grid_reverse_max_ == 0) {
         err = "network too large for one workgroup's LDS";
         return ABDF_E_ARG;
     }

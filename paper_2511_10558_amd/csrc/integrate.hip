@@ -22,17 +22,17 @@ Persistent integrate_wide_fp64(const DeviceNet &n) { return integrate_wide<false
 // in the LDS beside the matrices (in the FP32-LU form, beside FP64 ones: its
 // cells may come to need them).
 static Persistent integrate_kernel(const DeviceNet &n, int prec, bool fp64_too) {
-    if (n.S <= 64 && integrate_tiny(n, prec, true).lds <= kMaxLds) return integrate_tiny(n, prec, fp64_too);
+    if (n.S <= 64 && integrate_tiny(n, prec, true).total() <= kMaxLds) return integrate_tiny(n, prec, fp64_too);
     return prec == ABDF_PREC_FP32_LU ? integrate_wide_fp32(n) : integrate_wide_fp64(n);
 }
 
-size_t integrate_lds(const DeviceNet &n, int prec, bool fp64_too) { return integrate_kernel(n, prec, fp64_too).lds; }
-size_t reverse_lds(const DeviceNet &n) { return reverse_kernel(n).lds; }
+size_t integrate_lds(const DeviceNet &n, int prec, bool fp64_too) { return integrate_kernel(n, prec, fp64_too).total(); }
+size_t reverse_lds(const DeviceNet &n) { return reverse_kernel(n).total(); }
 
 static int resident_per_cu(const Persistent &p) {
     int nb = 0;
     const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, p.fn, p.threads, p.lds);
-    return (e == hipSuccess && nb > 0) ? nb : 1;
+    return e == hipSuccess ? nb : 1;   // 0: a workgroup does not fit a compute unit
 }
 
 int integrate_resident_per_cu(const DeviceNet &n, int prec, bool fp64_too) {
@@ -43,6 +43,7 @@ int reverse_resident_per_cu(const DeviceNet &n) { return resident_per_cu(reverse
 static hipError_t launch_persistent(const Persistent &p, const Slots &s, const DeviceNet &n, const IntegrateArgs &a,
                                     int grid, hipStream_t st) {
     if (grid <= 0) return hipSuccess;
+    if (p.total() > kMaxLds) return hipErrorInvalidValue;
     Slots ss = s;
     DeviceNet nn = n;
     IntegrateArgs aa = a;

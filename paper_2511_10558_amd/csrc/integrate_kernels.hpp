@@ -11,9 +11,15 @@ namespace abdf {
 struct Persistent {
     const void *fn;
     int threads;
-    size_t lds;
+    size_t lds;            // dynamic
+    size_t fixed;          // static
     bool defers = false;   // puts cells on FP64 factors back (IntegrateArgs::defer)
+    size_t total() const { return lds + fixed; }
 };
+
+// Static LDS of a persistent kernel: StepLds and the phase clocks.
+template <int W>
+constexpr size_t kFixedLds = sizeof(StepLds<W>) + kPhases * sizeof(unsigned long long);
 Persistent integrate_wide_fp64(const DeviceNet &n);
 Persistent integrate_wide_fp32(const DeviceNet &n);
 // for networks of at most 64 species; fp64_too: the FP32-LU form whose LDS also
@@ -151,7 +157,7 @@ Persistent integrate_wide(const DeviceNet &n) {
     // the folded norms' 512 values
     const size_t newton = sizeof(double) * ((kF32 ? 3 : 2) * size_t(n.NP) + n.S +
                                             std::max({size_t(n.R), kLuW + size_t(n.NP) / 2, size_t(512)}));
-    return {(const void *)&k_integrate<W, kF32>, 64 * W, std::max(lu, newton)};
+    return {(const void *)&k_integrate<W, kF32>, 64 * W, std::max(lu, newton), kFixedLds<W>};
 }
 
 }  // namespace abdf

@@ -114,7 +114,7 @@ static Persistent pick(const DeviceNet &n) {
     const void *fn = n.NP <= 16   ? (const void *)&k_integrate_tiny<T, 1, kFp64Too>
                      : n.NP <= 32 ? (const void *)&k_integrate_tiny<T, 2, kFp64Too>
                                   : (const void *)&k_integrate_tiny<T, 4, kFp64Too>;
-    return {fn, 64, TinyLayout<T, kFp64Too>(n).total, sizeof(T) == sizeof(float) && !kFp64Too};
+    return {fn, 64, TinyLayout<T, kFp64Too>(n).total, kFixedLds<1>, sizeof(T) == sizeof(float) && !kFp64Too};
 }
 
 Persistent integrate_tiny(const DeviceNet &n, int prec, bool fp64_too) {

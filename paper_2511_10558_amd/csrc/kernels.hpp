@@ -66,8 +66,9 @@ struct IntegrateArgs {
     int32_t defer;                   // (set by the launcher) the form that does not: it puts cells on FP64 factors back
 };
 
-// LDS bytes per kernel for a network
+// LDS bytes per kernel for a network (the persistent kernels': with their static LDS)
 inline size_t admit_lds(const DeviceNet &n) { return sizeof(double) * (4 * size_t(n.S) + n.R); }
+constexpr size_t kAdmitFixedLds = sizeof(SlotCtl) + (kWaves + 5) * sizeof(double);   // its static LDS
 size_t integrate_lds(const DeviceNet &n, int prec, bool fp64_too);
 size_t reverse_lds(const DeviceNet &n);
 
@@ -75,7 +76,7 @@ hipError_t launch_admit(const Slots &s, const DeviceNet &n, const AdmitArgs &a, 
 // Integrates (sweeps) the queued slots with grid workgroups.
 hipError_t launch_integrate(const Slots &s, const DeviceNet &n, const IntegrateArgs &a, int grid, hipStream_t st);
 hipError_t launch_reverse(const Slots &s, const DeviceNet &n, const IntegrateArgs &a, int grid, hipStream_t st);
-// Their workgroups resident per CU.
+// Their workgroups resident per CU (0: none fits).
 int integrate_resident_per_cu(const DeviceNet &n, int prec, bool fp64_too);
 int reverse_resident_per_cu(const DeviceNet &n);
 hipError_t launch_harvest(const Slots &s, const HarvestArgs &h, hipStream_t st);
@@ -119,7 +120,9 @@ size_t lu_bytes(int NP, int prec);
 hipError_t launch_selftest(int *bad, hipStream_t st);
 hipError_t launch_fill_i32(int32_t *v, int32_t value, int n, hipStream_t st);
 
-// Largest dynamic LDS one workgroup may use on the device.
+// Largest LDS of one workgroup, static and dynamic together.  The runtime launches
+// a kernel that passes it all the same, and the kernel faults: whatever depends on
+// the network is checked against it on the host.
 constexpr size_t kMaxLds = 160 * 1024;
 
 }  // namespace abdf

@@ -342,7 +342,7 @@ Persistent reverse_kernel(const DeviceNet &n) {
     constexpr int W = kIntegrateWaves;
     const size_t solve = sizeof(double) * (2 * size_t(n.NP) + (1 + W) * kLuW + kLuW * kLdb);
     const size_t step = sizeof(double) * (2 * size_t(n.S) + n.R);
-    return {(const void *)&k_reverse<W>, 64 * W, std::max({lu2_lds_bytes<double, W>(n.NP), solve, step})};
+    return {(const void *)&k_reverse<W>, 64 * W, std::max({lu2_lds_bytes<double, W>(n.NP), solve, step}), kFixedLds<W>};
 }
 
 hipError_t launch_adj_admit(const Slots &s, const DeviceNet &n, const AdjArgs &a, size_t lds, hipStream_t st) {

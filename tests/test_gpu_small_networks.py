@@ -75,3 +75,42 @@ def test_interrupted_cells_give_the_same_bits(n, years, precision, method):
     xf, sf, stf = solve_cells(ab, g, cells, device(), hbm_budget_bytes=budget, **kw)
     assert np.array_equal(sf, status) and np.array_equal(xf, x)
     assert np.array_equal(stf, stats)
+
+
+def with_reactions(net, n):
+    """net with its reactions repeated to n, every rate shared among its copies."""
+    i = np.arange(n) % len(net.alpha)
+    return synth.Network(f"{net.name}-{n}rx", net.species, net.comp, net.charge, net.rtype[i], net.reactants[i],
+                         net.products[i], net.alpha[i] / np.bincount(i)[i], net.beta[i], net.gamma[i], net.albedo)
+
+
+# 64 species: the one-wave kernel's dynamic LDS passes 160 KiB less its 624 bytes
+# of static LDS between 562 and 564 reactions, and 160 KiB between 584 and 586
+@pytest.mark.parametrize("n", [562, 564, 575, 584, 586])
+@pytest.mark.parametrize("precision", ["fp64", "fp32_lu"])
+def test_solve_where_the_tables_fill_the_lds(n, precision):
+    import paper_2511_10558_amd as ab
+    base = first_species(synth.network_for_config("net200"), 64)
+    net = with_reactions(base, n)
+    cells = synth.sample_cells(net, 2, seed=n, t_end_yr=1e2)
+    x, status, _ = solve_cells(ab, ab.Network.from_text(net.to_text()), cells, device(), precision=precision)
+    ref, _, _ = solve_cells(ab, ab.Network.from_text(base.to_text()), cells, device(), precision=precision)
+    assert (status == 0).all()
+    # the same chemistry, summed in another order: both within the solver's error at rtol 1e-6
+    assert max(rel_err_above(x[c], ref[c]) for c in range(2)) <= 1e-4
+
+
+# the largest network of 500 species that admission's LDS holds, (4 S + R) doubles
+# and 232 bytes, and the smallest that is refused
+@pytest.mark.parametrize("n,fits", [(18451, True), (18452, False)])
+def test_largest_network(n, fits):
+    import paper_2511_10558_amd as ab
+    net = with_reactions(synth.network_for_config("net500"), n)
+    cells = synth.sample_cells(net, 2, seed=n, t_end_yr=1e0)
+    g = ab.Network.from_text(net.to_text())
+    if not fits:
+        with pytest.raises(ab.AbdfError, match="E_ARG.*too large"):
+            solve_cells(ab, g, cells, device())
+        return
+    _, status, _ = solve_cells(ab, g, cells, device())
+    assert (status == 0).all()
