@@ -517,6 +517,28 @@ __global__ void __launch_bounds__(kAsmThreads) k_newton_matrix_only(DeviceNet n,
     }
 }
 
+// The same for networks whose 16 densest rows do not fit in the LDS (more than
+// some 1200 species): a workgroup to a row, every entry's terms from global memory.
+__global__ void __launch_bounds__(kAsmThreads) k_newton_matrix_large(DeviceNet n, const double *k, const double *x,
+                                                                   const double *cvec, double *M) {
+    const int S = n.S, i = blockIdx.x;
+    const size_t cell = blockIdx.y;
+    const double *kc = k + cell * n.R, *xc = x + cell * S;
+    const double c = cvec[cell];
+    double *row = M + (cell * S + i) * S;
+    for (int j = threadIdx.x; j < S; j += kAsmThreads) {
+        const int e = n.jidx[size_t(i) * n.NP + j];
+        double v = 0.0;
+        for (int t = e < 0 ? 0 : n.jterm_ptr[e], t1 = e < 0 ? 0 : n.jterm_ptr[e + 1]; t < t1; ++t) {
+            const int w = n.jt_rx_other[t], other = (w & 0xffff) - 1;
+            double p = n.jt_coef[t] * kc[w >> 16];
+            if (other >= 0) p *= xc[other];
+            v += p;
+        }
+        row[j] = (i == j ? 1.0 : 0.0) - c * v;
+    }
+}
+
 // Matrix-core lane-layout check: D = A B for integer-valued A (16x4), B (4x16).
 __global__ void k_selftest(int *bad) {
     const int l = threadIdx.x;
@@ -680,9 +702,12 @@ hipError_t launch_newton_matrix(const DeviceNet &n, long long cells, const doubl
                                 const double *c, double *M, hipStream_t st) {
     // grid.y holds at most 65535 cells
     const size_t lds = sizeof(double) * (size_t(n.S) + size_t(std::max(n.asm_nnz, 1)));
+    const bool large = lds > kMaxLds;
+    const auto kernel = large ? k_newton_matrix_large : k_newton_matrix_only;
+    const unsigned blocks = large ? unsigned(n.S) : unsigned((n.S + kAsmRows - 1) / kAsmRows);
     for (long long c0 = 0; c0 < cells; c0 += 65535) {
         const unsigned m = unsigned(std::min<long long>(65535, cells - c0));
-        hipLaunchKernelGGL(k_newton_matrix_only, dim3((n.S + kAsmRows - 1) / kAsmRows, m), dim3(kAsmThreads), lds, st, n,
+        hipLaunchKernelGGL(kernel, dim3(blocks, m), dim3(kAsmThreads), large ? 0 : lds, st, n,
                            k + size_t(c0) * n.R, x + size_t(c0) * n.S, c + c0, M + size_t(c0) * n.S * n.S);
         const hipError_t e = LAUNCH_CHECK();
         if (e != hipSuccess) return e;

@@ -151,6 +151,32 @@ def test_newton_matrix_matches_oracle(ab, dev, name):
         assert np.all(np.abs(M[c] - ref) <= bound + 1e-300)
 
 
+def _dense_rows(n_leaf, n_hub=16):
+    """Leaves that break up into hubs, every hub from every leaf: the hubs' rows of the
+    Jacobian are dense."""
+    sp = [(f"H{i}", {"C": 1}, 0) for i in range(n_hub)] + [(f"L{j}", {"C": 3}, 0) for j in range(n_leaf)]
+    rx = [(synth.COSMIC_RAY, [f"L{j}"], [f"H{(3 * q + m) % n_hub}" for m in range(3)], 1.0 + j % 5 + q, 0.0, 0.0)
+          for j in range(n_leaf) for q in range((n_hub + 2) // 3)]
+    return synth.make_network(f"dense-rows-{n_leaf}", sp, rx)
+
+
+# 16 rows of 1104 and of 1384 nonzeros: the LDS holds the first beside x, not the second
+@pytest.mark.parametrize("n_leaf", [1104, 1384])
+def test_newton_matrix_of_many_species(ab, dev, n_leaf):
+    net = _dense_rows(n_leaf)
+    g = ab.Network.from_text(net.to_text())
+    rng = np.random.default_rng(n_leaf)
+    x = np.exp(rng.uniform(np.log(1e-20), 0.0, (2, net.n_species)))
+    K = np.exp(rng.uniform(np.log(1e-17), np.log(1e-9), (2, net.n_reactions)))
+    cvec = np.array([1e3, 1e11])
+    M = ab.newton_matrix(g, t(K, dev), t(x, dev), t(cvec, dev)).cpu().numpy()
+    absnu = abs(chem.stoichiometry(net))
+    for c in range(2):
+        ref = np.eye(net.n_species) - cvec[c] * chem.Chemistry(net, K[c]).jac(x[c])
+        absJ = (absnu @ abs(chem.rate_derivative(net, K[c], x[c]))).toarray()
+        assert np.all(np.abs(M[c] - ref) <= 16 * EPS * (cvec[c] * absJ + np.abs(ref)) + 1e-300)
+
+
 def _newton_like_matrices(n, batch, seed):
     """Diagonally heavy, badly scaled matrices like I - cJ, plus plain random ones."""
     rng = np.random.default_rng(seed)
