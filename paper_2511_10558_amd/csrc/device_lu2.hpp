@@ -1318,6 +1318,39 @@ __device__ __forceinline__ void lu_solve_left(const T *__restrict__ A, int lda, 
 }
 
 
+// One wave's substitution through a 64 x 64 triangle, a lane per unknown: the
+// unknowns k in ascending (kAscending) or descending order, w_k = v_k / d_k
+// (kUnit: v_k), then v_i -= e_i[k stride] w_k for the lanes i still to come.  e, d:
+// this lane's entries and its diagonal entry.  A quotient is formed from the
+// pivot's reciprocal, taken by every lane at once, with one correction by its
+// remainder (Markstein 1990: the rounded quotient) instead of a division in the
+// chain.  kApart: a lane's products are summed apart and taken from v once, where
+// it is used; where they are small beside v (a Newton matrix's diagonal is the
+// largest entry) that is one rounding of v in place of up to 63.
+template <bool kAscending, bool kUnit, bool kApart>
+__device__ __forceinline__ double substitute(const double *e, int stride, double d, double v) {
+    const int lane = thread_id() & 63;
+    const double rd = kUnit ? 1.0 : 1.0 / d;
+    double sum = 0.0;
+#pragma unroll 8
+    for (int s = 0; s < kLuW; ++s) {
+        const int k = kAscending ? s : kLuW - 1 - s;
+        const double r = kApart ? v - sum : v;
+        const double q = r * rd, w = kUnit ? r : fma(fma(-d, q, r), rd, q);
+        const double x = lane_value(w, k), ek = e[k * stride];
+        const bool after = kAscending ? lane > k : lane < k;
+        if constexpr (kApart) {
+            const double upd = fma(ek, x, sum);
+            sum = lane == k ? 0.0 : (after ? upd : sum);
+            v = lane == k ? w : v;
+        } else {
+            const double upd = fma(-ek, x, v);
+            v = lane == k ? w : (after ? upd : v);
+        }
+    }
+    return v;
+}
+
 // Solves M^T z = b from the factors of P M = L U (M^T = U^T L^T P): forward
 // substitution with U^T, back substitution with L^T, then z[rowmap[i]] = v[i].
 // The off-diagonal blocks enter as column products (lane i & 63 owns column
@@ -1331,10 +1364,8 @@ __device__ __forceinline__ void lu_solve_left(const T *__restrict__ A, int lda, 
 //
 // A chain of block rows, each a round of loads and 64 dependent steps of one
 // wave.  The row map is in LDS (in z, which is written last), so no load waits
-// for another; a block's tile is asked for with its products; and a quotient is
-// formed from the pivot's reciprocal, taken by every lane at once, with one
-// correction by its remainder instead of a division in the chain.  (The solves
-// of a gradient of 64 cells of 200 species: 30 ms a workgroup before, 13.5 now.)
+// for another; a block's tile is asked for with its products; and no division is
+// in the chain (substitute).  (The solves of a gradient of 64 cells of 200 species: 30 ms a workgroup before, 13.5 now.)
 template <typename T, int W>
 __device__ __forceinline__ void lu_solve_left_T(const T *__restrict__ A, const int32_t *__restrict__ rowmap, int NP,
                                                 double *b, double *z, double *t, double *Db) {
@@ -1384,13 +1415,7 @@ __device__ __forceinline__ void lu_solve_left_T(const T *__restrict__ A, const i
         const int r0 = ib * kLuW, Wb = min(kLuW, NP - r0);
         double tv = block(r0, Wb, 0, r0);
         if (grp == 0) {
-            const double d = Db[col * kLdb + col], rd = 1.0 / d;
-#pragma unroll 8
-            for (int k = 0; k < kLuW; ++k) {
-                const double q = tv * rd, w = fma(fma(-d, q, tv), rd, q);
-                const double upd = fma(-Db[k * kLdb + col], lane_value(w, k), tv);
-                tv = col == k ? w : (col > k ? upd : tv);
-            }
+            tv = substitute<true, false, false>(Db + col, kLdb, Db[col * kLdb + col], tv);
             if (col < Wb) b[r0 + col] = tv;
         }
         __syncthreads();
@@ -1400,11 +1425,7 @@ __device__ __forceinline__ void lu_solve_left_T(const T *__restrict__ A, const i
         const int r0 = ib * kLuW, Wb = min(kLuW, NP - r0);
         double tv = block(r0, Wb, r0 + Wb, NP);
         if (grp == 0) {
-#pragma unroll 8
-            for (int k = kLuW - 1; k > 0; --k) {
-                const double upd = fma(-Db[k * kLdb + col], lane_value(tv, k), tv);
-                tv = col < k ? upd : tv;
-            }
+            tv = substitute<false, true, false>(Db + col, kLdb, 1.0, tv);
             if (col < Wb) b[r0 + col] = tv;
         }
         __syncthreads();

@@ -174,21 +174,10 @@ __global__ void __launch_bounds__(kSolveThreads) k_lu_solve(int n, const double 
             if (wave == 0) {
                 const double *Dr = D + lane * kLdb;
                 double v = t[lane];
-                if constexpr (!up) {
-#pragma unroll 8
-                    for (int k = 0; k < kLuW; ++k) {
-                        const double f = fma(-Dr[k], lane_value(v, k), v);
-                        v = lane > k ? f : v;
-                    }
-                } else {
-                    const double d = 1.0 / Dr[lane];
-#pragma unroll 8
-                    for (int k = kLuW - 1; k >= 0; --k) {
-                        const double x = lane_value(v * d, k);
-                        const double f = fma(-Dr[k], x, v);
-                        v = lane < k ? f : (lane == k ? x : v);
-                    }
-                }
+                if constexpr (!up)
+                    v = substitute<true, true, true>(Dr, 1, 1.0, v);
+                else
+                    v = substitute<false, false, true>(Dr, 1, Dr[lane], v);
                 y[r0 + lane] = v;
             }
             __syncthreads();

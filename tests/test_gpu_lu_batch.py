@@ -34,3 +34,18 @@ def test_lu_in_place_at_tile_edges(n, batch, prec):
         assert np.abs(A[i][perm[i]] - L @ U).max() <= 30 * n * u * np.abs(A[i]).max()
         res = np.abs(A[i] @ z[i] - b[i]).max() / (np.abs(A[i]).max() * np.abs(z[i]).max())
         assert res <= 60 * n * u
+
+
+@pytest.mark.parametrize("n", [1, 16, 63, 64, 65, 200])
+def test_lu_solve_divides(n):
+    # factors of a diagonal matrix: each unknown is one quotient, rounded once
+    import paper_2511_10558_amd as ab
+    dev = device()
+    rng = np.random.default_rng(n)
+    d, b = rng.normal(size=(40, n)), rng.normal(size=(40, n))
+    LU = np.zeros((40, n, n))
+    LU[:, np.arange(n), np.arange(n)] = d
+    import torch
+    perm = torch.arange(n, dtype=torch.int32, device=dev).repeat(40, 1)
+    z = ab.lu_solve(t(LU, dev), perm, t(b, dev)).cpu().numpy()
+    assert np.array_equal(z, b / d)
