@@ -1324,19 +1324,19 @@ __device__ __forceinline__ void lu_solve_left(const T *__restrict__ A, int lda, 
 // this lane's entries and its diagonal entry.  A quotient is formed from the
 // pivot's reciprocal, taken by every lane at once, with one correction by its
 // remainder (Markstein 1990: the rounded quotient) instead of a division in the
-// chain.  kApart: a lane's products are summed apart and taken from v once, where
+// chain (kDivide: by division).  kApart: a lane's products are summed apart and taken from v once, where
 // it is used; where they are small beside v (a Newton matrix's diagonal is the
 // largest entry) that is one rounding of v in place of up to 63.
-template <bool kAscending, bool kUnit, bool kApart>
-__device__ __forceinline__ double substitute(const double *e, int stride, double d, double v) {
+template <bool kAscending, bool kUnit, bool kApart, bool kDivide>
+__device__ __forceinline__ double substitute_lanes(const double *e, int stride, double d, double v) {
     const int lane = thread_id() & 63;
-    const double rd = kUnit ? 1.0 : 1.0 / d;
+    const double rd = kUnit || kDivide ? 1.0 : 1.0 / d;
     double sum = 0.0;
 #pragma unroll 8
     for (int s = 0; s < kLuW; ++s) {
         const int k = kAscending ? s : kLuW - 1 - s;
         const double r = kApart ? v - sum : v;
-        const double q = r * rd, w = kUnit ? r : fma(fma(-d, q, r), rd, q);
+        const double q = r * rd, w = kUnit ? r : (kDivide ? r / d : fma(fma(-d, q, r), rd, q));
         const double x = lane_value(w, k), ek = e[k * stride];
         const bool after = kAscending ? lane > k : lane < k;
         if constexpr (kApart) {
@@ -1349,6 +1349,18 @@ __device__ __forceinline__ double substitute(const double *e, int stride, double
         }
     }
     return v;
+}
+
+// The same for any d and v.  The corrected quotient makes a NaN of what a division
+// keeps finite or infinite: the reciprocal of a pivot below 2^-1024 or of zero is
+// infinite, a quotient may pass the range, a pivot or v may be infinite.  A block
+// whose unknowns do not all come out finite is done again by division.
+template <bool kAscending, bool kUnit, bool kApart>
+__device__ __forceinline__ double substitute(const double *e, int stride, double d, double v) {
+    const double w = substitute_lanes<kAscending, kUnit, kApart, false>(e, stride, d, v);
+    if constexpr (!kUnit)
+        if (__ballot(!isfinite(w)) != 0) return substitute_lanes<kAscending, kUnit, kApart, true>(e, stride, d, v);
+    return w;
 }
 
 // Solves M^T z = b from the factors of P M = L U (M^T = U^T L^T P): forward

@@ -49,3 +49,22 @@ def test_lu_solve_divides(n):
     perm = torch.arange(n, dtype=torch.int32, device=dev).repeat(40, 1)
     z = ab.lu_solve(t(LU, dev), perm, t(b, dev)).cpu().numpy()
     assert np.array_equal(z, b / d)
+
+
+def test_lu_solve_divides_at_the_range_ends():
+    # what a quotient by way of the reciprocal loses: subnormal, huge, zero and
+    # infinite pivots, quotients past the range.  One rounding each; where the
+    # remainder or the quotient is subnormal a second one of a unit in the last place
+    import torch
+    import paper_2511_10558_amd as ab
+    dev = device()
+    ends = np.array([5e-324, 3e-320, 1e-309, 2.3e-308, 1e-200, 0.7, 1e200, 4e307, 1.7e308, 0.0, np.inf, np.nan])
+    d, b = (v.ravel() for v in np.meshgrid(np.concatenate([ends, -ends]), ends))
+    perm = torch.zeros((len(d), 1), dtype=torch.int32, device=dev)
+    z = ab.lu_solve(t(d.reshape(-1, 1, 1), dev), perm, t(b.reshape(-1, 1), dev)).cpu().numpy().ravel()
+    with np.errstate(all="ignore"):
+        ref = b / d
+    assert np.array_equal(np.isnan(z), np.isnan(ref)) and np.array_equal(np.isinf(z), np.isinf(ref))
+    fin = np.isfinite(ref)
+    assert np.array_equal(z[np.isinf(ref)], ref[np.isinf(ref)])
+    assert np.all(np.abs(z[fin] - ref[fin]) <= np.spacing(np.abs(ref[fin])))
