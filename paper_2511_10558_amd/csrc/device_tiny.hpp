@@ -163,9 +163,12 @@ struct TinyCell {
         if (int(threadIdx.x) < S) xs[threadIdx.x] = xJ[threadIdx.x];
         wave_lds_order();
         jacobian_values<64, 2, 4>(n, k, xs, jv);
+        // a lane scatters what another one wrote (jacobian_values takes the long
+        // lists in an order of their own)
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         scatter(n, jv);
     }
-    // each lane scatters the nonzeros it wrote
+    // the nonzeros (global memory) into the dense J
     __device__ __forceinline__ void scatter(const DeviceNet &n, const double *jv) {
         for (int e = threadIdx.x; e < S * ld; e += 64) J[e] = 0.0;
         wave_lds_order();
