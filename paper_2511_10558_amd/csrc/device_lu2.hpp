@@ -113,7 +113,7 @@ struct LuLds {
     int32_t *piv_pos;   // pivot column -> position
     double *redv;       // [2][waves] arg-max partials
     int32_t *redi;
-    int32_t *rwave;     // [2] wave holding logical row r; [2] first zero pivot (1-based) or INT_MAX
+    int32_t *rwave;     // [2] wave holding logical row r; first zero pivot (1-based) or INT_MAX; DenseStorage::nan
     int32_t *dpos;      // [16] positions of the diagonal pivot rows
     int32_t *spec_bad;  // the diagonal pivots were refused
     T *crow;            // [2][waves][kCrowLd] candidate rows
@@ -286,6 +286,9 @@ struct SlotStorage {
     T *A;
     int lda;
     using v4 = typename V4<T>::type;
+    __device__ __forceinline__ void begin_column() {}
+    __device__ __forceinline__ static bool is_pad(int) { return false; }
+    __device__ __forceinline__ static void store_pad(int, int, T) {}
     // four entries of a row from column c, a multiple of 4
     __device__ __forceinline__ v4 load4(int row, int c) const {
         return *reinterpret_cast<const v4 *>(A + uint32_t(row * lda + c));
@@ -293,25 +296,50 @@ struct SlotStorage {
     __device__ __forceinline__ void store(int row, int c, T v) const { A[uint32_t(row * lda + c)] = v; }
 };
 
-// The caller's n x n FP64 matrix itself, factored in place; the padding to a
-// multiple of 16 (the identity's) is not stored, and the rows of L that belong
-// to it are zero.  Rows begin on 8-byte boundaries.
-template <typename T>
+// The caller's n x n FP64 matrix itself, factored in place.  The rows that pad it
+// to a multiple of 16 (the identity's, zero in its columns) go to pad, n entries
+// each: a column that is zero or NaN in every row left may take one as its pivot.
+// Their entries stay zeros of either sign or, beside a factor that is not finite,
+// become NaN, so a byte says which (as doubles they took the scratch of 256
+// matrices of order 500 past 64 MiB, whose allocation cost 0.3 ms a call).  Only
+// once one is NaN (nan: an LDS flag) are they read back.  The padding's columns are
+// not stored.  Rows begin on 8-byte boundaries.  kOneBlock (n <= 64): nothing is
+// read back, and pad is in the LDS.
+template <typename T, bool kOneBlock>
 struct DenseStorage {
     static constexpr bool kKeepInverses = false;
     double *A;
     int n;
+    uint8_t *pad;
+    int32_t *nan;
+    bool read_pad = false;
     using v4 = typename V4<T>::type;
+    __device__ __forceinline__ static double decode(int code) {
+        return code == 2 ? std::numeric_limits<double>::quiet_NaN() : (code == 1 ? -0.0 : 0.0);
+    }
+    // before a block column, after a barrier
+    __device__ __forceinline__ void begin_column() { read_pad = __builtin_amdgcn_readfirstlane(*nan) != 0; }
     __device__ __forceinline__ v4 load4(int row, int c) const {
         double d[4];
         __builtin_memcpy(d, A + uint32_t(min(row, n - 1) * n + c), sizeof(d));
         v4 v;
 #pragma unroll
         for (int k = 0; k < 4; ++k) v[k] = row < n ? T(d[k]) : T(0);
+        if (!kOneBlock && read_pad && row >= n) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[k] = T(decode(pad[(row - n) * n + c + k]));
+        }
         return v;
     }
     __device__ __forceinline__ void store(int row, int c, T v) const {
         if (row < n && c < n) A[uint32_t(row * n + c)] = double(v);
+    }
+    __device__ __forceinline__ bool is_pad(int row) const { return row >= n; }
+    __device__ __forceinline__ void store_pad(int row, int c, T v) const {
+        if (row >= n && c < n) {
+            pad[(row - n) * n + c] = v != v ? 2 : (signbit(v) ? 1 : 0);
+            if (v != v) *nan = 1;
+        }
     }
 };
 
@@ -339,7 +367,7 @@ struct DenseSource {
 // of L that later block columns need, one 64 x 64 block after the other.  A single
 // wave (W = 1) holds kTiles x kTiles tiles, NP <= 16 kTiles.
 template <typename T, int W, int kTiles, typename Src, typename Storage>
-__device__ __forceinline__ void lu_factor_left(const Storage &st, int NP, int32_t *__restrict__ perm_out,
+__device__ __forceinline__ void lu_factor_left(Storage st, int NP, int32_t *__restrict__ perm_out,
                                                T *__restrict__ dinv, int32_t *info, unsigned char *smem,
                                                const Src &src) {
     using M = Mfma<T>;
@@ -362,7 +390,10 @@ __device__ __forceinline__ void lu_factor_left(const Storage &st, int NP, int32_
 
     for (int i = tid0; i < NP; i += (64 * W)) perm[i] = i;
     if (tid0 < 16) dpos[tid0] = 0;      // every position read from it stays in the panel
-    if (tid0 == 0) rwave[2] = 0x7fffffff;
+    if (tid0 == 0) {
+        rwave[2] = 0x7fffffff;
+        rwave[3] = 0;
+    }
     __syncthreads();
 
     for (int j = 0; j < NB; ++j) {
@@ -371,6 +402,7 @@ __device__ __forceinline__ void lu_factor_left(const Storage &st, int NP, int32_
         const int tid = thread_id(), lane = tid & 63, wave = wave_of(tid);
         const int g = lane >> 4, lc = lane & 15;
         const int c0 = j * kLuW;
+        st.begin_column();
         const int Wj = min(kLuW, NP - c0);
         const int CTj = Wj / 16;
         for (int q = tid; q < NP; q += (64 * W)) {
@@ -1107,6 +1139,17 @@ __device__ __forceinline__ void lu_factor_left(const Storage &st, int NP, int32_
 #pragma unroll
                         for (int v = 0; v < 4; ++v)
                             st.store(sto[16 * rt + M::row(lane, v)], c0 + 16 * ct + lc, acc[s][ct][v]);
+            // the rows of the padding: one wave has them, unless rows were exchanged
+            int row[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) row[v] = rt < RT ? sto[16 * rt + M::row(lane, v)] : 0;
+            if (__any(st.is_pad(max(max(row[0], row[1]), max(row[2], row[3]))))) {
+#pragma unroll
+                for (int ct = 0; ct < kCT; ++ct)
+                    if (ct < CTj)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) st.store_pad(row[v], c0 + 16 * ct + lc, acc[s][ct][v]);
+            }
         }
         __syncthreads();
         if (kKeep || j + 1 < NB) {

@@ -20,8 +20,9 @@ constexpr int kLuWaves = 8;
 
 // Row i of the factors from storage row perm[i] to row i, 32 columns at a time:
 // every row of the strip is read before any is written.  Rows that are in place
-// (on the Newton matrices nearly all are) are neither read nor written.
-__device__ __forceinline__ void permute_rows(double *__restrict__ A, int n, const int32_t *perm) {
+// (on the Newton matrices nearly all are) are neither read nor written.  pad: the
+// rows of the padding (DenseStorage).
+__device__ __forceinline__ void permute_rows(double *__restrict__ A, int n, const int32_t *perm, const uint8_t *pad) {
     constexpr int kRows = 64 * kLuWaves / 32, kPer = kLuMaxNP / kRows;
     const int tid = thread_id(), col = tid & 31, r0 = tid >> 5;
     if (!__syncthreads_or(tid < n && perm[tid] != tid)) return;
@@ -30,41 +31,49 @@ __device__ __forceinline__ void permute_rows(double *__restrict__ A, int n, cons
         double v[kPer];
 #pragma unroll
         for (int k = 0; k < kPer; ++k) {
-            const int r = r0 + kRows * k, from = r < n ? min(perm[r], n - 1) : r;
-            v[k] = r < n && c < n && from != r ? A[uint32_t(from * n + c)] : 0.0;
+            const int r = r0 + kRows * k, from = r < n ? perm[r] : r;
+            v[k] = r < n && c < n && from < n && from != r ? A[uint32_t(from * n + c)] : 0.0;
+            if (r < n && c < n && from >= n) v[k] = DenseStorage<double, true>::decode(pad[(from - n) * n + c]);
         }
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < kPer; ++k) {
             const int r = r0 + kRows * k;
-            if (r < n && c < n && min(perm[r], n - 1) != r) A[uint32_t(r * n + c)] = v[k];
+            if (r < n && c < n && perm[r] != r) A[uint32_t(r * n + c)] = v[k];
         }
     }
 }
 
-// The workgroups resident at once take the matrices in turn, so that the
-// scratch for the inverses of the diagonal blocks of L (scratch: lu_scratch_elems
-// entries a workgroup) does not grow with the batch.
+// The workgroups resident at once take the matrices in turn, so that the scratch
+// (n > 64: lu_scratch_bytes a workgroup, the inverses of the diagonal blocks of L
+// and the rows of the padding) does not grow with the batch.
 template <typename T>
-__host__ __device__ constexpr size_t lu_scratch_elems(int NP) {
+__host__ __device__ constexpr size_t lu_inverse_elems(int NP) {
     return size_t((NP + kLuW - 1) / kLuW - 1) * kLuW * kLuW;
 }
-
 template <typename T>
+__host__ __device__ constexpr size_t lu_scratch_bytes(int n, int NP) {
+    return n <= kLuW ? 0 : lu_inverse_elems<T>(NP) * sizeof(T) + (size_t(NP - n) * n + 15) / 16 * 16;
+}
+
+template <typename T, bool kOneBlock>
 __global__ void __launch_bounds__(64 * kLuWaves) k_lu_factor(int n, int batch, double *A0, int32_t *perm_out,
-                                                             int32_t *info, T *scratch) {
+                                                             int32_t *info, unsigned char *scratch) {
     extern __shared__ double smem[];
     unsigned char *lds = reinterpret_cast<unsigned char *>(smem);
     const int NP = (n + 15) / 16 * 16;
-    const int32_t *perm = LuLds<T, kLuWaves>(NP, lds).perm;
-    T *dinv = scratch + blockIdx.x * lu_scratch_elems<T>(NP);
+    const LuLds<T, kLuWaves> l(NP, lds);
+    const int32_t *perm = l.perm;
+    T *dinv = reinterpret_cast<T *>(scratch + blockIdx.x * lu_scratch_bytes<T>(n, NP));
+    // one block column: Xb is free once the panel is factored
+    uint8_t *pad = reinterpret_cast<uint8_t *>(kOneBlock ? l.Xb : dinv + lu_inverse_elems<T>(NP));
     for (int m = blockIdx.x; m < batch; m += gridDim.x) {
         double *A = A0 + size_t(m) * n * n;
-        lu_factor_left<T, kLuWaves, 4>(DenseStorage<T>{A, n}, NP, nullptr, dinv, info ? info + m : nullptr, lds,
-                                    DenseSource<T>{A, n});
+        lu_factor_left<T, kLuWaves, 4>(DenseStorage<T, kOneBlock>{A, n, pad, l.rwave + 3}, NP, nullptr, dinv,
+                                       info ? info + m : nullptr, lds, DenseSource<T>{A, n});
         __syncthreads();
         for (int i = thread_id(); i < n; i += 64 * kLuWaves) perm_out[size_t(m) * n + i] = perm[i];
-        permute_rows(A, n, perm);
+        permute_rows(A, n, perm, pad);
         __syncthreads();
     }
 }
@@ -73,7 +82,8 @@ template <typename T>
 static LuFactorPlan plan_factor(int n, long long batch) {
     const int NP = (n + 15) / 16 * 16;
     LuFactorPlan p;
-    p.fn = reinterpret_cast<const void *>(&k_lu_factor<T>);
+    p.fn = n <= kLuW ? reinterpret_cast<const void *>(&k_lu_factor<T, true>)
+                     : reinterpret_cast<const void *>(&k_lu_factor<T, false>);
     p.lds = lu2_lds_bytes<T, kLuWaves>(NP);
     int per_cu = 0, cus = 0, dev = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, p.fn, 64 * kLuWaves, p.lds) != hipSuccess || per_cu < 1)
@@ -82,7 +92,7 @@ static LuFactorPlan plan_factor(int n, long long batch) {
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
         cus = 256;
     p.grid = int(std::min<long long>(batch, (long long)per_cu * cus));
-    p.scratch = size_t(p.grid) * lu_scratch_elems<T>(NP) * sizeof(T);
+    p.scratch = size_t(p.grid) * lu_scratch_bytes<T>(n, NP);
     return p;
 }
 

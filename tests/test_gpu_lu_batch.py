@@ -68,3 +68,22 @@ def test_lu_solve_divides_at_the_range_ends():
     fin = np.isfinite(ref)
     assert np.array_equal(z[np.isinf(ref)], ref[np.isinf(ref)])
     assert np.all(np.abs(z[fin] - ref[fin]) <= np.spacing(np.abs(ref[fin])))
+
+
+# Where every row left is NaN, a row that pads the matrix to a multiple of 16 is the
+# pivot (perm past n - 1).  Such a row is zero in the matrix's columns, and remains
+# zero or NaN; what stands in the factors there is that row, not one of the matrix.
+@pytest.mark.parametrize("n", [15, 17, 50, 65, 100, 200])
+@pytest.mark.parametrize("prec", ["fp64", "fp32_lu"])
+def test_lu_factor_of_nan_beside_padding(n, prec):
+    import paper_2511_10558_amd as ab
+    dev = device()
+    rng = np.random.default_rng(n)
+    A = rng.normal(size=(3, n, n)) + 3 * n * np.eye(n)
+    A[0, -1, -1] = np.nan             # the last pivot
+    A[1, :, 0] = np.nan               # a whole column
+    A[2, n // 2] = np.nan             # a whole row
+    LU, perm, _ = (v.cpu().numpy() for v in ab.lu_factor(t(A, dev), precision=prec))
+    for i in range(3):
+        pad = LU[i][perm[i] >= n]
+        assert len(pad) > 0 and np.all(np.isnan(pad) | (pad == 0.0))
