@@ -94,16 +94,15 @@ abdf_status check_opts(const abdf_options &o) {
 // for an engine that takes the network's cached workspace, the cached bytes),
 // at most `want`.
 long long slot_count(const abdf::HostNetwork &net, const abdf::DeviceNet &dn, const abdf_options &o, long long want,
-                     size_t extra_per_slot = 0, bool uses_cache = false) {
-    const size_t per = abdf::Engine::bytes_per_slot(dn, o.precision) + extra_per_slot;
-    long long n = want;
-    if (o.hbm_budget_bytes > 0) n = std::min<long long>(n, (long long)(o.hbm_budget_bytes / per));
-    size_t free_b = 0, total_b = 0;
+                     bool &padded, size_t extra_per_slot = 0, bool uses_cache = false) {
+    size_t avail = SIZE_MAX, free_b = 0, total_b = 0;
+    if (o.hbm_budget_bytes > 0) avail = o.hbm_budget_bytes;
     if (hipMemGetInfo(&free_b, &total_b) == hipSuccess && free_b > 0) {
         if (uses_cache) free_b += net.cached_workspace_bytes(dn.device);
-        n = std::min<long long>(n, (long long)(0.85 * double(free_b) / double(per)));
+        avail = std::min(avail, size_t(0.85 * double(free_b)));
     }
-    return n;
+    padded = abdf::Engine::padded(dn, avail, extra_per_slot);
+    return (long long)std::min<size_t>(size_t(want), avail / (abdf::Engine::bytes_per_slot(dn, padded) + extra_per_slot));
 }
 
 }  // namespace
@@ -196,11 +195,13 @@ abdf_status abdf_solve(const abdf_network *net, int64_t n_cells, const double *T
         std::string err;
         const abdf::DeviceNet *dn = net->host.device_tables(err);
         if (!dn) return fail(ABDF_E_DEVICE, err);
-        const long long nslots = slot_count(net->host, *dn, o, n_cells, 0, /*uses_cache=*/true);
+        bool padded = true;
+        const long long nslots = slot_count(net->host, *dn, o, n_cells, padded, 0, /*uses_cache=*/true);
         if (nslots < 1) return fail(ABDF_E_BUDGET, "not even one cell fits in the workspace budget");
         abdf::Engine eng(net->host, *dn, o.precision, o.max_steps);
         int r = eng.set_options(o, err);
         if (r != ABDF_OK) return fail(static_cast<abdf_status>(r), err);
+        eng.set_padded(padded);
         r = eng.init(int(nslots), err, /*cache_workspace=*/true);
         if (r != ABDF_OK) return fail(static_cast<abdf_status>(r), err);
         abdf::BatchIO io{n_cells, T, n_H, A_V, zeta, G0, x0, t_end, x_out, cell_status, stats};
@@ -250,17 +251,19 @@ abdf_status abdf_solve_noalloc(const abdf_network *net, int64_t n_cells, const d
     const size_t cap = o.hbm_budget_bytes > 0 ? std::min<size_t>(o.hbm_budget_bytes, abdf::kNoAllocScratchBytes)
                                               : abdf::kNoAllocScratchBytes;
     long long nslots = std::min<long long>(n_cells, hb.max_slots);
-    const size_t per = abdf::Engine::bytes_per_slot(*dn, o.precision);
+    const bool padded = abdf::Engine::workspace_bytes(*dn, 1, true) <= cap;
+    const size_t per = abdf::Engine::bytes_per_slot(*dn, padded);
     nslots = std::min<long long>(nslots, (long long)(cap / per) + 1);
-    while (nslots > 0 && abdf::Engine::workspace_bytes(*dn, nslots) > cap) --nslots;
+    while (nslots > 0 && abdf::Engine::workspace_bytes(*dn, nslots, padded) > cap) --nslots;
     if (nslots < 1)
         return fail(ABDF_E_BUDGET, "one cell of this network needs " +
-                                       std::to_string(abdf::Engine::workspace_bytes(*dn, 1)) +
+                                       std::to_string(abdf::Engine::workspace_bytes(*dn, 1, padded)) +
                                        " bytes of workspace, more than the " + std::to_string(cap) +
                                        " bytes the no-allocation entry point may use");
     abdf::Engine eng(net->host, *dn, o.precision, o.max_steps);
     r = eng.set_options(o, err, hb.atol);
     if (r != ABDF_OK) return fail(static_cast<abdf_status>(r), err);
+    eng.set_padded(padded);
     r = eng.init_external(int(nslots), scratch, cap, hb, err);
     if (r != ABDF_OK) return fail(static_cast<abdf_status>(r), err);
     abdf::BatchIO io{n_cells, T, n_H, A_V, zeta, G0, x0, t_end, x_out, cell_status, stats};
@@ -391,13 +394,15 @@ abdf_status abdf_server_create(const abdf_network *net, const abdf_server_option
         if (!dn) return fail(ABDF_E_DEVICE, err);
         // staging per slot: admission inputs (8 + S doubles), outputs (S doubles, status, stats)
         const size_t staging = (8 + 2 * size_t(dn->S)) * sizeof(double) + 16 + sizeof(abdf_cell_stats);
-        long long nslots = slot_count(net->host, *dn, o.solve, o.max_slots > 0 ? o.max_slots : INT32_MAX, staging);
+        bool padded = true;
+        long long nslots =
+            slot_count(net->host, *dn, o.solve, o.max_slots > 0 ? o.max_slots : INT32_MAX, padded, staging);
         if (nslots < 1) return fail(ABDF_E_BUDGET, "not even one cell fits in the workspace budget");
         int dev = 0;
         HIP_OR_FAIL(hipGetDevice(&dev));
         auto s = std::make_unique<abdf_server>();
         s->impl = std::make_unique<abdf::Server>(net->host, *dn, o, dev);
-        int r = s->impl->start(int(nslots), err);
+        int r = s->impl->start(int(nslots), padded, err);
         if (r != ABDF_OK) return fail(static_cast<abdf_status>(r), err);
         *out = s.release();
         return ok();

@@ -82,12 +82,12 @@ int Tape::record(const BatchIO &io, const double *alpha, const abdf_options &opt
     HIP_TRY(hipMemsetAsync(len_, 0, C * 4, st));
 
     // slots: what remains of the budget and of the free memory after the tape
-    const size_t per = Engine::bytes_per_slot(dn_, opt.precision) + R * 8;
-    long long nslots = C_;
-    if (opt.hbm_budget_bytes > 0) nslots = std::min<long long>(nslots, (long long)((opt.hbm_budget_bytes - total) / per));
-    size_t free_b = 0, total_b = 0;
+    size_t avail = SIZE_MAX, free_b = 0, total_b = 0;
+    if (opt.hbm_budget_bytes > 0) avail = opt.hbm_budget_bytes - total;
     if (hipMemGetInfo(&free_b, &total_b) == hipSuccess && free_b > 0)
-        nslots = std::min<long long>(nslots, (long long)(0.85 * double(free_b) / double(per)));
+        avail = std::min(avail, size_t(0.85 * double(free_b)));
+    const bool padded = Engine::padded(dn_, avail, R * 8);
+    const long long nslots = (long long)std::min<size_t>(size_t(C_), avail / (Engine::bytes_per_slot(dn_, padded) + R * 8));
     if (nslots < 1) {
         err = "not even one cell fits in the workspace budget beside the step tape";
         return ABDF_E_BUDGET;
@@ -100,6 +100,7 @@ int Tape::record(const BatchIO &io, const double *alpha, const abdf_options &opt
     eng_ = std::make_unique<Engine>(net_, dn_, opt.precision, opt.max_steps);
     int rc = eng_->set_options(opt, err);
     if (rc != ABDF_OK) return rc;
+    eng_->set_padded(padded);
     rc = eng_->init(int(nslots), err);
     if (rc != ABDF_OK) return rc;
     Slots &s = eng_->slots();

@@ -89,6 +89,7 @@ struct Slots {
     void *lu;         // [n] factors (double or float, NP x NP), rows in storage order, lu_stride bytes apart
     void *dinv;       // [n] inverses of the diagonal blocks' triangles [NB][2][64][64], dinv_stride bytes apart
     size_t lu_stride, dinv_stride;
+    int lda;          // leading dimension of the factors
     int32_t *perm;    // [n][NP]
     int32_t *fifo;    // [n] ring of admitted slots
     int32_t *held;    // [n] ring of interrupted slots

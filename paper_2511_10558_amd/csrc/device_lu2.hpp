@@ -149,8 +149,9 @@ __device__ __forceinline__ void wave_lds_order() {
 }
 
 // Leading dimension of the stored factors: rows 4 kB apart would put a block
-// column's rows in the same few channels of the L2 and of the memory.
-__host__ __device__ constexpr int lu_ld(int NP) { return NP % 128 == 0 ? NP + 16 : NP; }
+// column's rows in the same few channels of the L2 and of the memory.  (Slots::lda
+// is NP itself where not even one slot fits otherwise.)
+constexpr int lu_ld(int NP) { return NP % 128 == 0 ? NP + 16 : NP; }
 
 // Elements of the per-matrix inverse diagonal blocks.
 template <typename T>
@@ -279,7 +280,7 @@ __device__ __forceinline__ float lane_value(float v, int src) {
 }
 
 // Where lu_factor_left keeps the factors: rows in storage order, leading
-// dimension lu_ld(NP), in T (a slot's own storage).
+// dimension lda, in T (a slot's own storage).
 template <typename T>
 struct SlotStorage {
     static constexpr bool kKeepInverses = true;   // the solves use them
@@ -1422,13 +1423,13 @@ __device__ __forceinline__ double substitute(const double *e, int stride, double
 // for another; a block's tile is asked for with its products; and no division is
 // in the chain (substitute).  (The solves of a gradient of 64 cells of 200 species: 30 ms a workgroup before, 13.5 now.)
 template <typename T, int W>
-__device__ __forceinline__ void lu_solve_left_T(const T *__restrict__ A, const int32_t *__restrict__ rowmap, int NP,
+__device__ __forceinline__ void lu_solve_left_T(const T *__restrict__ A, int lda, const int32_t *__restrict__ rowmap, int NP,
                                                 double *b, double *z, double *t, double *Db) {
     static_assert(64 * W >= kLuMaxNP, "one thread per row");
     constexpr int kU = kLuW / W;          // rows of a block per wave
     const int tid = thread_id();
     const int col = tid & 63, grp = wave_of(tid);
-    const int NB = (NP + kLuW - 1) / kLuW, lda = lu_ld(NP);
+    const int NB = (NP + kLuW - 1) / kLuW;
     int32_t *perm = reinterpret_cast<int32_t *>(z);
     if (tid < NP) perm[tid] = rowmap[tid];
     __syncthreads();

@@ -426,7 +426,7 @@ __device__ __forceinline__ void factor_slot(const Slots &s, const DeviceNet &n, 
         __syncthreads();
     }
     NewtonMatrixSource<T> src{n.jmask, n.jbase, n.nbw, jv, uniform(cs.c)};
-    lu_factor_left<T, W, 4>(SlotStorage<T>{slot_lu<T>(s, slot), lu_ld(NP)}, NP, s.perm + size_t(slot) * NP, slot_dinv<T>(s, slot), nullptr,
+    lu_factor_left<T, W, 4>(SlotStorage<T>{slot_lu<T>(s, slot), s.lda}, NP, s.perm + size_t(slot) * NP, slot_dinv<T>(s, slot), nullptr,
                          reinterpret_cast<unsigned char *>(smem), src);
     __syncthreads();
 }
@@ -444,7 +444,7 @@ __device__ __forceinline__ void solve_slot(const Slots &s, int slot, const doubl
     const int N = min(NP, S + (S & 1));   // the padding past S is the identity's
     // FP64: 6 tiles of 16 registers a thread in flight
     constexpr int kDepth = sizeof(T) == sizeof(double) ? 6 : 8;
-    lu_solve_left<T, 64 * W, kDepth>(slot_lu<T>(s, slot), lu_ld(NP), slot_dinv<T>(s, slot), perm, NP, N, b, z,
+    lu_solve_left<T, 64 * W, kDepth>(slot_lu<T>(s, slot), s.lda, slot_dinv<T>(s, slot), perm, NP, N, b, z,
                                      scratch);
 }
 

@@ -180,7 +180,7 @@ struct TinyCell {
     // in LDS for the solves.
     template <typename U>
     __device__ __forceinline__ void factor(const Slots &s, int slot, double c) {
-        lu_factor_left<U, 1, kTiles>(SlotStorage<U>{slot_lu<U>(s, slot), lu_ld(NP)}, NP, s.perm + size_t(slot) * NP,
+        lu_factor_left<U, 1, kTiles>(SlotStorage<U>{slot_lu<U>(s, slot), s.lda}, NP, s.perm + size_t(slot) * NP,
                                      slot_dinv<U>(s, slot), nullptr, lu, TinySource<U>{J, S, ld, c});
         wave_lds_order();
     }

@@ -130,11 +130,14 @@ Engine::~Engine() {
 
 // Factor storage per slot: FP64-sized in both forms, since an FP32-LU cell can
 // fall back to FP64 factors.
-size_t Engine::bytes_per_slot(const DeviceNet &dn, int prec) {
-    (void)prec;
+static size_t lu_bytes(const DeviceNet &dn, bool padded) {
+    return size_t(dn.NP) * size_t(padded ? lu_leading_dim(dn.NP) : dn.NP) * sizeof(double);
+}
+
+size_t Engine::bytes_per_slot(const DeviceNet &dn, bool padded) {
     const size_t S = dn.S, R = dn.R, NP = dn.NP;
     return sizeof(SlotCtl) + 5 * sizeof(double) + R * sizeof(double) + kDRows * S * sizeof(double) +
-           5 * S * sizeof(double) + size_t(std::max(dn.nnzJ, 1)) * sizeof(double) + lu_bytes(int(NP), ABDF_PREC_FP64) +
+           5 * S * sizeof(double) + size_t(std::max(dn.nnzJ, 1)) * sizeof(double) + lu_bytes(dn, padded) +
            dinv_bytes(int(NP), ABDF_PREC_FP64) +
            NP * sizeof(int32_t) + 4 * sizeof(int32_t) + sizeof(long long);
 }
@@ -178,9 +181,9 @@ namespace {
 struct Layout {
     static constexpr int kParts = 20;
     size_t bytes[kParts];
-    Layout(const DeviceNet &dn, size_t n) {
+    Layout(const DeviceNet &dn, size_t n, bool padded) {
         const size_t S = dn.S, R = dn.R, NP = dn.NP;
-        const size_t lu_stride = lu_bytes(int(NP), ABDF_PREC_FP64), dinv_stride = dinv_bytes(int(NP), ABDF_PREC_FP64);
+        const size_t lu_stride = lu_bytes(dn, padded), dinv_stride = dinv_bytes(int(NP), ABDF_PREC_FP64);
         const size_t b[kParts] = {
             n * sizeof(SlotCtl), n * 5 * sizeof(double), n * R * sizeof(double), n * kDRows * S * sizeof(double),
             n * S * sizeof(double), n * S * sizeof(double), n * S * sizeof(double), n * S * sizeof(double),
@@ -197,13 +200,15 @@ struct Layout {
 };
 }  // namespace
 
-size_t Engine::workspace_bytes(const DeviceNet &dn, long long n) { return Layout(dn, size_t(n)).total(); }
+size_t Engine::workspace_bytes(const DeviceNet &dn, long long n, bool padded) {
+    return Layout(dn, size_t(n), padded).total();
+}
 
 // Points the slot arrays into base (workspace_bytes(nslots) bytes) and sets
 // the launch shapes.
 int Engine::layout(int nslots, void *base, std::string &err) {
     const size_t n = size_t(nslots), S = dn_.S, NP = dn_.NP;
-    const Layout lay(dn_, n);
+    const Layout lay(dn_, n, padded_);
     void *part[Layout::kParts];
     size_t off = 0;
     for (int i = 0; i < Layout::kParts; ++i) {
@@ -228,7 +233,8 @@ int Engine::layout(int nslots, void *base, std::string &err) {
     s_.jval = static_cast<double *>(part[9]);
     s_.lu = part[10];
     s_.dinv = part[11];
-    s_.lu_stride = lu_bytes(int(NP), ABDF_PREC_FP64);
+    s_.lu_stride = lu_bytes(dn_, padded_);
+    s_.lda = padded_ ? lu_leading_dim(int(NP)) : int(NP);
     s_.dinv_stride = dinv_bytes(int(NP), ABDF_PREC_FP64);
     s_.perm = static_cast<int32_t *>(part[12]);
     s_.fifo = static_cast<int32_t *>(part[13]);
@@ -274,7 +280,7 @@ int Engine::layout(int nslots, void *base, std::string &err) {
 
 int Engine::init(int nslots, std::string &err, bool cache_workspace) {
     const size_t n = size_t(nslots);
-    const size_t total = workspace_bytes(dn_, nslots);
+    const size_t total = workspace_bytes(dn_, nslots, padded_);
     cached_ = cache_workspace;
     base_ = cached_ ? net_.take_workspace(dn_.device, total, &base_bytes_) : nullptr;
     if (!base_) {
@@ -300,7 +306,7 @@ int Engine::init(int nslots, std::string &err, bool cache_workspace) {
 
 int Engine::init_external(int nslots, void *base, size_t bytes, const HostBuffers &hb, std::string &err) {
     ext_ = true;
-    if (nslots < 1 || nslots > hb.max_slots || workspace_bytes(dn_, nslots) > bytes) {
+    if (nslots < 1 || nslots > hb.max_slots || workspace_bytes(dn_, nslots, padded_) > bytes) {
         err = "slot count beyond the external workspace";
         return ABDF_E_ARG;
     }

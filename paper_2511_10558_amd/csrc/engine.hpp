@@ -72,7 +72,7 @@ class Engine {
     // kernel timers; the counters are cleared by a kernel on the solve's stream.  Returns an abdf_status.
     int init_external(int nslots, void *base, size_t bytes, const HostBuffers &hb, std::string &err);
     // Device bytes of the workspace of n slots (as init lays it out).
-    static size_t workspace_bytes(const DeviceNet &dn, long long n);
+    static size_t workspace_bytes(const DeviceNet &dn, long long n, bool padded);
     // relative change of c within which a slot keeps its factorisation (0: none)
     void set_lu_reuse(double v) { lu_reuse_ = v; s_.lu_reuse = v; }
     // highest order the order selection may reach (1..5; 0 or out of range: 5)
@@ -92,7 +92,12 @@ class Engine {
         s_.h_max = h_max;
     }
     // Bytes of device workspace per slot.
-    static size_t bytes_per_slot(const DeviceNet &dn, int prec);
+    // padded: the factors' rows padded against channel conflicts.
+    static size_t bytes_per_slot(const DeviceNet &dn, bool padded);
+    // Whether the slots are padded when `bytes` are there for them (with `extra`
+    // more a slot): unless only an unpadded one fits.
+    static bool padded(const DeviceNet &dn, size_t bytes, size_t extra = 0) { return bytes_per_slot(dn, true) + extra <= bytes; }
+    void set_padded(bool v) { padded_ = v; }   // before init
     // Solves every cell of io; returns an abdf_status.
     int solve(const BatchIO &io, const abdf_options &opt, hipStream_t st, std::string &err);
 
@@ -164,6 +169,7 @@ class Engine {
     int n_free_ = 0;
     int bound_ = 0;
     size_t lds_admit_ = 0;
+    bool padded_ = true;
     int grid_ = 0;                      // workgroups of the last launch
     int grid_max_ = 256, grid_fp64_max_ = 256, grid_reverse_max_ = 256;
     // kernel timers of launches not yet read back

@@ -621,9 +621,7 @@ static bool rhs_stream_shape(const DeviceNet &n, int &ku, int &gpw) {
               : (ku == 2 ? (const void *)&K<2, 2> : ku == 4 ? (const void *)&K<4, 2> : ku == 8 ? (const void *)&K<8, 2> \
                  : (const void *)&K<12, 2>))
 
-size_t lu_bytes(int NP, int prec) {
-    return size_t(NP) * lu_ld(NP) * (prec == ABDF_PREC_FP32_LU ? sizeof(float) : sizeof(double));
-}
+int lu_leading_dim(int NP) { return lu_ld(NP); }
 
 size_t dinv_bytes(int NP, int prec) {
     return prec == ABDF_PREC_FP32_LU ? lu2_dinv_elems<float>(NP) * sizeof(float)

@@ -116,7 +116,7 @@ hipError_t launch_lu_factor(const LuFactorPlan &p, int n, long long batch, doubl
                             void *scratch, hipStream_t st);
 hipError_t launch_lu_solve(int n, long long batch, const double *LU, const int32_t *perm, double *b, hipStream_t st);
 size_t dinv_bytes(int NP, int prec);
-size_t lu_bytes(int NP, int prec);
+int lu_leading_dim(int NP);
 hipError_t launch_selftest(int *bad, hipStream_t st);
 hipError_t launch_fill_i32(int32_t *v, int32_t value, int n, hipStream_t st);
 

@@ -300,7 +300,7 @@ k_reverse(Slots s, DeviceNet n, IntegrateArgs a) {
                 const double *rb = s.rb + size_t(slot) * S;
                 for (int i = thread_id(); i < NP; i += NT) b[i] = i < S ? rb[i] : 0.0;
                 __syncthreads();
-                lu_solve_left_T<double, W>(slot_lu<double>(s, slot), s.perm + size_t(slot) * NP, NP, b, z, t, Db);
+                lu_solve_left_T<double, W>(slot_lu<double>(s, slot), s.lda, s.perm + size_t(slot) * NP, NP, b, z, t, Db);
                 double *d = s.d + size_t(slot) * S;
                 for (int i = thread_id(); i < S; i += NT) d[i] = z[i];
                 __syncthreads();

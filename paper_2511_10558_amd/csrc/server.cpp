@@ -42,13 +42,14 @@ Server::~Server() {
     if (st_) (void)hipStreamDestroy(st_);
 }
 
-int Server::start(int nslots, std::string &err) {
+int Server::start(int nslots, bool padded, std::string &err) {
     HIP_TRY(hipSetDevice(device_));
     HIP_TRY(hipStreamCreateWithFlags(&st_, hipStreamNonBlocking));
     HIP_TRY(hipEventCreateWithFlags(&admit_done_, hipEventDisableTiming));
     eng_ = std::make_unique<Engine>(net_, dn_, opt_.solve.precision, opt_.solve.max_steps);
     int rc = eng_->set_options(opt_.solve, err);
     if (rc != ABDF_OK) return rc;
+    eng_->set_padded(padded);
     rc = eng_->init(nslots, err);
     if (rc != ABDF_OK) return rc;
     const size_t n = size_t(nslots), S = size_t(dn_.S);

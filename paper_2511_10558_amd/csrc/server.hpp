@@ -30,7 +30,7 @@ class Server {
     Server(const HostNetwork &net, const DeviceNet &dn, const abdf_server_options &opt, int device);
     ~Server();
     // Allocates the slot pool and starts the worker; returns an abdf_status.
-    int start(int nslots, std::string &err);
+    int start(int nslots, bool padded, std::string &err);
     int submit(const abdf_request &req, uint64_t *id, std::string &err);
     int poll(abdf_completion *out, int max, int *n_out, int timeout_ms, std::string &err);
     int cancel(uint64_t id, std::string &err);

@@ -114,3 +114,19 @@ def test_largest_network(n, fits):
         return
     _, status, _ = solve_cells(ab, g, cells, device())
     assert (status == 0).all()
+
+
+# a budget for one slot with the factors' rows unpadded (120 species: 128 doubles a
+# row; padded rows would take another 16 kB)
+@pytest.mark.parametrize("noalloc", [False, True])
+def test_budget_of_one_unpadded_slot(noalloc):
+    import paper_2511_10558_amd as ab
+    net = first_species(synth.network_for_config("net200"), 120)
+    S, R = net.n_species, net.n_reactions
+    absJ = abs(chem.stoichiometry(net)) @ abs(chem.rate_derivative(net, np.ones(R), np.ones(S)))
+    budget = 8 * (128 * 128 + 2 * 2 * 64 * 64 + R + 13 * S + absJ.nnz) + 4 * 128 + 8000
+    g = ab.Network.from_text(net.to_text())
+    cells = synth.sample_cells(net, 3, seed=8, t_end_yr=1e3)
+    x, status, _ = solve_cells(ab, g, cells, device())
+    xb, sb, _ = solve_cells(ab, g, cells, device(), hbm_budget_bytes=budget, noalloc=noalloc)
+    assert (status == 0).all() and np.array_equal(sb, status) and np.array_equal(xb, x)
