@@ -196,6 +196,8 @@ const char *abdf_network_species_name(const abdf_network *net, int32_t i);
  *   cell_status           : [n_cells] ABDF_CELL_* codes
  *   stats                 : [n_cells] counters, or NULL
  * Cells beyond the workspace budget are admitted as earlier cells finish.
+ * The cells run in launches of up to 50 ms.  Above 64 species these fill every
+ * compute unit, and work of other streams gets in when one ends.
  * Errors: ABDF_E_ARG (null pointers, n_cells < 0, rtol <= 0, atol < 0,
  * max_steps < 1, unknown precision), ABDF_E_BUDGET, ABDF_E_NOMEM, ABDF_E_DEVICE.
  */
@@ -213,7 +215,7 @@ abdf_status abdf_solve(const abdf_network *net, int64_t n_cells,
  * other allocating routine.  Its workspace is a 64 MiB device array built into
  * the library (each device the library runs on holds its own copy until the
  * process ends) and static host buffers; it holds as many slots as fit there
- * (e.g. 24 cells of the 500-species network, ~100 of the 200-species one, at
+ * (e.g. 22 cells of the 500-species network, 92 of the 200-species one, at
  * most 4096), bounded further by opt->hbm_budget_bytes, and admits further
  * cells as slots free up.
  * Requirements and limits:

@@ -122,10 +122,6 @@ Engine::~Engine() {
         else
             (void)hipFree(base_);
     }
-    if (h_q_) (void)hipHostFree(h_q_);
-    if (h_fin_) (void)hipHostFree(h_fin_);
-    if (h_admit_slots_) (void)hipHostFree(h_admit_slots_);
-    if (h_admit_cells_) (void)hipHostFree(h_admit_cells_);
 }
 
 // Factor storage per slot: FP64-sized in both forms, since an FP32-LU cell can
@@ -292,15 +288,17 @@ int Engine::init(int nslots, std::string &err, bool cache_workspace) {
         }
         base_bytes_ = total;
     }
-    free_store_.resize(n);
+    // ordinary memory: freeing pinned memory waits for every stream of the device
+    store_.resize(n);
+    free_store_.resize(3 * n);
+    h_q_ = &queue_store_;
     free_ = free_store_.data();
+    h_fin_ = free_ + n;
+    h_admit_slots_ = h_fin_ + n;
+    h_admit_cells_ = store_.data();
     int rc = layout(nslots, base_, err);
     if (rc != ABDF_OK) return rc;
     HIP_TRY(hipMemset(s_.q, 0, sizeof(SlotQueue)));
-    HIP_TRY(hipHostMalloc(reinterpret_cast<void **>(&h_q_), sizeof(SlotQueue), hipHostMallocDefault));
-    HIP_TRY(hipHostMalloc(reinterpret_cast<void **>(&h_fin_), n * sizeof(int32_t), hipHostMallocDefault));
-    HIP_TRY(hipHostMalloc(reinterpret_cast<void **>(&h_admit_slots_), n * sizeof(int32_t), hipHostMallocDefault));
-    HIP_TRY(hipHostMalloc(reinterpret_cast<void **>(&h_admit_cells_), n * sizeof(long long), hipHostMallocDefault));
     return ABDF_OK;
 }
 
@@ -370,7 +368,6 @@ int Engine::admit(const BatchIO &io, const abdf_options &opt, long long &next, h
     a.atol = opt.atol;
     a.newton_tol = newton_tolerance(opt);
     a.tc = opt.phi_tc;
-    // the pinned admission buffers are rewritten only after the next poll's synchronisation
     next += want;
     return admit_cells(a, st, err);
 }
@@ -434,9 +431,13 @@ int Engine::harvest(HarvestArgs h, hipStream_t st, std::string &err) {
 }
 
 // Longest launch of a batch solve or sweep (it returns earlier when its cells
-// are done): long enough that the workgroups' wait for the slowest at its end
-// (one attempt, up to 2 ms) is nothing.
-constexpr double kBatchLaunchMs = 500.0;
+// are done).  The eight-wave kernel fills every compute unit's registers, so work
+// of other streams and threads waits for a launch's end; at the end the
+// workgroups wait for the slowest attempt (up to 2 ms) and the host.  With 500 ms
+// a small kernel on another stream waited up to 405 ms beside a solve of 1024
+// cells of 500 species, with 50 ms up to 47; the solve takes 1 to 2% longer, one of
+// 2000 cells of 200 species 0.6% and of 16000 of 12 species 4%.
+constexpr double kBatchLaunchMs = 50.0;
 
 int Engine::solve(const BatchIO &io, const abdf_options &opt, hipStream_t st, std::string &err) {
     TraceRange tr("abdf solve");

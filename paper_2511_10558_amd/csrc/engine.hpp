@@ -156,15 +156,18 @@ class Engine {
     int layout(int nslots, void *base, std::string &err);
     int32_t *d_admit_slots_ = nullptr;
     long long *d_admit_cells_ = nullptr;
-    SlotQueue *h_q_ = nullptr;          // pinned copy of the device's queue counters
+    SlotQueue *h_q_ = nullptr;          // host copy of the device's queue counters
+    SlotQueue queue_store_{};
     unsigned long long held_seen_ = 0, ticks_seen_[kPhases] = {};
     int32_t launch_ = 0;                // launches since the counters were reset
     int32_t n64_seen_ = 0;              // SlotQueue::n64 as last read
     bool fp64_too_ = false;             // the last launch's form (IntegrateArgs::fp64_too)
-    int32_t *h_fin_ = nullptr;          // pinned [nslots]
-    int32_t *h_admit_slots_ = nullptr;  // pinned [nslots]
-    long long *h_admit_cells_ = nullptr;
-    std::vector<int32_t> free_store_;  // free-slot stack when the engine owns it
+    int32_t *h_fin_ = nullptr;          // [nslots]
+    int32_t *h_admit_slots_ = nullptr;  // [nslots]
+    long long *h_admit_cells_ = nullptr;   // [nslots]
+    // the host buffers when the engine owns them
+    std::vector<int32_t> free_store_;
+    std::vector<long long> store_;
     int32_t *free_ = nullptr;
     int n_free_ = 0;
     int bound_ = 0;
