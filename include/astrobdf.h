@@ -101,9 +101,11 @@ typedef struct abdf_options {
     double atol;               /* absolute tolerance in x units, >= 0 (default 1e-20) */
     int32_t max_steps;         /* step attempts per cell (default 100000) */
     int32_t precision;         /* ABDF_PREC_* (default FP64) */
-    int32_t check_every;       /* server: how long its cells run between looks at the queue, in
-                                * units of about 4 ms (default 8; a server's 4).  Batch calls
-                                * poll as their cells need it. */
+    int32_t check_every;       /* server: how long finished cells may wait before they are handed
+                                * out and their slots filled again, in units of 0.5 ms (some
+                                * step attempts; default 8, a server's 4).  New requests are
+                                * admitted at once while slots are free.  Batch calls poll as
+                                * their cells need it. */
     int32_t max_order;         /* highest BDF order the order selection may reach, 1..5;
                                 * 0 = 5 (default 5).  1 is the implicit Euler method
                                 * with the same error control. */

@@ -383,7 +383,12 @@ IntegrateArgs Engine::next_launch(double ms, bool stop_on_idle) {
     return a;
 }
 
-int Engine::integrate(double ms, bool stop_on_idle, hipStream_t st, std::string &err) {
+// A server's launch does not look at its call before this, so that requests in quick
+// succession do not end one launch after another at its first attempt.
+constexpr double kCallMs = 0.5;
+
+int Engine::integrate(double ms, bool stop_on_idle, hipStream_t st, std::string &err, const int32_t *call,
+                      double ms_done) {
     if (bound_ <= 0) return ABDF_OK;
     TraceRange tr("abdf integrate");
     // while cells of the one-wave FP32-LU kernel are on FP64 factors, its form that
@@ -392,6 +397,9 @@ int Engine::integrate(double ms, bool stop_on_idle, hipStream_t st, std::string 
     grid_ = std::min(bound_, fp64_too_ ? grid_fp64_max_ : grid_max_);
     IntegrateArgs a = next_launch(ms, stop_on_idle);
     a.fp64_too = fp64_too_;
+    a.call = call;
+    a.ticks_call = (unsigned long long)(kCallMs * 1e5);
+    a.ticks_done = (unsigned long long)(ms_done * 1e5);
     HIP_TRY(launch_integrate(s_, dn_, a, grid_, st));
     return ABDF_OK;
 }
@@ -430,15 +438,6 @@ int Engine::harvest(HarvestArgs h, hipStream_t st, std::string &err) {
     return ABDF_OK;
 }
 
-// Longest launch of a batch solve or sweep (it returns earlier when its cells
-// are done).  The eight-wave kernel fills every compute unit's registers, so work
-// of other streams and threads waits for a launch's end; at the end the
-// workgroups wait for the slowest attempt (up to 2 ms) and the host.  With 500 ms
-// a small kernel on another stream waited up to 405 ms beside a solve of 1024
-// cells of 500 species, with 50 ms up to 47; the solve takes 1 to 2% longer, one of
-// 2000 cells of 200 species 0.6% and of 16000 of 12 species 4%.
-constexpr double kBatchLaunchMs = 50.0;
-
 int Engine::solve(const BatchIO &io, const abdf_options &opt, hipStream_t st, std::string &err) {
     TraceRange tr("abdf solve");
     long long next = 0;
@@ -451,7 +450,7 @@ int Engine::solve(const BatchIO &io, const abdf_options &opt, hipStream_t st, st
     int rc = admit(io, opt, next, st, err);
     if (rc != ABDF_OK) return rc;
     while (bound_ > 0) {
-        rc = integrate(kBatchLaunchMs, next < io.n_cells, st, err);
+        rc = integrate(kLaunchMs, next < io.n_cells, st, err);
         if (rc != ABDF_OK) return rc;
         int nfin = 0;
         rc = sync_counts(st, nfin, err);
@@ -503,7 +502,7 @@ int Engine::reverse(const AdjIO &io, hipStream_t st, std::string &err) {
     if (rc != ABDF_OK) return rc;
     while (bound_ > 0) {
         grid_ = std::min(bound_, grid_reverse_max_);
-        HIP_TRY(launch_reverse(s_, dn_, next_launch(kBatchLaunchMs, next < io.n_cells), grid_, st));
+        HIP_TRY(launch_reverse(s_, dn_, next_launch(kLaunchMs, next < io.n_cells), grid_, st));
         int nfin = 0;
         rc = sync_counts(st, nfin, err);
         if (rc != ABDF_OK) return rc;

@@ -46,6 +46,16 @@ struct HostBuffers {
     double *atol;            // [kMaxSpecies] per-species absolute tolerances
     int max_slots;
 };
+
+// Longest launch [ms] of an integration or sweep (it returns earlier when its cells
+// are done).  The eight-wave kernel fills every compute unit's registers, so work
+// of other streams and threads waits for a launch's end; at the end the
+// workgroups wait for the slowest attempt (up to 2 ms) and the host.  With 500 ms
+// a small kernel on another stream waited up to 405 ms beside a solve of 1024
+// cells of 500 species, with 50 ms up to 47; the solve takes 1 to 2% longer, one of
+// 2000 cells of 200 species 0.6% and of 16000 of 12 species 4%.
+constexpr double kLaunchMs = 50.0;
+
 constexpr int kMaxSpecies = 512;   // the factorisation holds at most this order
 
 // Process-wide kernel timers (abdf_profile_*).
@@ -114,7 +124,10 @@ class Engine {
     int admit_cells(const AdmitArgs &a, hipStream_t st, std::string &err);
     // One launch of the integration: it ends when no slot is left to run, after
     // about `ms` milliseconds, or (stop_on_idle) when a workgroup runs idle.
-    int integrate(double ms, bool stop_on_idle, hipStream_t st, std::string &err);
+    // A server's launch (call, host memory the device reads) also ends when *call is
+    // set, and after ms_done as soon as a cell has finished.
+    int integrate(double ms, bool stop_on_idle, hipStream_t st, std::string &err, const int32_t *call = nullptr,
+                  double ms_done = 0.0);
     // Waits for the stream and reads the finished count.
     int sync_counts(hipStream_t st, int &nfin, std::string &err);
     // Copies the nfin finished slots out (h.count = nfin, h.slots = the finished

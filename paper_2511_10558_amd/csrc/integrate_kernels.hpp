@@ -48,14 +48,23 @@ struct PhaseClock {
 
 // Whether this workgroup puts its cell back and ends: the launch's time is up,
 // or (when cells wait on the host for slots, or for the form that holds FP64
-// factors) another workgroup found the queue empty.  Uniform; contains a barrier.
+// factors) another workgroup found the queue empty; a server's launch also ends
+// when the host calls or has results to hand out.  Uniform; contains a barrier.
 template <int W>
 __device__ __forceinline__ bool time_up(const Slots &s, const IntegrateArgs &a, unsigned long long t0,
                                         StepLds<W> &L) {
     if (threadIdx.x == 0) {
-        bool up = wall_clock64() - t0 > a.ticks;
+        const unsigned long long ran = wall_clock64() - t0;
+        bool up = ran > a.ticks;
         if (a.stop_on_idle || (a.defer && (L.cs.n_attempts & 7) == 0))   // not a load of every short attempt
             up |= __hip_atomic_load(&s.q->stop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == a.launch;
+        if (a.call) {
+            // host memory is some 2 us away: not every attempt (of 50 us and more, or 20 us of a wave alone)
+            if (ran > a.ticks_call && (L.cs.n_attempts & (W == 1 ? 15 : 3)) == 0)
+                up |= __hip_atomic_load(a.call, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) != 0;
+            if (ran > a.ticks_done)
+                up |= __hip_atomic_load(&s.q->nfin, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > 0;
+        }
         L.flag = up;
     }
     __syncthreads();

@@ -59,6 +59,9 @@ struct PhysArgs {
 struct IntegrateArgs {
     unsigned long long held_limit;   // slots put back by earlier launches: Slots::q->held_tail as last read
     unsigned long long ticks;        // workgroups put their cell back once this many 100 MHz ticks have passed
+    unsigned long long ticks_call;   // a server's launch, after this many: looks at *call,
+    unsigned long long ticks_done;   // after this many: ends as soon as a cell has finished
+    const int32_t *call;             // host memory, nonzero: the host has work for it (null: not a server's)
     int32_t launch;                  // number of this launch (> 0)
     int32_t stop_on_idle;            // cells wait on the host: end as soon as a workgroup finds the queue empty
     int32_t prof;                    // accumulate SlotQueue::ticks

@@ -27,6 +27,7 @@ Server::~Server() {
     {
         std::lock_guard<std::mutex> l(mu_);
         stop_ = true;
+        if (call_) call();
     }
     cv_work_.notify_all();
     if (th_.joinable()) th_.join();
@@ -34,6 +35,7 @@ Server::~Server() {
     if (st_) (void)hipStreamSynchronize(st_);
     eng_.reset();
     if (d_in_) (void)hipFree(d_in_);
+    if (call_) (void)hipHostFree(call_);
     if (h_in_) (void)hipHostFree(h_in_);
     if (h_x_) (void)hipHostFree(h_x_);
     if (h_st_) (void)hipHostFree(h_st_);
@@ -82,6 +84,8 @@ int Server::start(int nslots, bool padded, std::string &err) {
     HIP_TRY(hipHostMalloc(reinterpret_cast<void **>(&h_st_), b_st, hipHostMallocDefault));
     HIP_TRY(hipHostMalloc(reinterpret_cast<void **>(&h_stats_), b_stats, hipHostMallocDefault));
     // h_slots_ and h_cells_ live inside the h_in_ allocation
+    HIP_TRY(hipHostMalloc(reinterpret_cast<void **>(&call_), sizeof(int32_t), hipHostMallocDefault));
+    *call_ = 0;
     owner_.assign(n, {nullptr, 0});
     th_ = std::thread([this] { run(); });
     return ABDF_OK;
@@ -149,6 +153,7 @@ int Server::submit(const abdf_request &q, uint64_t *id, std::string &err) {
         }
         queued_cells_ += n;
         incoming_.push_back(std::move(r));
+        if (room_) call();
     }
     cv_work_.notify_all();
     return ABDF_OK;
@@ -184,6 +189,7 @@ int Server::cancel(uint64_t id, std::string &err) {
             return ABDF_E_ARG;
         }
         cancel_ids_.push_back(id);
+        call();
     }
     cv_work_.notify_all();
     return ABDF_OK;
@@ -356,9 +362,10 @@ void Server::run() {
     std::string err;
     int rc = hipSetDevice(device_) == hipSuccess ? ABDF_OK : ABDF_E_DEVICE;
     if (rc != ABDF_OK) err = "hipSetDevice in the server worker";
-    // how long a launch may run before the worker looks for new requests and
-    // hands out finished ones: about 4 ms per unit of check_every (default 4)
-    const double launch_ms = 4.0 * std::max(1, opt_.solve.check_every);
+    // how long finished cells may wait in a launch: 0.5 ms, some step attempts, per unit
+    // of check_every.  New requests, cancellations and the end of the server call
+    // the worker back at once.
+    const double done_ms = 0.5 * std::max(1, opt_.solve.check_every);
     t_last_ = now();
     while (rc == ABDF_OK) {
         std::vector<uint64_t> cancels;
@@ -371,6 +378,8 @@ void Server::run() {
             for (auto &r : incoming_) pending_.push_back(std::move(r));
             incoming_.clear();
             cancels.swap(cancel_ids_);
+            *static_cast<volatile int32_t *>(call_) = 0;   // no launch is running
+            room_ = false;
         }
         if (!cancels.empty()) apply_cancels(cancels);
         if (!pending_.empty() && eng_->free_count() > 0) {
@@ -378,7 +387,13 @@ void Server::run() {
             if (rc != ABDF_OK) break;
         }
         if (occupied_ > 0) {
-            rc = eng_->integrate(launch_ms, !pending_.empty(), st_, err);
+            {
+                // what has arrived since ends the launch at once
+                std::lock_guard<std::mutex> l(mu_);
+                room_ = pending_.empty() && eng_->free_count() > 0;
+                if (stop_ || !cancel_ids_.empty() || (room_ && !incoming_.empty())) call();
+            }
+            rc = eng_->integrate(kLaunchMs, !pending_.empty(), st_, err, call_, done_ms);
             if (rc != ABDF_OK) break;
             rc = collect(err);
         }

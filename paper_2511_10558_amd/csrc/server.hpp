@@ -59,6 +59,7 @@ class Server {
     int admit_pending(std::string &err);
     int collect(std::string &err);
     void complete(Request *r);
+    void call() { *static_cast<volatile int32_t *>(call_) = 1; }   // mu_ held
     void apply_cancels(const std::vector<uint64_t> &ids);
 
     const HostNetwork &net_;
@@ -77,6 +78,8 @@ class Server {
     std::vector<uint64_t> cancel_ids_;
     std::deque<abdf_completion> completed_;
     bool stop_ = false;
+    int32_t *call_ = nullptr;         // pinned; set: the running launch ends for new work (IntegrateArgs::call)
+    bool room_ = false;               // a request that arrives now can be admitted
     int error_ = ABDF_OK;
     std::string error_msg_;
     uint64_t next_id_ = 1;
