@@ -477,8 +477,10 @@ enum {
     ABDF_PROF_RHS = 5,      /* Newton residual: rates times abundances, species sums */
     ABDF_PROF_ADJ_SOLVE = 6,  /* reverse sweep: transposed triangular solves */
     ABDF_PROF_ADJ_STEP = 7,   /* reverse sweep: adjoint step update and parameter gradient */
-    ABDF_PROF_RHS_SIDE = 8,     /* unused (always zero) */
-    ABDF_PROF_NEWTON_SIDE = 9,  /* unused (always zero) */
+    /* zero since the phases of an attempt are one launch: they were the residual
+     * and the correction on a second stream beside the factorisation */
+    ABDF_PROF_RHS_SIDE = 8,
+    ABDF_PROF_NEWTON_SIDE = 9,
     ABDF_PROF_RHS_EVAL = 10,  /* abdf_rhs: the right-hand-side kernel on its own */
     ABDF_PROF_KINDS = 11
 };

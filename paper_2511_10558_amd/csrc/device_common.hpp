@@ -123,12 +123,12 @@ struct Slots {
 constexpr int32_t kWindowDone = 100;   // the window is swept; the cell continues in the next pass
 constexpr int32_t kSitsOut = 101;      // the cell has no window in this pass
 
-// The factor storage of a slot in element type T.
 // Absolute tolerance of species i in a slot's error and Newton weights.
 __device__ __forceinline__ double atol_of(const Slots &s, const SlotCtl &cs, int i) {
     return s.atol_sp ? s.atol_sp[i] : cs.atol;
 }
 
+// The factor storage of a slot in element type T.
 template <typename T>
 __device__ __forceinline__ T *slot_lu(const Slots &s, int slot) {
     return reinterpret_cast<T *>(static_cast<char *>(s.lu) + size_t(slot) * s.lu_stride);

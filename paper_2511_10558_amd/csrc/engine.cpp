@@ -3,10 +3,10 @@
 // Cells are admitted into slots and queued on the device; a launch of the
 // persistent integration kernel lets every workgroup carry one queued cell
 // after another to its end (integrate.hip).  The launch returns when the queue
-// is empty, when its time is up (the server looks for new requests, a batch
-// solve for errors), or when a workgroup runs idle while cells still wait on
-// the host for a slot; the host then reads the counts, copies finished results
-// out, and refills freed slots with pending cells.
+// is empty, when its time is up (work of other streams gets in then), when a
+// workgroup runs idle while cells still wait on the host for a slot, or, in the
+// server, for a new request or finished results; the host then reads the counts,
+// copies finished results out, and refills freed slots with pending cells.
 #include "engine.hpp"
 
 #include <atomic>

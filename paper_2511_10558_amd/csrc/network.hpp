@@ -17,10 +17,9 @@ constexpr int kRhsSegment = 32;   // right-hand-side entries summed by one lane 
 constexpr int kRhsResidentGroups = 16;   // lane groups the streaming right-hand side holds in registers
 constexpr int kRhsResidentLen = 40;      // the longest lane it holds
 
-// Device copies of the network tables (one per HIP device).
-// Terms of a Jacobian nonzero that jacobian_values sums in its first pass.
-constexpr int kJacShort = 2;
+constexpr int kJacShort = 2;      // terms of a Jacobian nonzero that jacobian_values sums in its first pass
 
+// Device copies of the network tables (one per HIP device).
 struct DeviceNet {
     int device = -1;
     int S = 0, R = 0, NP = 0;
