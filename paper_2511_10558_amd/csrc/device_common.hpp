@@ -61,6 +61,11 @@ struct SlotQueue {
     int32_t stop;                             // the last launch in which a workgroup found the queue empty
     int32_t n64;                              // one-wave FP32-LU kernel: running cells on FP64 factors
     int32_t pad;
+    // a server's launches: after ticks_call they look at *call, host memory, nonzero
+    // when the host has work for them; after ticks_done they end as soon as a cell
+    // has finished
+    const int32_t *call;
+    unsigned long long ticks_call, ticks_done;
 };
 constexpr int kQueueInts = sizeof(SlotQueue) / sizeof(int32_t);
 

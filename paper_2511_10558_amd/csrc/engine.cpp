@@ -116,12 +116,10 @@ Engine::~Engine() {
     }
     for (hipEvent_t e : event_pool_) (void)hipEventDestroy(e);
     if (ext_) return;   // nothing below was allocated
-    if (base_) {
-        if (cached_)
-            net_.keep_workspace(dn_.device, base_, base_bytes_);
-        else
-            (void)hipFree(base_);
-    }
+    if (cached_ && block_.ptr && block_.host)
+        net_.keep_workspace(dn_.device, block_);
+    else
+        block_.free();
 }
 
 // Factor storage per slot: FP64-sized in both forms, since an FP32-LU cell can
@@ -278,28 +276,28 @@ int Engine::init(int nslots, std::string &err, bool cache_workspace) {
     const size_t n = size_t(nslots);
     const size_t total = workspace_bytes(dn_, nslots, padded_);
     cached_ = cache_workspace;
-    base_ = cached_ ? net_.take_workspace(dn_.device, total, &base_bytes_) : nullptr;
-    if (!base_) {
-        hipError_t e = hipMalloc(&base_, total);
+    // pinned: the queue's counts, cells to admit, slots to admit, finished slots
+    // (copies to and from ordinary memory hold up other threads' calls)
+    const size_t host_total = sizeof(SlotQueue) + n * (sizeof(long long) + 2 * sizeof(int32_t));
+    if (cached_) block_ = net_.take_workspace(dn_.device, total, host_total);
+    if (!block_.ptr) {
+        hipError_t e = hipMalloc(&block_.ptr, total);
         if (e != hipSuccess) {
-            base_ = nullptr;
+            block_.ptr = nullptr;
             err = "device workspace of " + std::to_string(total) + " bytes: " + hipGetErrorString(e);
             return ABDF_E_NOMEM;
         }
-        base_bytes_ = total;
+        block_.bytes = total;
+        HIP_TRY(hipHostMalloc(&block_.host, host_total, hipHostMallocDefault));
+        block_.host_bytes = host_total;
     }
-    // ordinary memory: freeing pinned memory waits for every stream of the device
-    store_.resize(n);
-    free_store_.resize(3 * n);
-    h_q_ = &queue_store_;
+    h_q_ = static_cast<SlotQueue *>(block_.host);
+    h_admit_cells_ = reinterpret_cast<long long *>(h_q_ + 1);
+    h_admit_slots_ = reinterpret_cast<int32_t *>(h_admit_cells_ + n);
+    h_fin_ = h_admit_slots_ + n;
+    free_store_.resize(n);
     free_ = free_store_.data();
-    h_fin_ = free_ + n;
-    h_admit_slots_ = h_fin_ + n;
-    h_admit_cells_ = store_.data();
-    int rc = layout(nslots, base_, err);
-    if (rc != ABDF_OK) return rc;
-    HIP_TRY(hipMemset(s_.q, 0, sizeof(SlotQueue)));
-    return ABDF_OK;
+    return layout(nslots, block_.ptr, err);
 }
 
 int Engine::init_external(int nslots, void *base, size_t bytes, const HostBuffers &hb, std::string &err) {
@@ -308,8 +306,6 @@ int Engine::init_external(int nslots, void *base, size_t bytes, const HostBuffer
         err = "slot count beyond the external workspace";
         return ABDF_E_ARG;
     }
-    base_ = base;
-    base_bytes_ = bytes;
     free_ = hb.free_list;
     h_q_ = hb.queue;
     h_fin_ = hb.fin;
@@ -368,18 +364,20 @@ int Engine::admit(const BatchIO &io, const abdf_options &opt, long long &next, h
     a.atol = opt.atol;
     a.newton_tol = newton_tolerance(opt);
     a.tc = opt.phi_tc;
+    // the admission buffers are rewritten only after the next poll's synchronisation
     next += want;
     return admit_cells(a, st, err);
 }
 
 // One launch of a persistent kernel over the occupied slots.
-IntegrateArgs Engine::next_launch(double ms, bool stop_on_idle) {
+IntegrateArgs Engine::next_launch(bool stop_on_idle) {
     IntegrateArgs a{};
     a.held_limit = held_seen_;
-    a.ticks = (unsigned long long)(ms * 1e5);   // the device's constant clock: 100 MHz
+    a.ticks = (unsigned long long)(kLaunchMs * 1e5);   // the device's constant clock: 100 MHz
     a.launch = ++launch_;
-    a.stop_on_idle = stop_on_idle;
-    a.prof = !ext_ && Profiler::on();
+    if (stop_on_idle) a.flags |= kStopOnIdle;
+    if (!ext_ && Profiler::on()) a.flags |= kProf;
+    if (serve_) a.flags |= kServe;
     return a;
 }
 
@@ -387,20 +385,28 @@ IntegrateArgs Engine::next_launch(double ms, bool stop_on_idle) {
 // succession do not end one launch after another at its first attempt.
 constexpr double kCallMs = 0.5;
 
-int Engine::integrate(double ms, bool stop_on_idle, hipStream_t st, std::string &err, const int32_t *call,
-                      double ms_done) {
+int Engine::serve(const int32_t *call, double ms_done, hipStream_t st, std::string &err) {
+    int rc = reset_counts(st, err);
+    if (rc != ABDF_OK) return rc;
+    SlotQueue q{};
+    q.call = call;
+    q.ticks_call = (unsigned long long)(kCallMs * 1e5);
+    q.ticks_done = (unsigned long long)(ms_done * 1e5);
+    *h_q_ = q;
+    HIP_TRY(hipMemcpyAsync(s_.q, h_q_, sizeof(SlotQueue), hipMemcpyHostToDevice, st));
+    HIP_TRY(hipStreamSynchronize(st));
+    serve_ = true;
+    return ABDF_OK;
+}
+
+int Engine::integrate(bool stop_on_idle, hipStream_t st, std::string &err) {
     if (bound_ <= 0) return ABDF_OK;
     TraceRange tr("abdf integrate");
     // while cells of the one-wave FP32-LU kernel are on FP64 factors, its form that
     // holds those runs in every other launch (all cells advance in it, fewer at once)
     fp64_too_ = n64_seen_ > 0 && !fp64_too_;
     grid_ = std::min(bound_, fp64_too_ ? grid_fp64_max_ : grid_max_);
-    IntegrateArgs a = next_launch(ms, stop_on_idle);
-    a.fp64_too = fp64_too_;
-    a.call = call;
-    a.ticks_call = (unsigned long long)(kCallMs * 1e5);
-    a.ticks_done = (unsigned long long)(ms_done * 1e5);
-    HIP_TRY(launch_integrate(s_, dn_, a, grid_, st));
+    HIP_TRY(launch_integrate(s_, dn_, next_launch(stop_on_idle), fp64_too_, grid_, st));
     return ABDF_OK;
 }
 
@@ -450,7 +456,7 @@ int Engine::solve(const BatchIO &io, const abdf_options &opt, hipStream_t st, st
     int rc = admit(io, opt, next, st, err);
     if (rc != ABDF_OK) return rc;
     while (bound_ > 0) {
-        rc = integrate(kLaunchMs, next < io.n_cells, st, err);
+        rc = integrate(next < io.n_cells, st, err);
         if (rc != ABDF_OK) return rc;
         int nfin = 0;
         rc = sync_counts(st, nfin, err);
@@ -502,7 +508,7 @@ int Engine::reverse(const AdjIO &io, hipStream_t st, std::string &err) {
     if (rc != ABDF_OK) return rc;
     while (bound_ > 0) {
         grid_ = std::min(bound_, grid_reverse_max_);
-        HIP_TRY(launch_reverse(s_, dn_, next_launch(kLaunchMs, next < io.n_cells), grid_, st));
+        HIP_TRY(launch_reverse(s_, dn_, next_launch(next < io.n_cells), grid_, st));
         int nfin = 0;
         rc = sync_counts(st, nfin, err);
         if (rc != ABDF_OK) return rc;

@@ -48,12 +48,13 @@ struct HostBuffers {
 };
 
 // Longest launch [ms] of an integration or sweep (it returns earlier when its cells
-// are done).  The eight-wave kernel fills every compute unit's registers, so work
-// of other streams and threads waits for a launch's end; at the end the
-// workgroups wait for the slowest attempt (up to 2 ms) and the host.  With 500 ms
-// a small kernel on another stream waited up to 405 ms beside a solve of 1024
-// cells of 500 species, with 50 ms up to 47; the solve takes 1 to 2% longer, one of
-// 2000 cells of 200 species 0.6% and of 16000 of 12 species 4%.
+// are done).  Work of other streams and threads waits for a launch's end where the
+// eight-wave kernel takes all registers of (nearly) every compute unit, and where
+// its stream shares the hardware queue: beside 1024 cells of 500 species a small
+// kernel on another stream waited up to 405 ms in launches of 500 ms, and 47 in
+// launches of 50.  At a launch's end the workgroups wait for the slowest attempt (up
+// to 2 ms) and the host: the solve of 500 species takes 1 to 2% longer, 2000
+// cells of 200 species 0.6%, 16000 of 12 species 2%.
 constexpr double kLaunchMs = 50.0;
 
 constexpr int kMaxSpecies = 512;   // the factorisation holds at most this order
@@ -115,6 +116,9 @@ class Engine {
     int reverse(const AdjIO &io, hipStream_t st, std::string &err);
 
     // Building blocks of a driver loop (batch solve, server, adjoint).
+    // Empties the queue; from here on launches also end when *call (host memory the
+    // device reads) is set, and after ms_done as soon as a cell has finished.
+    int serve(const int32_t *call, double ms_done, hipStream_t st, std::string &err);
     int nslots() const { return s_.nslots; }
     int free_count() const { return n_free_; }
     // Occupied slots: admitted and not yet harvested.
@@ -123,11 +127,8 @@ class Engine {
     // Admits a.count cells into the slots a.slots (taken with take_slot).
     int admit_cells(const AdmitArgs &a, hipStream_t st, std::string &err);
     // One launch of the integration: it ends when no slot is left to run, after
-    // about `ms` milliseconds, or (stop_on_idle) when a workgroup runs idle.
-    // A server's launch (call, host memory the device reads) also ends when *call is
-    // set, and after ms_done as soon as a cell has finished.
-    int integrate(double ms, bool stop_on_idle, hipStream_t st, std::string &err, const int32_t *call = nullptr,
-                  double ms_done = 0.0);
+    // kLaunchMs, or (stop_on_idle) when a workgroup runs idle.
+    int integrate(bool stop_on_idle, hipStream_t st, std::string &err);
     // Waits for the stream and reads the finished count.
     int sync_counts(hipStream_t st, int &nfin, std::string &err);
     // Copies the nfin finished slots out (h.count = nfin, h.slots = the finished
@@ -147,7 +148,7 @@ class Engine {
 
   private:
     int admit(const BatchIO &io, const abdf_options &opt, long long &next, hipStream_t st, std::string &err);
-    IntegrateArgs next_launch(double ms, bool stop_on_idle);
+    IntegrateArgs next_launch(bool stop_on_idle);
 
     const HostNetwork &net_;
     const DeviceNet &dn_;
@@ -163,24 +164,21 @@ class Engine {
     Slots s_{};
     bool ext_ = false;                 // workspace and host buffers belong to the caller
     bool cached_ = false;              // the workspace goes back to the network's cache
-    void *base_ = nullptr;
-    size_t base_bytes_ = 0;
+    HostNetwork::Block block_;
+    bool serve_ = false;
     int reset_counts(hipStream_t st, std::string &err);
     int layout(int nslots, void *base, std::string &err);
     int32_t *d_admit_slots_ = nullptr;
     long long *d_admit_cells_ = nullptr;
-    SlotQueue *h_q_ = nullptr;          // host copy of the device's queue counters
-    SlotQueue queue_store_{};
+    SlotQueue *h_q_ = nullptr;          // pinned copy of the device's queue counters
     unsigned long long held_seen_ = 0, ticks_seen_[kPhases] = {};
     int32_t launch_ = 0;                // launches since the counters were reset
     int32_t n64_seen_ = 0;              // SlotQueue::n64 as last read
-    bool fp64_too_ = false;             // the last launch's form (IntegrateArgs::fp64_too)
-    int32_t *h_fin_ = nullptr;          // [nslots]
-    int32_t *h_admit_slots_ = nullptr;  // [nslots]
-    long long *h_admit_cells_ = nullptr;   // [nslots]
-    // the host buffers when the engine owns them
-    std::vector<int32_t> free_store_;
-    std::vector<long long> store_;
+    bool fp64_too_ = false;             // the last launch's form (launch_integrate)
+    int32_t *h_fin_ = nullptr;          // pinned [nslots]
+    int32_t *h_admit_slots_ = nullptr;  // pinned [nslots]
+    long long *h_admit_cells_ = nullptr;
+    std::vector<int32_t> free_store_;  // free-slot stack when the engine owns it
     int32_t *free_ = nullptr;
     int n_free_ = 0;
     int bound_ = 0;

@@ -47,13 +47,14 @@ static hipError_t launch_persistent(const Persistent &p, const Slots &s, const D
     Slots ss = s;
     DeviceNet nn = n;
     IntegrateArgs aa = a;
-    aa.defer = p.defers;
+    if (p.defers) aa.flags |= kDefer;
     void *args[] = {&ss, &nn, &aa};
     return hipLaunchKernel(p.fn, dim3(unsigned(grid)), dim3(p.threads), args, p.lds, st);
 }
 
-hipError_t launch_integrate(const Slots &s, const DeviceNet &n, const IntegrateArgs &a, int grid, hipStream_t st) {
-    return launch_persistent(integrate_kernel(n, s.prec, a.fp64_too), s, n, a, grid, st);
+hipError_t launch_integrate(const Slots &s, const DeviceNet &n, const IntegrateArgs &a, bool fp64_too, int grid,
+                            hipStream_t st) {
+    return launch_persistent(integrate_kernel(n, s.prec, fp64_too), s, n, a, grid, st);
 }
 
 hipError_t launch_reverse(const Slots &s, const DeviceNet &n, const IntegrateArgs &a, int grid, hipStream_t st) {

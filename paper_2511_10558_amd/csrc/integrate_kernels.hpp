@@ -13,7 +13,7 @@ struct Persistent {
     int threads;
     size_t lds;            // dynamic
     size_t fixed;          // static
-    bool defers = false;   // puts cells on FP64 factors back (IntegrateArgs::defer)
+    bool defers = false;   // puts cells on FP64 factors back (kDefer)
     size_t total() const { return lds + fixed; }
 };
 
@@ -56,13 +56,13 @@ __device__ __forceinline__ bool time_up(const Slots &s, const IntegrateArgs &a, 
     if (threadIdx.x == 0) {
         const unsigned long long ran = wall_clock64() - t0;
         bool up = ran > a.ticks;
-        if (a.stop_on_idle || (a.defer && (L.cs.n_attempts & 7) == 0))   // not a load of every short attempt
+        if ((a.flags & kStopOnIdle) || ((a.flags & kDefer) && (L.cs.n_attempts & 7) == 0))   // not a load of every short attempt
             up |= __hip_atomic_load(&s.q->stop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == a.launch;
-        if (a.call) {
+        if (a.flags & kServe) {
             // host memory is some 2 us away: not every attempt (of 50 us and more, or 20 us of a wave alone)
-            if (ran > a.ticks_call && (L.cs.n_attempts & (W == 1 ? 15 : 3)) == 0)
-                up |= __hip_atomic_load(a.call, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) != 0;
-            if (ran > a.ticks_done)
+            if (ran > s.q->ticks_call && (L.cs.n_attempts & (W == 1 ? 15 : 3)) == 0)
+                up |= __hip_atomic_load(s.q->call, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) != 0;
+            if (ran > s.q->ticks_done)
                 up |= __hip_atomic_load(&s.q->nfin, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > 0;
         }
         L.flag = up;
@@ -80,8 +80,8 @@ __device__ __forceinline__ int take_slot(const Slots &s, const IntegrateArgs &a,
         L.slot = slot;
         if (slot >= 0)
             L.cs = s.ctl[slot];
-        else if (a.stop_on_idle ||
-                 (a.defer && __hip_atomic_load(&s.q->n64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > 0))
+        else if ((a.flags & kStopOnIdle) ||
+                 ((a.flags & kDefer) && __hip_atomic_load(&s.q->n64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > 0))
             __hip_atomic_store(&s.q->stop, a.launch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();
@@ -100,7 +100,7 @@ k_integrate(Slots s, DeviceNet n, IntegrateArgs a) {
     const unsigned long long t0 = wall_clock64();
     if (threadIdx.x < kPhases) t_phase[threadIdx.x] = 0;
     const bool rk = s.method == ABDF_METHOD_ESDIRK5;
-    PhaseClock clk{a.prof && threadIdx.x == 0, 0};
+    PhaseClock clk{(a.flags & kProf) && threadIdx.x == 0, 0};
     while (true) {
         const int slot = take_slot<W>(s, a, L);
         if (slot < 0) break;
@@ -153,7 +153,7 @@ k_integrate(Slots s, DeviceNet n, IntegrateArgs a) {
         if (up) break;
     }
     __syncthreads();
-    if (a.prof && threadIdx.x < kPhases)
+    if ((a.flags & kProf) && threadIdx.x < kPhases)
         atomicAdd(&s.q->ticks[threadIdx.x],
                   t_phase[threadIdx.x] - (threadIdx.x == kPhaseNewton ? t_phase[kPhaseRhs] : 0ull));
 }

@@ -21,13 +21,13 @@ __global__ void __launch_bounds__(64) k_integrate_tiny(Slots s, DeviceNet n, Int
     const unsigned long long t0 = wall_clock64();
     if (threadIdx.x < kPhases) t_phase[threadIdx.x] = 0;
     const bool rk = s.method == ABDF_METHOD_ESDIRK5;
-    PhaseClock clk{a.prof && threadIdx.x == 0, 0};
-    constexpr bool kF32 = sizeof(T) == sizeof(float), kDefer = kF32 && !kFp64Too;
+    PhaseClock clk{(a.flags & kProf) && threadIdx.x == 0, 0};
+    constexpr bool kF32 = sizeof(T) == sizeof(float), kPutBack = kF32 && !kFp64Too;
     TinyCell<T, kTiles, kFp64Too> cell(n, reinterpret_cast<unsigned char *>(smem));
     while (true) {
         const int slot = take_slot<1>(s, a, L);
         if (slot < 0) break;
-        if (kDefer && L.cs.lu_mode == kLu64) {
+        if (kPutBack && L.cs.lu_mode == kLu64) {
             if (threadIdx.x == 0) hold_slot(s, slot);
             continue;
         }
@@ -79,7 +79,7 @@ __global__ void __launch_bounds__(64) k_integrate_tiny(Slots s, DeviceNet n, Int
                 control_bdf<1>(s, slot, L, y, phase, nullptr);
             if (kF32 && L.cs.lu_mode == kLu64 && mode != kLu64) {
                 if (threadIdx.x == 0) atomicAdd(&s.q->n64, 1);
-                put_back = kDefer;
+                put_back = kPutBack;
             }
             if (L.cs.status != kRunning) break;
             up = time_up<1>(s, a, t0, L);
@@ -100,7 +100,7 @@ __global__ void __launch_bounds__(64) k_integrate_tiny(Slots s, DeviceNet n, Int
         if (up) break;
     }
     __syncthreads();
-    if (a.prof && threadIdx.x < kPhases)
+    if ((a.flags & kProf) && threadIdx.x < kPhases)
         atomicAdd(&s.q->ticks[threadIdx.x],
                   t_phase[threadIdx.x] - (threadIdx.x == kPhaseNewton ? t_phase[kPhaseRhs] : 0ull));
 }

@@ -55,18 +55,20 @@ struct PhysArgs {
     const double *T, *nH, *Av, *zeta, *G0;
 };
 
-// One launch of the persistent integration (or reverse sweep).
+// One launch of the persistent integration (or reverse sweep).  (Short: with 32
+// bytes more of arguments, in scalar registers for the whole kernel, the FP32-LU
+// solves took 9% longer.)
 struct IntegrateArgs {
     unsigned long long held_limit;   // slots put back by earlier launches: Slots::q->held_tail as last read
     unsigned long long ticks;        // workgroups put their cell back once this many 100 MHz ticks have passed
-    unsigned long long ticks_call;   // a server's launch, after this many: looks at *call,
-    unsigned long long ticks_done;   // after this many: ends as soon as a cell has finished
-    const int32_t *call;             // host memory, nonzero: the host has work for it (null: not a server's)
     int32_t launch;                  // number of this launch (> 0)
-    int32_t stop_on_idle;            // cells wait on the host: end as soon as a workgroup finds the queue empty
-    int32_t prof;                    // accumulate SlotQueue::ticks
-    int32_t fp64_too;                // one-wave FP32-LU kernel: the form that also holds FP64 factors
-    int32_t defer;                   // (set by the launcher) the form that does not: it puts cells on FP64 factors back
+    int32_t flags;
+};
+enum {
+    kStopOnIdle = 1,   // cells wait on the host: end as soon as a workgroup finds the queue empty
+    kProf = 2,         // accumulate SlotQueue::ticks
+    kServe = 4,        // a server's: end for SlotQueue::call and for finished cells too
+    kDefer = 8         // (set by the launcher) the one-wave FP32-LU form that puts cells on FP64 factors back
 };
 
 // LDS bytes per kernel for a network (the persistent kernels': with their static LDS)
@@ -77,7 +79,9 @@ size_t reverse_lds(const DeviceNet &n);
 
 hipError_t launch_admit(const Slots &s, const DeviceNet &n, const AdmitArgs &a, size_t lds, hipStream_t st);
 // Integrates (sweeps) the queued slots with grid workgroups.
-hipError_t launch_integrate(const Slots &s, const DeviceNet &n, const IntegrateArgs &a, int grid, hipStream_t st);
+// fp64_too: the one-wave FP32-LU kernel in the form that also holds FP64 factors.
+hipError_t launch_integrate(const Slots &s, const DeviceNet &n, const IntegrateArgs &a, bool fp64_too, int grid,
+                            hipStream_t st);
 hipError_t launch_reverse(const Slots &s, const DeviceNet &n, const IntegrateArgs &a, int grid, hipStream_t st);
 // Their workgroups resident per CU (0: none fits).
 int integrate_resident_per_cu(const DeviceNet &n, int prec, bool fp64_too);

@@ -123,7 +123,7 @@ HostNetwork::~HostNetwork() {
         if (!spare[i].ptr) continue;
         int prev = 0;
         if (hipGetDevice(&prev) == hipSuccess && hipSetDevice(int(i)) == hipSuccess) {
-            (void)hipFree(spare[i].ptr);
+            spare[i].free();
             (void)hipSetDevice(prev);
         }
     }
@@ -434,41 +434,33 @@ const DeviceNet *HostNetwork::device_tables_present(int devid) const {
     return devid >= 0 && devid < int(dev.size()) ? dev[devid] : nullptr;
 }
 
-void *HostNetwork::take_workspace(int devid, size_t bytes, size_t *got) const {
-    void *drop = nullptr, *p = nullptr;
-    {
-        std::lock_guard<std::mutex> lock(mu);
-        if (devid < 0 || devid >= int(spare.size()) || !spare[devid].ptr) return nullptr;
-        if (spare[devid].bytes >= bytes) {
-            p = spare[devid].ptr;
-            *got = spare[devid].bytes;
-        } else {
-            drop = spare[devid].ptr;   // too small: released, so that a larger one can be allocated
-        }
-        spare[devid] = Block{};
-    }
-    if (drop) (void)hipFree(drop);
-    return p;
+void HostNetwork::Block::free() {
+    if (ptr) (void)hipFree(ptr);
+    if (host) (void)hipHostFree(host);
+    *this = Block{};
 }
 
-void HostNetwork::keep_workspace(int devid, void *ptr, size_t bytes) const {
-    void *drop = nullptr;
+HostNetwork::Block HostNetwork::take_workspace(int devid, size_t bytes, size_t host_bytes) const {
+    Block b;
     {
         std::lock_guard<std::mutex> lock(mu);
-        if (devid < 0) {
-            drop = ptr;
-        } else {
+        if (devid < 0 || devid >= int(spare.size())) return b;
+        b = spare[devid];
+        spare[devid] = Block{};
+    }
+    if (b.bytes < bytes || b.host_bytes < host_bytes) b.free();   // so that a larger one can be allocated
+    return b;
+}
+
+void HostNetwork::keep_workspace(int devid, Block b) const {
+    {
+        std::lock_guard<std::mutex> lock(mu);
+        if (devid >= 0) {
             if (int(spare.size()) <= devid) spare.resize(devid + 1);
-            Block &b = spare[devid];
-            if (bytes > b.bytes) {
-                drop = b.ptr;
-                b = Block{ptr, bytes};
-            } else {
-                drop = ptr;
-            }
+            if (b.bytes > spare[devid].bytes) std::swap(b, spare[devid]);
         }
     }
-    if (drop) (void)hipFree(drop);
+    b.free();
 }
 
 size_t HostNetwork::cached_workspace_bytes(int devid) const {

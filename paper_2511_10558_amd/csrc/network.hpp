@@ -102,8 +102,16 @@ struct HostNetwork {
     // per-device uploads, created on first use
     mutable std::mutex mu;
     mutable std::vector<DeviceNet *> dev;
-    // one solver workspace per device kept between calls (the largest returned)
-    struct Block { void *ptr = nullptr; size_t bytes = 0; };
+    // one solver workspace per device kept between calls (the largest returned),
+    // with its pinned host buffers: freeing either waits for every stream of the
+    // device, and a call that did so waited out other threads' solves
+    struct Block {
+        void *ptr = nullptr;
+        size_t bytes = 0;
+        void *host = nullptr;
+        size_t host_bytes = 0;
+        void free();
+    };
     mutable std::vector<Block> spare;
 
     ~HostNetwork();
@@ -115,12 +123,12 @@ struct HostNetwork {
     const DeviceNet *device_tables(std::string &err) const;
     // The tables of device devid if already uploaded, else nullptr (uploads nothing).
     const DeviceNet *device_tables_present(int devid) const;
-    // A cached workspace of at least `bytes` on device devid (removed from the
-    // cache; its size in *got), or nullptr (a smaller cached one is freed).
-    void *take_workspace(int devid, size_t bytes, size_t *got) const;
+    // The cached workspace of device devid (removed from the cache) if it has at
+    // least these bytes, else an empty one (a smaller cached one is freed).
+    Block take_workspace(int devid, size_t bytes, size_t host_bytes) const;
     // Returns a workspace to the cache, which keeps the larger of it and the
     // one it holds and frees the other.
-    void keep_workspace(int devid, void *ptr, size_t bytes) const;
+    void keep_workspace(int devid, Block b) const;
     // Bytes cached on device devid.
     size_t cached_workspace_bytes(int devid) const;
 };

@@ -276,7 +276,7 @@ k_reverse(Slots s, DeviceNet n, IntegrateArgs a) {
     __shared__ unsigned long long t_phase[kPhases];
     const unsigned long long t0 = wall_clock64();
     if (threadIdx.x < kPhases) t_phase[threadIdx.x] = 0;
-    PhaseClock clk{a.prof && threadIdx.x == 0, 0};
+    PhaseClock clk{(a.flags & kProf) && threadIdx.x == 0, 0};
     const int S = s.S, R = n.R, NP = s.NP;
     while (true) {
         const int slot = take_slot<W>(s, a, L);
@@ -335,7 +335,7 @@ k_reverse(Slots s, DeviceNet n, IntegrateArgs a) {
         clk.stop(&t_phase[kPhaseAdjStep]);
     }
     __syncthreads();
-    if (a.prof && threadIdx.x < kPhases) atomicAdd(&s.q->ticks[threadIdx.x], t_phase[threadIdx.x]);
+    if ((a.flags & kProf) && threadIdx.x < kPhases) atomicAdd(&s.q->ticks[threadIdx.x], t_phase[threadIdx.x]);
 }
 
 Persistent reverse_kernel(const DeviceNet &n) {

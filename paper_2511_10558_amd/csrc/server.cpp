@@ -86,6 +86,11 @@ int Server::start(int nslots, bool padded, std::string &err) {
     // h_slots_ and h_cells_ live inside the h_in_ allocation
     HIP_TRY(hipHostMalloc(reinterpret_cast<void **>(&call_), sizeof(int32_t), hipHostMallocDefault));
     *call_ = 0;
+    // how long finished cells may wait in a launch: 0.5 ms, some step attempts, per unit
+    // of check_every.  New requests, cancellations and the end of the server call
+    // the worker back at once.
+    rc = eng_->serve(call_, 0.5 * std::max(1, opt_.solve.check_every), st_, err);
+    if (rc != ABDF_OK) return rc;
     owner_.assign(n, {nullptr, 0});
     th_ = std::thread([this] { run(); });
     return ABDF_OK;
@@ -362,10 +367,6 @@ void Server::run() {
     std::string err;
     int rc = hipSetDevice(device_) == hipSuccess ? ABDF_OK : ABDF_E_DEVICE;
     if (rc != ABDF_OK) err = "hipSetDevice in the server worker";
-    // how long finished cells may wait in a launch: 0.5 ms, some step attempts, per unit
-    // of check_every.  New requests, cancellations and the end of the server call
-    // the worker back at once.
-    const double done_ms = 0.5 * std::max(1, opt_.solve.check_every);
     t_last_ = now();
     while (rc == ABDF_OK) {
         std::vector<uint64_t> cancels;
@@ -393,7 +394,7 @@ void Server::run() {
                 room_ = pending_.empty() && eng_->free_count() > 0;
                 if (stop_ || !cancel_ids_.empty() || (room_ && !incoming_.empty())) call();
             }
-            rc = eng_->integrate(kLaunchMs, !pending_.empty(), st_, err, call_, done_ms);
+            rc = eng_->integrate(!pending_.empty(), st_, err);
             if (rc != ABDF_OK) break;
             rc = collect(err);
         }

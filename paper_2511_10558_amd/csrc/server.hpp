@@ -78,7 +78,7 @@ class Server {
     std::vector<uint64_t> cancel_ids_;
     std::deque<abdf_completion> completed_;
     bool stop_ = false;
-    int32_t *call_ = nullptr;         // pinned; set: the running launch ends for new work (IntegrateArgs::call)
+    int32_t *call_ = nullptr;         // pinned; set: the running launch ends for new work (SlotQueue::call)
     bool room_ = false;               // a request that arrives now can be admitted
     int error_ = ABDF_OK;
     std::string error_msg_;
