@@ -198,7 +198,7 @@ const char *abdf_network_species_name(const abdf_network *net, int32_t i);
  *   cell_status           : [n_cells] ABDF_CELL_* codes
  *   stats                 : [n_cells] counters, or NULL
  * Cells beyond the workspace budget are admitted as earlier cells finish.
- * The cells run in launches of up to 50 ms.  Above 64 species these fill every
+ * The cells run in launches of up to 100 ms.  Above 64 species these fill every
  * compute unit, and work of other streams gets in when one ends.
  * Errors: ABDF_E_ARG (null pointers, n_cells < 0, rtol <= 0, atol < 0,
  * max_steps < 1, unknown precision), ABDF_E_BUDGET, ABDF_E_NOMEM, ABDF_E_DEVICE.

@@ -51,11 +51,12 @@ struct HostBuffers {
 // are done).  Work of other streams and threads waits for a launch's end where the
 // eight-wave kernel takes all registers of (nearly) every compute unit, and where
 // its stream shares the hardware queue: beside 1024 cells of 500 species a small
-// kernel on another stream waited up to 405 ms in launches of 500 ms, and 47 in
-// launches of 50.  At a launch's end the workgroups wait for the slowest attempt (up
-// to 2 ms) and the host: the solve of 500 species takes 1 to 2% longer, 2000
-// cells of 200 species 0.6%, 16000 of 12 species 2%.
-constexpr double kLaunchMs = 50.0;
+// kernel on another stream waited up to 405 ms in launches of 500 ms, 97 in
+// launches of 100 and 47 of 50.  At a launch's end the workgroups wait for the
+// slowest attempt (up to 2 ms) and the host: against 500 ms, launches of 100 (50)
+// cost 4096 cells of 500 species 1.0% (2.3%), 2000 of 200 species 0.3% (1%) and
+// 16000 of 12 species 1.5% (2%).
+constexpr double kLaunchMs = 100.0;
 
 constexpr int kMaxSpecies = 512;   // the factorisation holds at most this order
 

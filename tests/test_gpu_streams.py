@@ -17,9 +17,9 @@ def _args(net, n, dev, **kw):
 
 
 def test_other_streams_get_in_between():
-    # A solve that fills the device for some 0.8 s, in launches of 50 ms: a small
+    # A solve that fills the device for some 0.8 s, in launches of 100 ms: a small
     # kernel waits for the end of one, a small solve (10 ms alone, two
-    # synchronisations) of two or three.  The bounds leave four times that.
+    # synchronisations) of two or three.  The bounds leave twice that.
     import torch
     import paper_2511_10558_amd as ab
     dev = device()
