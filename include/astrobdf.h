@@ -101,11 +101,10 @@ typedef struct abdf_options {
     double atol;               /* absolute tolerance in x units, >= 0 (default 1e-20) */
     int32_t max_steps;         /* step attempts per cell (default 100000) */
     int32_t precision;         /* ABDF_PREC_* (default FP64) */
-    int32_t check_every;       /* server: how long finished cells may wait before they are handed
-                                * out and their slots filled again, in units of 0.5 ms (some
-                                * step attempts; default 8, a server's 4).  New requests are
-                                * admitted at once while slots are free.  Batch calls poll as
-                                * their cells need it. */
+    int32_t check_every;       /* server: least time its cells run before a request that is complete
+                                * is handed out, in units of 0.5 ms (some step attempts; default 8,
+                                * a server's 4).  New requests are admitted at once while slots
+                                * are free.  Batch calls poll as their cells need it. */
     int32_t max_order;         /* highest BDF order the order selection may reach, 1..5;
                                 * 0 = 5 (default 5).  1 is the implicit Euler method
                                 * with the same error control. */

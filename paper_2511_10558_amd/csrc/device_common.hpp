@@ -62,10 +62,10 @@ struct SlotQueue {
     int32_t n64;                              // one-wave FP32-LU kernel: running cells on FP64 factors
     int32_t pad;
     // a server's launches: after ticks_call they look at *call, host memory, nonzero
-    // when the host has work for them; after ticks_done they end as soon as a cell
-    // has finished
+    // when they should end; a finished slot also goes to fin_host, host memory
     const int32_t *call;
-    unsigned long long ticks_call, ticks_done;
+    int32_t *fin_host;
+    unsigned long long ticks_call;
 };
 constexpr int kQueueInts = sizeof(SlotQueue) / sizeof(int32_t);
 

@@ -83,6 +83,8 @@ __device__ inline void finish_slot(const Slots &s, int slot, SlotCtl &cs, int st
         cs.status = status;
         const int p = atomicAdd(&s.q->nfin, 1);
         s.fin[p] = slot;
+        if (int32_t *host = s.q->fin_host)
+            __hip_atomic_store(host + p, slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
 

@@ -5,7 +5,7 @@
 // after another to its end (integrate.hip).  The launch returns when the queue
 // is empty, when its time is up (work of other streams gets in then), when a
 // workgroup runs idle while cells still wait on the host for a slot, or, in the
-// server, for a new request or finished results; the host then reads the counts,
+// server, for a new or a completed request; the host then reads the counts,
 // copies finished results out, and refills freed slots with pending cells.
 #include "engine.hpp"
 
@@ -385,13 +385,13 @@ IntegrateArgs Engine::next_launch(bool stop_on_idle) {
 // succession do not end one launch after another at its first attempt.
 constexpr double kCallMs = 0.5;
 
-int Engine::serve(const int32_t *call, double ms_done, hipStream_t st, std::string &err) {
+int Engine::serve(const int32_t *call, int32_t *fin_host, hipStream_t st, std::string &err) {
     int rc = reset_counts(st, err);
     if (rc != ABDF_OK) return rc;
     SlotQueue q{};
     q.call = call;
     q.ticks_call = (unsigned long long)(kCallMs * 1e5);
-    q.ticks_done = (unsigned long long)(ms_done * 1e5);
+    q.fin_host = fin_host;
     *h_q_ = q;
     HIP_TRY(hipMemcpyAsync(s_.q, h_q_, sizeof(SlotQueue), hipMemcpyHostToDevice, st));
     HIP_TRY(hipStreamSynchronize(st));

@@ -117,9 +117,10 @@ class Engine {
     int reverse(const AdjIO &io, hipStream_t st, std::string &err);
 
     // Building blocks of a driver loop (batch solve, server, adjoint).
-    // Empties the queue; from here on launches also end when *call (host memory the
-    // device reads) is set, and after ms_done as soon as a cell has finished.
-    int serve(const int32_t *call, double ms_done, hipStream_t st, std::string &err);
+    // Empties the queue; from here on launches also end when *call is set, and the
+    // slots that finish in them appear in fin_host [nslots] in turn (host memory
+    // that the device reads and writes).
+    int serve(const int32_t *call, int32_t *fin_host, hipStream_t st, std::string &err);
     int nslots() const { return s_.nslots; }
     int free_count() const { return n_free_; }
     // Occupied slots: admitted and not yet harvested.

@@ -49,7 +49,7 @@ struct PhaseClock {
 // Whether this workgroup puts its cell back and ends: the launch's time is up,
 // or (when cells wait on the host for slots, or for the form that holds FP64
 // factors) another workgroup found the queue empty; a server's launch also ends
-// when the host calls or has results to hand out.  Uniform; contains a barrier.
+// when the host calls.  Uniform; contains a barrier.
 template <int W>
 __device__ __forceinline__ bool time_up(const Slots &s, const IntegrateArgs &a, unsigned long long t0,
                                         StepLds<W> &L) {
@@ -58,13 +58,9 @@ __device__ __forceinline__ bool time_up(const Slots &s, const IntegrateArgs &a, 
         bool up = ran > a.ticks;
         if ((a.flags & kStopOnIdle) || ((a.flags & kDefer) && (L.cs.n_attempts & 7) == 0))   // not a load of every short attempt
             up |= __hip_atomic_load(&s.q->stop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == a.launch;
-        if (a.flags & kServe) {
-            // host memory is some 2 us away: not every attempt (of 50 us and more, or 20 us of a wave alone)
-            if (ran > s.q->ticks_call && (L.cs.n_attempts & (W == 1 ? 15 : 3)) == 0)
-                up |= __hip_atomic_load(s.q->call, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) != 0;
-            if (ran > s.q->ticks_done)
-                up |= __hip_atomic_load(&s.q->nfin, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > 0;
-        }
+        // host memory is some 2 us away: not every attempt (of 50 us and more, or 20 us of a wave alone)
+        if ((a.flags & kServe) && (L.cs.n_attempts & (W == 1 ? 15 : 3)) == 0 && ran > s.q->ticks_call)
+            up |= __hip_atomic_load(s.q->call, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) != 0;
         L.flag = up;
     }
     __syncthreads();

@@ -67,7 +67,7 @@ struct IntegrateArgs {
 enum {
     kStopOnIdle = 1,   // cells wait on the host: end as soon as a workgroup finds the queue empty
     kProf = 2,         // accumulate SlotQueue::ticks
-    kServe = 4,        // a server's: end for SlotQueue::call and for finished cells too
+    kServe = 4,        // a server's: end for SlotQueue::call too
     kDefer = 8         // (set by the launcher) the one-wave FP32-LU form that puts cells on FP64 factors back
 };
 

@@ -36,6 +36,7 @@ Server::~Server() {
     eng_.reset();
     if (d_in_) (void)hipFree(d_in_);
     if (call_) (void)hipHostFree(call_);
+    if (h_done_) (void)hipHostFree(h_done_);
     if (h_in_) (void)hipHostFree(h_in_);
     if (h_x_) (void)hipHostFree(h_x_);
     if (h_st_) (void)hipHostFree(h_st_);
@@ -86,10 +87,9 @@ int Server::start(int nslots, bool padded, std::string &err) {
     // h_slots_ and h_cells_ live inside the h_in_ allocation
     HIP_TRY(hipHostMalloc(reinterpret_cast<void **>(&call_), sizeof(int32_t), hipHostMallocDefault));
     *call_ = 0;
-    // how long finished cells may wait in a launch: 0.5 ms, some step attempts, per unit
-    // of check_every.  New requests, cancellations and the end of the server call
-    // the worker back at once.
-    rc = eng_->serve(call_, 0.5 * std::max(1, opt_.solve.check_every), st_, err);
+    HIP_TRY(hipHostMalloc(reinterpret_cast<void **>(&h_done_), n * sizeof(int32_t), hipHostMallocDefault));
+    std::fill(h_done_, h_done_ + n, -1);
+    rc = eng_->serve(call_, h_done_, st_, err);
     if (rc != ABDF_OK) return rc;
     owner_.assign(n, {nullptr, 0});
     th_ = std::thread([this] { run(); });
@@ -293,6 +293,30 @@ int Server::admit_pending(std::string &err) {
     return ABDF_OK;
 }
 
+// Waits for the running launch, and ends it for a request whose last cell has
+// finished, once it has run for check_every x 0.5 ms.  (Ended for every finished
+// cell, a server with thousands of cells of 500 species in slots did 793
+// cell-solves/s of 1209.)
+void Server::watch() {
+    const auto start = std::chrono::steady_clock::now();
+    const std::chrono::microseconds least(500 * std::max(1, opt_.solve.check_every));
+    const volatile int32_t *done = h_done_;
+    bool complete = false, called = false;
+    int seen = 0;
+    while (hipStreamQuery(st_) == hipErrorNotReady) {
+        for (; seen < eng_->nslots() && done[seen] >= 0; ++seen) {
+            Request *r = owner_[done[seen]].first.get();
+            if (r && r->last(r->done + ++r->ahead)) complete = true;
+        }
+        if (complete && !called && std::chrono::steady_clock::now() - start >= least) {
+            std::lock_guard<std::mutex> l(mu_);
+            call();
+            called = true;
+        }
+        std::this_thread::sleep_for(std::chrono::microseconds(50));
+    }
+}
+
 int Server::collect(std::string &err) {
     int nfin = 0;
     int rc = eng_->sync_counts(st_, nfin, err);
@@ -304,6 +328,7 @@ int Server::collect(std::string &err) {
     }
     t_last_ = t;
     if (nfin == 0) return ABDF_OK;
+    std::fill(h_done_, h_done_ + nfin, -1);
     HarvestArgs h{};
     h.count = nfin;
     h.x_out = d_x_;
@@ -332,7 +357,8 @@ int Server::collect(std::string &err) {
         }
         if (h_st_[i] != ABDF_CELL_OK) ++r->failed;
         ++r->done;
-        if (r->done == r->next && (r->next == r->n || r->cancelled)) complete(r.get());
+        r->ahead = 0;
+        if (r->last(r->done)) complete(r.get());
     }
     std::lock_guard<std::mutex> l(mu_);
     occupied_shared_ = occupied_;
@@ -396,6 +422,7 @@ void Server::run() {
             }
             rc = eng_->integrate(!pending_.empty(), st_, err);
             if (rc != ABDF_OK) break;
+            watch();
             rc = collect(err);
         }
     }

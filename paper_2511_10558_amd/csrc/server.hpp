@@ -50,13 +50,16 @@ class Server {
         long long next = 0;        // next cell to admit
         long long done = 0;        // cells finished
         long long failed = 0;
+        long long ahead = 0;       // cells finished in the running launch
         bool cancelled = false;
+        bool last(long long d) const { return d == next && (next == n || cancelled); }   // d done: no more to come
         double t_submit = 0.0, t_first_admit = -1.0;
     };
     static constexpr int kIn = 8;
 
     void run();
     int admit_pending(std::string &err);
+    void watch();
     int collect(std::string &err);
     void complete(Request *r);
     void call() { *static_cast<volatile int32_t *>(call_) = 1; }   // mu_ held
@@ -101,6 +104,7 @@ class Server {
     long long *h_cells_ = nullptr, *d_cells_ = nullptr;
     double *h_x_ = nullptr, *d_x_ = nullptr;          // [nslots][S]
     int32_t *h_st_ = nullptr, *d_st_ = nullptr;
+    int32_t *h_done_ = nullptr;                       // [nslots] slots as they finish in a launch, -1: none (SlotQueue::fin_host)
     abdf_cell_stats *h_stats_ = nullptr, *d_stats_ = nullptr;
 };
 
